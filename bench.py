@@ -33,10 +33,11 @@ HBM_PEAK_GBS = 8000.0
 # write w, the x sweep read u_k and w and write u_{k+1}, each once: 48 B.
 ALGO_BYTES_PER_CELL_ITERATION = 48.0
 # The bytes of each kernel class taken alone (the inputs it reads, the field it writes).
-ALGO_BYTES_PER_CELL = {"relations_y": 16, "solve_y": 24, "relations_x": 16, "solve_x": 24, "xrow": 24}
+ALGO_BYTES_PER_CELL = {"relations_y": 16, "solve_y": 24, "relations_x": 16, "solve_x": 24, "xrow": 24, "yline": 24}
 KERNEL_SOURCES = ["paper_1806_10550_amd/csrc/tf_kernels.hip", "paper_1806_10550_amd/csrc/tf_internal.h",
                   "paper_1806_10550_amd/csrc/tf_device.h", "paper_1806_10550_amd/csrc/tf_sweep.h",
-                  "paper_1806_10550_amd/csrc/tf_xrow.hip"]
+                  "paper_1806_10550_amd/csrc/tf_xrow.hip", "paper_1806_10550_amd/csrc/tf_line.h",
+                  "paper_1806_10550_amd/csrc/tf_line.hip"]
 def traffic_file(config="large8192"):
     return os.path.join(ROOT, "profiles", f"traffic_{config}.json")
 
@@ -94,8 +95,9 @@ def iteration_traffic(ncells, config="large8192"):
     if t.get("kernel_hash") != kernel_hash():
         return None
     ks = t.get("kernels", {})
-    per = {"relations_y": 1, "solve_y": 1, "chain": 1}
-    per.update({"xrow": 1} if "xrow" in ks else {"relations_x": 1, "solve_x": 1, "chain": 2})
+    parts = [["yline"] if "yline" in ks else ["relations_y", "solve_y", "chain"],
+             ["xrow"] if "xrow" in ks else ["relations_x", "solve_x", "chain"]]
+    per = {k: sum(k in p for p in parts) for p in parts for k in p}
     if any(k not in ks for k in per):
         return None
     return sum(n * (ks[k]["fetch_kib"] + ks[k]["write_kib"]) * 1024.0 * t.get("copy_scale", 1.0)
@@ -474,13 +476,12 @@ def main():
     ncells = n * n
     steps_per_s = args.steps / elapsed
 
-    # The roofline record covers the kernels of one Newton iteration (the six launches of the
-    # y and x sweeps) as a unit: 48 algorithmic bytes per cell per iteration (each sweep reads
+    # The roofline record covers the kernels of one Newton iteration (the launches of the y and
+    # x sweeps) as a unit: 48 algorithmic bytes per cell per iteration (each sweep reads
     # its two inputs and writes its output once) over their mean time per iteration from the
     # per-launch HIP events of the profiled run.
-    # the kernels of one iteration: the y sweep's three, then the x sweep's (one whole-row
-    # kernel, or three with the partitioned variant)
-    sweep = ["relations_y", "chain_y", "solve_y"] + (
+    # the kernels of one iteration: per sweep one whole-line kernel or the partitioned variant's three
+    sweep = (["yline"] if prof.get("yline", (0, 0))[1] else ["relations_y", "chain_y", "solve_y"]) + (
         ["xrow"] if prof.get("xrow", (0, 0))[1] else ["relations_x", "chain_x", "solve_x"])
     iter_kernel_s = sum(prof[k][0] for k in sweep) / 1e3 / total_iters
     achieved = ALGO_BYTES_PER_CELL_ITERATION * ncells / iter_kernel_s / 1e9

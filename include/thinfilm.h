@@ -127,10 +127,10 @@ tf_status tf_set_diagnostics(tf_grid *g, int mass_every_step);
  *   TF_XSWEEP_PARTITIONED  three kernels per sweep: segment relations of 64-cell tiles,
  *                          the interface chain of each row, then the segment solves
  *                          (any nx);
- *   TF_XSWEEP_ROW          one kernel: a workgroup holds whole rows, eliminates 16-cell
- *                          sub-segments per lane and couples them by a tree of merges in
- *                          LDS (4 <= nx <= 8192);
- *   TF_XSWEEP_AUTO         the row kernel when nx allows it (the default at tf_create).
+ *   TF_XSWEEP_ROW          one kernel: each row is held by one to eight waves, which eliminate
+ *                          sub-segments of 4 to 16 cells per lane and couple them by cyclic
+ *                          reduction across the lanes (4 <= nx <= 8192);
+ *   TF_XSWEEP_AUTO         the choice of tf_xsweep_choice (the default at tf_create).
  * TF_EINVAL for an unknown variant or TF_XSWEEP_ROW with nx > 8192. tf_get_xsweep returns
  * the variant in use (-1 for a NULL grid). The transposed row solves of tf_adjoint_step
  * follow the setting: TF_XSWEEP_ROW (with nx <= 4096) solves whole rows in one kernel,
@@ -353,8 +353,8 @@ int tf_autotune_choice(int length, int batch, int transposed);
  * too). TF_EINVAL for length or batch below 4. Grids (tf_create) and ensembles
  * (tf_ensemble_create, per film, with ny = the rows of all its films, since its x sweep is one
  * launch over all of them) take the variant tf_xsweep_choice(nx, ny) returns at creation: the
- * tuned entry of the nearest shape (log distance below 0.7), else the whole-row kernel when
- * the launch has at most 2048 rows; never the whole-row kernel for rows above 4096 cells.
+ * tuned entry of the nearest shape (log distance below 0.7), else the whole-row kernel; never
+ * the whole-row kernel for rows above 4096 cells.
  * Returns 0 (partitioned) or 1 (whole-row). */
 tf_status tf_autotune_xsweep(int length, int batch, const char *cache_path);
 int tf_xsweep_choice(int nx, int ny);

@@ -705,11 +705,9 @@ struct Scratch {
 } // namespace
 
 namespace tf {
-// x-sweep variant for ny rows of nx cells in one launch: the tuned entry with the nearest
-// shape, else the measured rule (the whole-row kernel while the launch has at most 2048
-// rows: with few rows the partitioned solver's three launches are latency bound, with many
-// its tile kernels stream faster); the whole-row kernel is only chosen where its 4-wave
-// workgroups hold the row (nx <= 4096).
+// x-sweep variant for ny rows of nx cells in one launch: the tuned entry with the nearest shape,
+// else the whole-row kernel (faster than the partitioned solver's three launches at every length and
+// number of rows measured, figures at xline_geom in tf_line.hip); it is only chosen for nx <= 4096.
 int xsweep_choice(int nx, int ny)
 {
     if (!xrow_supported(nx) || nx > XR_ROW4_MAX_NX) return 0;
@@ -723,7 +721,7 @@ int xsweep_choice(int nx, int ny)
         if (d < best_d) { best_d = d; v = kv.second.variant; }
     }
     if (v >= 0 && best_d < 0.7) return v;
-    return ny <= 2048 ? 1 : 0;
+    return 1;
 }
 } // namespace tf
 
@@ -1306,7 +1304,7 @@ tf_status tf_autotune_xsweep(int length, int batch, const char *cache_path)
     P.tiles_y = (batch + tf::TILE - 1) / tf::TILE;
     const tf::ChainParams C{batch, tf::seg_count(length), rel, chain, ext};
     auto run = [&](int v) -> hipError_t {
-        if (v == 1) return tf::launch_xrow(P, s);
+        if (v == 1) return tf::launch_line(1, P, s);
         tf::PassParams Q = P;
         Q.res = nullptr;
         hipError_t e = tf::launch_pass(1, false, Q, s);

@@ -35,8 +35,8 @@ tf_status fail(tf_status s, const std::string &msg)
         if (e_ != hipSuccess) return fail(TF_EDEVICE, std::string(#call) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-enum ProfKind { P_REL_Y, P_CHAIN_Y, P_SOLVE_Y, P_REL_X, P_CHAIN_X, P_SOLVE_X, P_RHS, P_MASS, P_XROW, P_NKIND };
-const char *kProfNames = "relations_y,chain_y,solve_y,relations_x,chain_x,solve_x,rhs_theta,mass,xrow";
+enum ProfKind { P_REL_Y, P_CHAIN_Y, P_SOLVE_Y, P_REL_X, P_CHAIN_X, P_SOLVE_X, P_RHS, P_MASS, P_XROW, P_YLINE, P_NKIND };
+const char *kProfNames = "relations_y,chain_y,solve_y,relations_x,chain_x,solve_x,rhs_theta,mass,xrow,yline";
 
 constexpr int RES_SLOTS = 4;
 constexpr int RES_STRIDE = tf::RES_SPREAD * tf::RES_WORDS; // words per reduction slot
@@ -191,6 +191,9 @@ tf::PassParams base_params(const tf_grid *g, double dt)
     return P;
 }
 
+// The y sweep takes whole columns wherever tf::yline_geom gives them.
+bool yline(const tf_grid *g) { return tf::yline_geom(g->nx, g->ny).W > 0; }
+
 // One ADI-Newton iteration: y sweep (relations, chain, solve) into w, x sweep into
 // u_kp1. The reduction record of slot `slot` receives max|G| (y relations pass) and
 // max|v/u_k| and flags (x solve pass); slot (slot+2)%RES_SLOTS is cleared for later.
@@ -211,12 +214,19 @@ tf_status enqueue_iteration(tf_grid *g, const double *bnp, const double *uk, dou
     P.res_clear = clr;
     P.tiles_x = (g->nx + tf::TILE - 1) / tf::TILE;
     P.tiles_y = g->Py;
-    if ((st = timed(g, P_REL_Y, [&] { return tf::launch_pass(0, false, P, g->stream); })) != TF_OK) return st;
-    tf::ChainParams C{g->nx, g->Py, g->rel, g->chain, g->ext};
-    if ((st = timed(g, P_CHAIN_Y, [&] { return tf::launch_chain(C, g->stream); })) != TF_OK) return st;
+    if (yline(g)) {
+        // whole columns in one kernel
+        if ((st = timed(g, P_YLINE, [&] { return tf::launch_line(0, P, g->stream); })) != TF_OK) return st;
+    } else {
+        if ((st = timed(g, P_REL_Y, [&] { return tf::launch_pass(0, false, P, g->stream); })) != TF_OK) return st;
+        tf::ChainParams C{g->nx, g->Py, g->rel, g->chain, g->ext};
+        if ((st = timed(g, P_CHAIN_Y, [&] { return tf::launch_chain(C, g->stream); })) != TF_OK) return st;
+        P.res = nullptr;
+        P.res_clear = nullptr;
+        if ((st = timed(g, P_SOLVE_Y, [&] { return tf::launch_pass(0, true, P, g->stream); })) != TF_OK) return st;
+    }
     P.res = nullptr;
     P.res_clear = nullptr;
-    if ((st = timed(g, P_SOLVE_Y, [&] { return tf::launch_pass(0, true, P, g->stream); })) != TF_OK) return st;
     // x sweep: (I + c J_x) v = w, u_{k+1} = u_k + v
     P.in2 = g->w;
     P.out = ukp1;
@@ -226,7 +236,7 @@ tf_status enqueue_iteration(tf_grid *g, const double *bnp, const double *uk, dou
         // one whole-row kernel: assembly, elimination, in-row tree, back-substitution, update
         P.res = res;
         P.mass = diag ? g->mpart : nullptr;
-        return timed(g, P_XROW, [&] { return tf::launch_xrow(P, g->stream); });
+        return timed(g, P_XROW, [&] { return tf::launch_line(1, P, g->stream); });
     }
     if ((st = timed(g, P_REL_X, [&] { return tf::launch_pass(1, false, P, g->stream); })) != TF_OK) return st;
     tf::ChainParams Cx{g->ny, g->Px, g->rel, g->chain, g->ext};
@@ -295,10 +305,11 @@ tf_status mass_of(tf_grid *g, const double *u, double *mass, double *hmin, bool 
 }
 
 int x_tiles(const tf_grid *g) { return g->Px * ((g->ny + tf::TILE - 1) / tf::TILE); }
-// Mass records the x sweep leaves (one per x-solve tile or per whole-row workgroup).
+// Mass records the x sweep leaves (one per x-solve tile or per wave of the whole-row kernel).
 int mass_records(const tf_grid *g)
 {
-    return g->xsweep == TF_XSWEEP_ROW ? tf::xrow_blocks(g->nx, g->ny) : x_tiles(g);
+    if (g->xsweep == TF_XSWEEP_ROW) return g->ny * tf::xline_geom(g->nx).W;
+    return x_tiles(g);
 }
 
 // Mass and minimum of the last iterate from the records its x solve left per tile (Sec.
@@ -487,7 +498,7 @@ tf_status tf_create(int nx, int ny, double ds, void *stream, tf_grid **out)
               && hipMalloc(&g->ext, lines_seg * tf::NEXT * sizeof(double)) == hipSuccess
               && hipMalloc(&g->chain, lines_seg * tf::NCHAIN * sizeof(double)) == hipSuccess
               && hipMalloc(&g->partials, 4096 * 4 * sizeof(double)) == hipSuccess
-              && hipMalloc(&g->mpart, (size_t)std::max(x_tiles(g), tf::xrow_supported(nx) ? tf::xrow_blocks(nx, ny) : 0)
+              && hipMalloc(&g->mpart, (size_t)std::max(x_tiles(g), ny * tf::xline_geom(nx).W)
                                           * 4 * sizeof(double)) == hipSuccess
               && hipMalloc(&g->mout, 2 * sizeof(double)) == hipSuccess
               && hipMalloc(&g->res, RES_SLOTS * RES_STRIDE * sizeof(unsigned long long)) == hipSuccess

@@ -408,6 +408,23 @@ __device__ __forceinline__ void comp_add(double &s, double &c, double s2, double
     c = cc;
 }
 
+// Value of the next (lane + 1) / previous (lane - 1) lane of the wave by whole-wave DPP
+// shifts (VALU moves, no LDS permute); the edge lanes get 0 (the y sweep replaces what
+// they would need by the tile-edge correction of b^n).
+__device__ __forceinline__ double dpp_shift(double v, int ctrl)
+{
+    // bound_ctrl set: a lane whose source lies outside the wave reads 0, so no "old" value
+    // has to be materialised first
+    const long long b = __double_as_longlong(v);
+    const int lo = ctrl == 0x130 ? __builtin_amdgcn_mov_dpp((int)b, 0x130, 0xf, 0xf, true)
+                                 : __builtin_amdgcn_mov_dpp((int)b, 0x138, 0xf, 0xf, true);
+    const int hi = ctrl == 0x130 ? __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x130, 0xf, 0xf, true)
+                                 : __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x138, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+__device__ __forceinline__ double lane_next(double v) { return dpp_shift(v, 0x130); } // wave_shl:1
+__device__ __forceinline__ double lane_prev(double v) { return dpp_shift(v, 0x138); } // wave_shr:1
+
 __device__ __forceinline__ double wave_max(double v)
 {
 #pragma unroll

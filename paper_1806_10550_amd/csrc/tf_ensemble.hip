@@ -42,11 +42,11 @@ struct tf_ensemble {
     tf_scheme S{};
     std::vector<tf::FilmDesc> desc;
     long long ncells = 0, nrec = 0;
-    int ny_items = 0, nx_items = 0, ncy_items = 0, ncx_items = 0, nxr_items = 0;
+    // work lists of one iteration (build_items), each a range of d_items
+    struct Range { size_t off = 0; int n = 0; };
+    Range ty, tx, cy, cx, bnt, yl[tf::N_YL], xl[tf::N_XL];
     tf::FilmDesc *d_desc = nullptr;
     tf::FilmState *d_state = nullptr, *h_state = nullptr;
-    // [y tiles | x tiles | y chain blocks | x chain blocks | whole-row blocks]; the x tiles and
-    // x chain blocks cover the films whose x sweep is partitioned, the row blocks the others
     int *d_items = nullptr;
     std::vector<int> xsweep;  // per film: 1 = whole-row x sweep, 0 = partitioned
     int *d_active = nullptr, *h_active = nullptr;
@@ -61,7 +61,7 @@ struct tf_ensemble {
 
 namespace {
 
-tf::EnsParams params(const tf_ensemble *e, int which)
+tf::EnsParams params(const tf_ensemble *e, const tf_ensemble::Range &r)
 {
     tf::EnsParams p{};
     p.desc = e->d_desc;
@@ -75,15 +75,8 @@ tf::EnsParams params(const tf_ensemble *e, int which)
     p.chain = e->chain;
     p.bn = e->bn;
     p.theta = e->S.theta;
-    const int off_y = 0, off_x = 3 * e->ny_items, off_cy = off_x + 3 * e->nx_items, off_cx = off_cy + 2 * e->ncy_items;
-    const int off_xr = off_cx + 2 * e->ncx_items;
-    switch (which) {
-    case 0: p.items = e->d_items + off_y; p.nitems = e->ny_items; break;
-    case 1: p.items = e->d_items + off_x; p.nitems = e->nx_items; break;
-    case 2: p.items = e->d_items + off_cy; p.nitems = e->ncy_items; break;
-    case 3: p.items = e->d_items + off_cx; p.nitems = e->ncx_items; break;
-    default: p.items = e->d_items + off_xr; p.nitems = e->nxr_items; break;
-    }
+    p.items = e->d_items + r.off;
+    p.nitems = r.n;
     return p;
 }
 
@@ -91,16 +84,21 @@ tf_status enqueue_iteration(tf_ensemble *e)
 {
     const tf::EnsScheme S{e->S.theta, e->S.tol, e->S.dt_min, e->S.dt_max, e->S.dt_shrink, e->S.dt_grow,
                           e->S.max_newton, e->S.grow_after, e->S.adaptive};
-    if (e->S.theta < 1.0) TF_EHIP(tf::launch_bn_ens(params(e, 0), e->stream));
-    TF_EHIP(tf::launch_pass_ens(0, false, e->km, params(e, 0), e->stream));
-    TF_EHIP(tf::launch_chain_ens(params(e, 2), 0, e->stream));
-    TF_EHIP(tf::launch_pass_ens(0, true, e->km, params(e, 0), e->stream));
-    if (e->nx_items > 0) {
-        TF_EHIP(tf::launch_pass_ens(1, false, e->km, params(e, 1), e->stream));
-        TF_EHIP(tf::launch_chain_ens(params(e, 3), 1, e->stream));
-        TF_EHIP(tf::launch_pass_ens(1, true, e->km, params(e, 1), e->stream));
+    if (e->S.theta < 1.0) TF_EHIP(tf::launch_bn_ens(params(e, e->bnt), e->stream));
+    if (e->ty.n > 0) {
+        TF_EHIP(tf::launch_pass_ens(0, false, e->km, params(e, e->ty), e->stream));
+        TF_EHIP(tf::launch_chain_ens(params(e, e->cy), 0, e->stream));
+        TF_EHIP(tf::launch_pass_ens(0, true, e->km, params(e, e->ty), e->stream));
     }
-    if (e->nxr_items > 0) TF_EHIP(tf::launch_xrow_ens(e->km, params(e, 4), e->stream));
+    for (int c = 0; c < tf::N_YL; ++c)
+        if (e->yl[c].n > 0) TF_EHIP(tf::launch_line_ens(0, tf::YL_CLASSES[c], e->km, params(e, e->yl[c]), e->stream));
+    if (e->tx.n > 0) {
+        TF_EHIP(tf::launch_pass_ens(1, false, e->km, params(e, e->tx), e->stream));
+        TF_EHIP(tf::launch_chain_ens(params(e, e->cx), 1, e->stream));
+        TF_EHIP(tf::launch_pass_ens(1, true, e->km, params(e, e->tx), e->stream));
+    }
+    for (int c = 0; c < tf::N_XL; ++c)
+        if (e->xl[c].n > 0) TF_EHIP(tf::launch_line_ens(1, tf::XL_CLASSES[c], e->km, params(e, e->xl[c]), e->stream));
     TF_EHIP(tf::launch_ens_control(e->d_state, e->nfilms, S, e->d_active, e->stream));
     return TF_OK;
 }
@@ -142,37 +140,54 @@ tf_status set_all_models(tf_ensemble *e, const tf::Model &M, int km)
     return TF_OK;
 }
 
-// Work lists of one iteration (see tf_ensemble::d_items); the x sweep of film f is
-// whole-row when xsweep[f] == 1.
+int line_class(const tf::LineGeom &g, const tf::LineGeom *classes, int n)
+{
+    for (int c = 0; c < n; ++c)
+        if (classes[c].cpl == g.cpl && classes[c].W == g.W) return c;
+    return -1;
+}
+
+// Work lists of one iteration: the y sweep of a film is whole-column where tf::yline_geom gives a
+// geometry (as for a single film), its x sweep whole-row when xsweep[f] == 1; the others take tiles
+// and chain blocks. The b^n list covers every film's y tiles.
 void build_items(tf_ensemble *e, std::vector<int> &items)
 {
-    std::vector<int> items_y, items_x, items_cy, items_cx, items_xr;
+    std::vector<int> ty, tx, cy, cx, bnt, yl[tf::N_YL], xl[tf::N_XL];
     for (int f = 0; f < e->nfilms; ++f) {
         const tf::FilmDesc &d = e->desc[f];
-        const int tyx = (d.nx + tf::TILE - 1) / tf::TILE;
-        for (int ty = 0; ty < d.Py; ++ty)
-            for (int tx = 0; tx < tyx; ++tx) { items_y.push_back(f); items_y.push_back(tx); items_y.push_back(ty); }
-        for (int lb = 0; lb < (d.nx + 63) / 64; ++lb) { items_cy.push_back(f); items_cy.push_back(lb); }
-        if (e->xsweep[f] == 1) {
-            for (int rb = 0; rb < tf::xrow_blocks(d.nx, d.ny); ++rb) { items_xr.push_back(f); items_xr.push_back(rb); }
+        const int yc = line_class(tf::yline_geom(d.nx, d.ny), tf::YL_CLASSES, tf::N_YL);
+        const int xc = e->xsweep[f] == 1 ? line_class(tf::xline_geom(d.nx), tf::XL_CLASSES, tf::N_XL) : -1;
+        const int tyx = (d.nx + tf::TILE - 1) / tf::TILE, txy = (d.ny + tf::TILE - 1) / tf::TILE;
+        for (int j = 0; j < d.Py; ++j)
+            for (int i = 0; i < tyx; ++i) {
+                bnt.insert(bnt.end(), {f, i, j});
+                if (yc < 0) ty.insert(ty.end(), {f, i, j});
+            }
+        if (yc >= 0)
+            for (int b = 0; b < (d.nx + tf::LN_COLS - 1) / tf::LN_COLS; ++b) yl[yc].insert(yl[yc].end(), {f, b});
+        else
+            for (int b = 0; b < (d.nx + 63) / 64; ++b) cy.insert(cy.end(), {f, b});
+        if (xc >= 0) {
+            for (int j = 0; j < d.ny; ++j) xl[xc].insert(xl[xc].end(), {f, j});
         } else {
-            const int txy = (d.ny + tf::TILE - 1) / tf::TILE;
-            for (int ty = 0; ty < txy; ++ty)
-                for (int tx = 0; tx < d.Px; ++tx) { items_x.push_back(f); items_x.push_back(tx); items_x.push_back(ty); }
-            for (int lb = 0; lb < (d.ny + 63) / 64; ++lb) { items_cx.push_back(f); items_cx.push_back(lb); }
+            for (int j = 0; j < txy; ++j)
+                for (int i = 0; i < d.Px; ++i) tx.insert(tx.end(), {f, i, j});
+            for (int b = 0; b < (d.ny + 63) / 64; ++b) cx.insert(cx.end(), {f, b});
         }
     }
-    e->ny_items = (int)items_y.size() / 3;
-    e->nx_items = (int)items_x.size() / 3;
-    e->ncy_items = (int)items_cy.size() / 2;
-    e->ncx_items = (int)items_cx.size() / 2;
-    e->nxr_items = (int)items_xr.size() / 2;
     items.clear();
-    items.insert(items.end(), items_y.begin(), items_y.end());
-    items.insert(items.end(), items_x.begin(), items_x.end());
-    items.insert(items.end(), items_cy.begin(), items_cy.end());
-    items.insert(items.end(), items_cx.begin(), items_cx.end());
-    items.insert(items.end(), items_xr.begin(), items_xr.end());
+    auto put = [&](tf_ensemble::Range &r, const std::vector<int> &v, int per) {
+        r.off = items.size();
+        r.n = (int)(v.size() / per);
+        items.insert(items.end(), v.begin(), v.end());
+    };
+    put(e->ty, ty, 3);
+    put(e->tx, tx, 3);
+    put(e->bnt, bnt, 3);
+    put(e->cy, cy, 2);
+    put(e->cx, cx, 2);
+    for (int c = 0; c < tf::N_YL; ++c) put(e->yl[c], yl[c], 2);
+    for (int c = 0; c < tf::N_XL; ++c) put(e->xl[c], xl[c], 2);
 }
 
 // Rows of all films: the x sweep of an ensemble is one launch over every film's rows, so the
@@ -189,9 +204,9 @@ size_t max_items(const tf_ensemble *e)
 {
     size_t n = 0;
     for (const auto &d : e->desc) {
-        n += 3 * (size_t)d.Py * ((d.nx + tf::TILE - 1) / tf::TILE) + 2 * (size_t)((d.nx + 63) / 64);
-        n += std::max(3 * (size_t)((d.ny + tf::TILE - 1) / tf::TILE) * d.Px + 2 * (size_t)((d.ny + 63) / 64),
-                      tf::xrow_supported(d.nx) ? 2 * (size_t)tf::xrow_blocks(d.nx, d.ny) : 0);
+        const size_t yt = (size_t)d.Py * ((d.nx + tf::TILE - 1) / tf::TILE);
+        n += 6 * yt + 2 * (size_t)((d.nx + tf::LN_COLS - 1) / tf::LN_COLS);
+        n += 3 * (size_t)((d.ny + tf::TILE - 1) / tf::TILE) * d.Px + 2 * (size_t)((d.ny + 63) / 64) + 2 * (size_t)d.ny;
     }
     return n;
 }

@@ -75,6 +75,41 @@ __host__ __device__ inline XRowGeom xrow_geom(int nx)
     return g;
 }
 
+// Whole lines across the lanes of one or several waves (tf_line.hip): LN_CPL consecutive positions
+// per lane (4, 8 or 16), W waves per line, right-aligned: slot s (64 wave + lane) owns the
+// positions w = CPL s + k, cell q = w - sh with sh = 64 W CPL - n < 64 CPL; positions before the
+// line (w < sh, in the first wave) hold copies of its first cells and are decoupled from it.
+constexpr int LN_MAXW = 8;                    // waves of the longest line
+// LDS offset of position w (-2 <= w <= 64 W CPL + 1) in a line's row: one padding double per lane,
+// so that lanes reading in step (stride CPL + 1) hit distinct banks.
+template <int CPL>
+__host__ __device__ constexpr int ln_at(int w) { return w + 3 + (w >= 0 ? w / CPL : -1); }
+template <int CPL>
+__host__ __device__ constexpr int ln_off(int t) { return t + (t >= 0 ? t / CPL : -1); } // of a lane's block
+constexpr int LN_XS = 66;                     // exchange slots of a wave: its lanes and two outer records
+constexpr int LN_XCH = 10 * LN_XS;            // doubles of one wave's exchange records
+constexpr int LN_BND = 40;                    // doubles per wave shared by the waves of a line
+__host__ __device__ constexpr int ln_row(int cpl, int W) { return 64 * W * (cpl + 1) + 8; }
+// per wave: the exchange records, then the solution of its positions
+__host__ __device__ constexpr int ln_priv(int cpl) { return 64 * (cpl + 1) > LN_XCH ? 64 * (cpl + 1) : LN_XCH; }
+__host__ __device__ constexpr int ln_row2(int cpl, int W)
+{
+    return ln_row(cpl, W) > W * ln_priv(cpl) ? ln_row(cpl, W) : W * ln_priv(cpl);
+}
+// y sweep: a workgroup holds LN_COLS neighbouring columns and the two columns on each side in one
+// LDS tile of LN_UC columns; position w of column cc at lny_at(w) + cc.
+constexpr int LN_COLS = 4, LN_UC = LN_COLS + 4;
+template <int CPL>
+__host__ __device__ constexpr int lny_at(int w) { return LN_UC * (w + 2) + (w >= 0 ? w / CPL : -1) + 1; }
+template <int CPL>
+__host__ __device__ constexpr int lny_off(int t) { return LN_UC * t + (t >= 0 ? t / CPL : -1); }
+__host__ __device__ constexpr int lny_u(int cpl, int W) { return LN_UC * (64 * W * cpl + 4) + 64 * W + 4; }
+__host__ __device__ constexpr int lny_u2(int cpl, int W)
+{
+    const int b = LN_COLS * ln_row(cpl, W), v = LN_COLS * W * ln_priv(cpl), u = lny_u(cpl, W);
+    return u > b ? (u > v ? u : v) : (b > v ? b : v);
+}
+
 // Segments of a line of n >= 2 cells: TILE cells each, except that a last segment of
 // a single cell borrows one from its neighbour (every segment has >= 2 cells).
 __host__ __device__ inline int seg_count(int n) { return (n + TILE - 1) / TILE; }
@@ -207,11 +242,20 @@ enum ResultFlag { FLAG_NONPOS = 1, FLAG_NAN = 2 };
 hipError_t launch_flux_divergence_f1(int nx, int ny, double ids, double ids2, const Model &M, const double *u,
                                      double *out, hipStream_t s);
 hipError_t launch_pass(int dir, bool solve, const PassParams &p, hipStream_t s);
-// Whole-row x sweep: reads u (u_k) and in2 (w), writes out (u_{k+1}), the reduction record
-// (res: max|v/u_k|, flags) and, when mass is set, one mass record per workgroup.
 bool xrow_supported(int nx);
-int xrow_blocks(int nx, int ny);           // workgroups of one launch (= mass records)
-hipError_t launch_xrow(const PassParams &p, hipStream_t s);
+// Whole-line sweeps (tf_line.hip): dir 0 does the whole y sweep, reading u (u_k) and in2 (b^n) and
+// writing out (w), with max|G| in res; dir 1 the whole x sweep like launch_xrow, one mass record per
+// wave. Geometry of a line of n cells (W = 0: not supported).
+struct LineGeom {
+    int cpl, W; // positions per lane, waves per line
+};
+LineGeom xline_geom(int nx);
+LineGeom yline_geom(int nx, int ny);
+// the classes an ensemble's films fall into (rows of at most XR_ROW4_MAX_NX cells)
+constexpr LineGeom YL_CLASSES[] = {{4, 1}, {8, 1}, {16, 1}, {16, 2}};
+constexpr LineGeom XL_CLASSES[] = {{4, 1}, {8, 1}, {16, 1}, {16, 2}, {16, 3}, {16, 4}};
+constexpr int N_YL = 4, N_XL = 6;
+hipError_t launch_line(int dir, const PassParams &p, hipStream_t s);
 // Stored-band solves of whole lines (4 ..= XR_ROW4_MAX_NX cells) in one kernel: pm true
 // position-major (plain or transposed; mode 0 out = x, mode 1 out += x with the maxima in
 // red[0..1]), pm false line-major (transposed, mode 0 only). stop (nullable): a device word;
@@ -223,9 +267,9 @@ hipError_t launch_sbline(bool trans, bool pm, int mode, int nl, int np, const do
 // x-sweep variant for a film of nx x ny cells (0: partitioned, 1: whole-row): the autotuned
 // choice for the nearest shape, else the built-in rule (tf_adjoint.hip).
 int xsweep_choice(int nx, int ny);
-// Whole-row x sweep over the ensemble's row films (items: (film, row block); every such film
-// has nx <= XR_ROW4_MAX_NX); km: the KernelModel every film shares.
-hipError_t launch_xrow_ens(int km, const EnsParams &e, hipStream_t s);
+// The same over an ensemble's films of one geometry class (items: (film, block): four columns or
+// one row); km: the KernelModel every film shares.
+hipError_t launch_line_ens(int dir, const LineGeom &g, int km, const EnsParams &e, hipStream_t s);
 hipError_t launch_model_coeffs(const Model &M, const double *h, int n, double *out, hipStream_t s);
 hipError_t launch_chain(const ChainParams &c, hipStream_t s);
 hipError_t launch_flux_divergence(int nx, int ny, double ids, double ids2, const Model &M,

@@ -46,23 +46,6 @@ namespace tf {
 // lane shuffles; the fluxes through the two faces on the tile's x edges are formed once per
 // position before the sweeps and enter the b^n of lanes 0 and 63.
 // ------------------------------------------------------------------------------------
-// Value of the next (lane + 1) / previous (lane - 1) lane of the wave by whole-wave DPP
-// shifts (VALU moves, no LDS permute); the edge lanes get 0 (the y sweep replaces what
-// they would need by the tile-edge correction of b^n).
-__device__ __forceinline__ double dpp_shift(double v, int ctrl)
-{
-    // bound_ctrl set: a lane whose source lies outside the wave reads 0, so no "old" value
-    // has to be materialised first
-    const long long b = __double_as_longlong(v);
-    const int lo = ctrl == 0x130 ? __builtin_amdgcn_mov_dpp((int)b, 0x130, 0xf, 0xf, true)
-                                 : __builtin_amdgcn_mov_dpp((int)b, 0x138, 0xf, 0xf, true);
-    const int hi = ctrl == 0x130 ? __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x130, 0xf, 0xf, true)
-                                 : __builtin_amdgcn_mov_dpp((int)(b >> 32), 0x138, 0xf, 0xf, true);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-__device__ __forceinline__ double lane_next(double v) { return dpp_shift(v, 0x130); } // wave_shl:1
-__device__ __forceinline__ double lane_prev(double v) { return dpp_shift(v, 0x138); } // wave_shr:1
-
 // Cell quantities at (line l, position q) of the LDS u tile.
 template <int DIR, int KM>
 __device__ __forceinline__ CellS cell_s(const double *sU, const PassParams &p, int l, int q)
@@ -530,24 +513,7 @@ __global__ void TF_PASS_ATTR k_pass_ens(EnsParams e)
     const int f = e.items[3 * t], tx = e.items[3 * t + 1], ty = e.items[3 * t + 2];
     FilmState *s = e.state + f;
     if (!s->active) return;
-    const FilmDesc d = e.desc[f];
-    double *B[3] = {e.buf0, e.buf1, e.buf2};
-    PassParams p{};
-    p.nx = d.nx;
-    p.ny = d.ny;
-    p.ids2 = 1.0 / (d.ds * d.ds);
-    p.f0s = p.ids2 * d.M.cap;
-    p.ka = 0.5 * e.theta * s->dt * p.ids2;
-    p.K0 = 3.0 * p.ka * p.ids2 * d.M.cap;
-    p.K1 = p.ka * d.M.Dn;
-    p.M = d.M;
-    p.u = B[s->it] + d.off;
-    p.in2 = DIR == 0 ? (e.theta < 1.0 ? e.bn : B[s->cur]) + d.off : e.w + d.off;
-    p.out = DIR == 0 ? e.w + d.off : B[s->nxt] + d.off;
-    p.rel = e.rel + d.roff * NREL;
-    p.ext = e.ext + d.roff * NEXT;
-    p.res = s->red;
-    p.res_spread = ENS_RES_SPREAD;
+    const PassParams p = ens_pass_params(e, e.desc[f], s, DIR);
     tile_body<DIR, SOLVE, KM>(p, tx, ty);
 }
 

@@ -78,4 +78,28 @@ __device__ __forceinline__ FaceS face_s(const CellS &L, const CellS &R, bool int
     return f;
 }
 
+// Parameters of one sweep pass of film f of an ensemble (dir 0: y sweep, 1: x sweep) from the
+// device tables.
+__device__ __forceinline__ PassParams ens_pass_params(const EnsParams &e, const FilmDesc &d, FilmState *s, int dir)
+{
+    double *B[3] = {e.buf0, e.buf1, e.buf2};
+    PassParams p{};
+    p.nx = d.nx;
+    p.ny = d.ny;
+    p.ids2 = 1.0 / (d.ds * d.ds);
+    p.f0s = p.ids2 * d.M.cap;
+    p.ka = 0.5 * e.theta * s->dt * p.ids2;
+    p.K0 = 3.0 * p.ka * p.ids2 * d.M.cap;
+    p.K1 = p.ka * d.M.Dn;
+    p.M = d.M;
+    p.u = B[s->it] + d.off;
+    p.in2 = dir == 0 ? (e.theta < 1.0 ? e.bn : B[s->cur]) + d.off : e.w + d.off;
+    p.out = dir == 0 ? e.w + d.off : B[s->nxt] + d.off;
+    p.rel = e.rel + d.roff * NREL;
+    p.ext = e.ext + d.roff * NEXT;
+    p.res = s->red;
+    p.res_spread = ENS_RES_SPREAD;
+    return p;
+}
+
 } // namespace tf

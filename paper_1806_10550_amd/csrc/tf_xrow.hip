@@ -20,51 +20,9 @@
 //            mass diagnostic of u_{k+1} in one coalesced store loop.
 // No band, factor or interface record goes to HBM: 24 algorithmic bytes per cell (u_k is
 // read twice, the second time for the update, mostly from L2).
-#include "tf_sweep.h"
+#include "tf_line.h"
 
 namespace tf {
-
-bool xrow_supported(int nx)
-{
-    if (nx < 4 || nx > XR_MAX_NX) return false;
-    const XRowGeom g = xrow_geom(nx);
-    return g.W <= g.waves && g.R * (g.pu + g.p2) <= xr_lds(g.waves);
-}
-
-// Bands of row p of I + c J_x from the faces p-1/2 (fm) and p+1/2 (fp).
-struct Band {
-    double a, b, c, d, e;
-};
-__device__ __forceinline__ Band xr_band(const FaceS &fm, const FaceS &fp)
-{
-    Band B;
-    B.a = fm.kA;
-    B.b = __builtin_fma(-3.0, fm.kA, -fp.kA) - fm.P;
-    B.c = __builtin_fma(3.0, fp.kA + fm.kA, 1.0) + (fp.P - fm.Q);
-    B.d = __builtin_fma(-3.0, fp.kA, fp.Q) - fm.kA;
-    B.e = fp.kA;
-    return B;
-}
-// Ghost columns folded back (even reflection of the perturbation) at the row ends.
-__device__ __forceinline__ void fold_left(Band &B, int pos) // pos: 0 or 1
-{
-    if (pos == 0) { B.c += B.b; B.d += B.a; B.b = 0.0; B.a = 0.0; }
-    else { B.b += B.a; B.a = 0.0; }
-}
-__device__ __forceinline__ void fold_right(Band &B, int pos) // pos: nx-1 (0) or nx-2 (1)
-{
-    if (pos == 0) { B.c += B.d; B.b += B.e; B.d = 0.0; B.e = 0.0; }
-    else { B.d += B.e; B.e = 0.0; }
-}
-
-// Orders this wave's LDS writes before its later LDS reads by other lanes of the same wave:
-// the wave's LDS operations complete in issue order once the counter drains, and the empty
-// asm statement keeps the compiler from moving memory accesses across the point.
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f); // lgkmcnt(0)
-    __asm__ volatile("" ::: "memory");
-}
 
 // ---- record algebra of the row tree ---------------------------------------------------
 // A block [a, e] of sub-segments has the record
@@ -150,29 +108,6 @@ __device__ __forceinline__ void rec_split(double *rec, int S, int a, int c)
     rec[1 * S + c] = bm1;
     rec[2 * S + c] = to0;
     rec[3 * S + c] = to1;
-}
-
-// LU step at position k of a lane's sub-segment with the outer unknowns l1 = x_{p0-2},
-// l2 = x_{p0-1} kept symbolic (z: constant part, ph: coefficient of l1, ps: of l2); the
-// factors of every position stay in the arrays for the back-substitution.
-template <int CPL>
-__device__ __forceinline__ void xr_elim(int k, const Band &B, double rhs, double (&fa)[CPL], double (&fb)[CPL],
-                                        double (&fz)[CPL], double (&fph)[CPL], double (&fps)[CPL])
-{
-    const double al2 = k >= 2 ? fa[k - 2] : 0.0, be2 = k >= 2 ? fb[k - 2] : 0.0;
-    const double al1 = k >= 1 ? fa[k - 1] : 0.0, be1 = k >= 1 ? fb[k - 1] : 0.0;
-    const double z2 = k >= 2 ? fz[k - 2] : 0.0, z1 = k >= 1 ? fz[k - 1] : 0.0;
-    // rows p0-2 and p0-1 stand for the outer unknowns l1 (ph = 1) and l2 (ps = 1)
-    const double ph2 = k >= 2 ? fph[k - 2] : (k == 0 ? 1.0 : 0.0), ph1 = k >= 1 ? fph[k - 1] : 0.0;
-    const double ps2 = k >= 2 ? fps[k - 2] : (k == 1 ? 1.0 : 0.0), ps1 = k >= 1 ? fps[k - 1] : 1.0;
-    const double gam = B.b - B.a * al2;
-    const double mu = B.c - B.a * be2 - gam * al1;
-    const double rm = rcp_pivot(mu);
-    fa[k] = (B.d - gam * be1) * rm;
-    fb[k] = B.e * rm;
-    fz[k] = (rhs - B.a * z2 - gam * z1) * rm;
-    fph[k] = (-B.a * ph2 - gam * ph1) * rm;
-    fps[k] = (-B.a * ps2 - gam * ps1) * rm;
 }
 
 // The relation record of slot s from the factors of its sub-segment (Rel layout, field f at
@@ -270,252 +205,6 @@ __device__ __forceinline__ void xr_backsub(const double *rec, int S, int s, doub
         x2 = x1;
         x1 = v;
     }
-}
-
-// ---- the kernel body -------------------------------------------------------------------
-// Lane s of a row owns the XR_CPL positions p0 + k, p0 = nx - XR_CPL (S - s), k < XR_CPL.
-// Positions before the row (only in lane 0, when XR_CPL does not divide nx) are identity
-// rows with a zero right-hand side: the ghost folds at the left end leave the first real
-// row without a coupling to them, so they solve to zero and change nothing. Every lane
-// thus runs the same fixed-length loop; the row ends fall on lanes whose p0 <= 1 (left)
-// and on positions XR_CPL-2, XR_CPL-1 of lane S-1 (right).
-template <int KM>
-__device__ __forceinline__ void xrow_body(const PassParams &p, const XRowGeom &g, int rowblock, double *lds)
-{
-    constexpr int CPL = XR_CPL;
-    const int nx = p.nx, ny = p.ny;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int rg = wave / g.W;                       // row group of this wave (uniform)
-    const int s = (wave - rg * g.W) * 64 + lane;     // slot (sub-segment) of this lane in its row
-    const int nthr = 64 * g.W;                       // threads of a row group
-    const int tr = s;                                // thread index within the row group
-    const int j = rowblock * g.R + rg;               // grid row of this row group
-    const bool row_ok = rg < g.R && j < ny;
-    double *const sU = lds + (size_t)rg * (g.pu + g.p2);
-    double *const sX = sU + g.pu;                    // u_N + u_S, then the tree
-    const double ka = p.ka;
-    const int S = g.S;
-    const int sh = CPL * S - nx;                     // staged index w = q + sh
-
-    // ---- stage u(j) at w = -2 .. 16 S + 1 (two ghost cells each side) and u(j-1) + u(j+1)
-    // at w = -1 .. 16 S (one); positions before lane 0's ghosts hold the first ghost's value.
-    // Every global load of a thread is issued before its first LDS store.
-    if (row_ok) {
-        const double *uc = p.u + (size_t)j * nx;
-        const double *un = p.u + (size_t)crefl(j - 1, ny) * nx;
-        const double *us = p.u + (size_t)crefl(j + 1, ny) * nx;
-        double vu[XR_STAGE], vx[XR_STAGE];
-#pragma unroll
-        for (int k = 0; k < XR_STAGE; ++k) {
-            const int i = tr + k * nthr;            // w = i - 2 (u row), i - 1 (X row)
-            if (i < CPL * S + 4) vu[k] = uc[crefl(max(i - 2 - sh, -2), nx)];
-            if (i < CPL * S + 2) {
-                const int c = crefl(max(i - 1 - sh, -1), nx);
-                vx[k] = us[c] + un[c];
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < XR_STAGE; ++k) {
-            const int i = tr + k * nthr;
-            if (i < CPL * S + 4) sU[xr_at(i - 2)] = vu[k];
-            if (i < CPL * S + 2) sX[xr_at(i - 1)] = vx[k];
-        }
-    }
-    const bool act = row_ok && s < S;
-    const int p0 = nx - CPL * (S - s);
-    const bool lnear = p0 <= 1;                      // holds a left-end position (or padding)
-    const bool re = s == S - 1;                      // holds the right end at k = CPL-2, CPL-1
-    // right-hand side w of this lane's cells (padding positions read cell 0)
-    double wr[CPL];
-    if (act) {
-        const double *wrow = p.in2 + (size_t)j * nx;
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) wr[k] = wrow[max(p0 + k, 0)];
-    }
-    __syncthreads();
-
-    // u and ds^2 times the 5-point Laplacian at position p0 + t of this lane (t >= -1)
-    const int base = xr_base(s);
-    auto U = [&](int t) { return sU[base + xr_off(t)]; };
-    auto cell = [&](int t) {
-        const double uq = U(t);
-        return cell_core<KM>(p, uq, __builtin_fma(-4.0, uq, (U(t + 1) + U(t - 1)) + sX[base + xr_off(t)]));
-    };
-    // phase 1: assemble and eliminate the sub-segment with its outer unknowns l1 = x_{p0-2},
-    // l2 = x_{p0-1} kept symbolic (z: constant part, ph: coefficient of l1, ps: of l2); the
-    // factors stay in registers for the back-substitution
-    double fa[CPL], fb[CPL], fz[CPL], fph[CPL], fps[CPL];
-    if (act) {
-        CellS c0 = cell(0);
-        FaceS fm = face_s<false>(cell(-1), c0, true, ka); // re-formed below at x = 0
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) {
-            const int gp = p0 + k;
-            const CellS cp = cell(k + 1);
-            const FaceS fp = face_s<false>(c0, cp, !(re && k == CPL - 1), ka);
-            Band B = xr_band(fm, fp);
-            double rhs = wr[k];
-            if (re && k >= CPL - 2) fold_right(B, CPL - 1 - k);
-            if (lnear) {
-                if (gp < 0) {
-                    B = {0.0, 0.0, 1.0, 0.0, 0.0};
-                    rhs = 0.0;
-                } else if (gp == 0) {
-                    // the face x = 0 carries no flux
-                    B = xr_band(FaceS{0.0, 0.0, 0.0, 0.0}, fp);
-                    if (re && k >= CPL - 2) fold_right(B, CPL - 1 - k);
-                    fold_left(B, 0);
-                } else if (gp == 1) {
-                    fold_left(B, 1);
-                }
-            }
-            xr_elim(k, B, rhs, fa, fb, fz, fph, fps);
-            c0 = cp;
-            fm = fp;
-        }
-    }
-    __syncthreads(); // the staged rows are consumed: X becomes the record tree and the u
-                     // row's space holds one factor array until the back-substitution
-    double *const rec = sX;
-    if (act) {
-        xr_record(rec, S, s, fa, fb, fz, fph, fps);
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) sU[base + k] = fps[k];
-    }
-    __syncthreads();
-    xr_tree(rec, S, tr, row_ok);
-    // back-substitution from the outer pairs; v replaces the parked factor in the u row
-    if (act) xr_backsub(rec, S, s, sU + base, fa, fb, fz, fph);
-    __syncthreads();
-
-    // output: u_{k+1} = u_k + v, update ratio, flags, mass diagnostic (coalesced)
-    double emax = 0.0;
-    unsigned flags = 0;
-    const bool diag = p.mass != nullptr;
-    double ms = 0.0, mc = 0.0, mmin = __builtin_inf();
-    if (row_ok) {
-        double *orow = p.out + (size_t)j * nx;
-        const double *urow = p.u + (size_t)j * nx;
-        double uk[XR_STAGE];
-#pragma unroll
-        for (int k = 0; k < XR_STAGE; ++k) {
-            const int i = tr + k * nthr;
-            uk[k] = urow[min(i, nx - 1)];
-        }
-#pragma unroll
-        for (int k = 0; k < XR_STAGE; ++k) {
-            const int i = tr + k * nthr;
-            if (i < nx) {
-                const double v = sU[xr_at(i + sh)];
-                const double un = uk[k] + v;
-                emax = fmax(emax, fabs(v) * rcp(fabs(uk[k])));
-                if (!(un > 0.0)) flags |= (un != un || v != v) ? FLAG_NAN : FLAG_NONPOS;
-                orow[i] = un;
-                if (diag) {
-                    two_sum_acc(ms, mc, un);
-                    mmin = fmin(mmin, un);
-                }
-            }
-        }
-    }
-    const double wm = wave_max(emax);
-    const unsigned wf = wave_or(flags);
-    if (lane == 0 && p.res != nullptr) {
-        unsigned long long *rs = p.res + (size_t)((blockIdx.x * 8 + wave) % p.res_spread) * RES_WORDS;
-        atomicMax(&rs[RES_EMAX], (unsigned long long)__double_as_longlong(wm));
-        if (wf) atomicOr(&rs[RES_FLAGS], (unsigned long long)wf);
-    }
-    if (diag) {
-        // fixed-order butterfly over the lanes, then the waves in order: the record of the
-        // workgroup does not depend on scheduling
-        __shared__ double sM[3 * XR_WAVES];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            comp_add(ms, mc, __shfl_xor(ms, o), __shfl_xor(mc, o));
-            mmin = fmin(mmin, __shfl_xor(mmin, o));
-        }
-        if (lane == 0) {
-            sM[3 * wave] = ms;
-            sM[3 * wave + 1] = mc;
-            sM[3 * wave + 2] = mmin;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            const int nw = blockDim.x >> 6;
-            double sm = sM[0], c = sM[1], m = sM[2];
-            for (int w = 1; w < nw; ++w) {
-                comp_add(sm, c, sM[3 * w], sM[3 * w + 1]);
-                m = fmin(m, sM[3 * w + 2]);
-            }
-            double *o = p.mass + 4 * (size_t)rowblock;
-            o[0] = sm;
-            o[1] = c;
-            o[2] = m;
-            o[3] = 0.0;
-        }
-    }
-}
-
-template <int KM, int WAVES>
-__global__ void __launch_bounds__(64 * WAVES) k_xrow(PassParams p, XRowGeom g, int nblocks)
-{
-    __shared__ double lds[xr_lds(WAVES)];
-    const int rb = xcd_tile(blockIdx.x, nblocks);
-    xrow_body<KM>(p, g, rb, lds);
-}
-
-template <int KM>
-static void launch_xrow_km(const PassParams &p, const XRowGeom &g, hipStream_t s)
-{
-    const int nb = (p.ny + g.R - 1) / g.R;
-    const dim3 grid(nb), block(64 * g.W * g.R);
-    if (g.waves == 4) k_xrow<KM, 4><<<grid, block, 0, s>>>(p, g, nb);
-    else k_xrow<KM, XR_WAVES><<<grid, block, 0, s>>>(p, g, nb);
-}
-
-// Ensemble version: block -> (film, row block) from the work list; the film's geometry,
-// model, dt and buffer rotation come from the device tables. Every film on this path has
-// rows of at most XR_ROW4_MAX_NX cells (4-wave workgroups). Films that are not iterating
-// exit at once (before any barrier: the test is uniform over the block).
-template <int KM>
-__global__ void __launch_bounds__(256) k_xrow_ens(EnsParams e)
-{
-    __shared__ double lds[xr_lds(4)];
-    const int t = xcd_tile(blockIdx.x, e.nitems);
-    const int f = e.items[2 * t], rb = e.items[2 * t + 1];
-    FilmState *st = e.state + f;
-    if (!st->active) return;
-    const FilmDesc d = e.desc[f];
-    double *B[3] = {e.buf0, e.buf1, e.buf2};
-    PassParams p{};
-    p.nx = d.nx;
-    p.ny = d.ny;
-    p.ids2 = 1.0 / (d.ds * d.ds);
-    p.f0s = p.ids2 * d.M.cap;
-    p.ka = 0.5 * e.theta * st->dt * p.ids2;
-    p.K0 = 3.0 * p.ka * p.ids2 * d.M.cap;
-    p.K1 = p.ka * d.M.Dn;
-    p.M = d.M;
-    p.u = B[st->it] + d.off;
-    p.in2 = e.w + d.off;
-    p.out = B[st->nxt] + d.off;
-    p.res = st->red;
-    p.res_spread = ENS_RES_SPREAD;
-    xrow_body<KM>(p, xrow_geom(d.nx), rb, lds);
-}
-
-hipError_t launch_xrow_ens(int km, const EnsParams &e, hipStream_t s)
-{
-    const dim3 grid(e.nitems), block(256);
-    switch (km) {
-    case KM_P32: k_xrow_ens<KM_P32><<<grid, block, 0, s>>>(e); break;
-    case KM_POWER: k_xrow_ens<KM_POWER><<<grid, block, 0, s>>>(e); break;
-    case KM_LINEAR: k_xrow_ens<KM_LINEAR><<<grid, block, 0, s>>>(e); break;
-    case KM_NLC: k_xrow_ens<KM_NLC><<<grid, block, 0, s>>>(e); break;
-    default: k_xrow_ens<KM_POLYMER><<<grid, block, 0, s>>>(e); break;
-    }
-    return hipGetLastError();
 }
 
 // ---- stored-band whole-line solve -------------------------------------------------------
@@ -634,27 +323,6 @@ hipError_t launch_sbline(bool trans, bool pm, int mode, int nl, int np, const do
     else if (trans) k_sbline<true, true, 1><<<grid, block, 0, s>>>(nl, np, bands, rhs, out, red, g, nb, stop);
     else if (mode == 0) k_sbline<false, true, 0><<<grid, block, 0, s>>>(nl, np, bands, rhs, out, red, g, nb, stop);
     else k_sbline<false, true, 1><<<grid, block, 0, s>>>(nl, np, bands, rhs, out, red, g, nb, stop);
-    return hipGetLastError();
-}
-
-int xrow_blocks(int nx, int ny)
-{
-    const XRowGeom g = xrow_geom(nx);
-    return (ny + g.R - 1) / g.R;
-}
-
-hipError_t launch_xrow(const PassParams &p, hipStream_t s)
-{
-    if (!xrow_supported(p.nx)) return hipErrorInvalidValue;
-    const XRowGeom g = xrow_geom(p.nx);
-    switch (p.M.kind) {
-    case MODEL_LINEAR: launch_xrow_km<KM_LINEAR>(p, g, s); break;
-    case MODEL_NLC: launch_xrow_km<KM_NLC>(p, g, s); break;
-    case MODEL_POLYMER: launch_xrow_km<KM_POLYMER>(p, g, s); break;
-    default:
-        if (p.M.p32) launch_xrow_km<KM_P32>(p, g, s);
-        else launch_xrow_km<KM_POWER>(p, g, s);
-    }
     return hipGetLastError();
 }
 

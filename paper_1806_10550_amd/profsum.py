@@ -24,7 +24,8 @@ KERNEL_CLASSES = [
     (r"k_pass<1, false", "relations_x"),
     (r"k_pass<1, true", "solve_x"),
     (r"k_chain", "chain"),
-    (r"k_xrow", "xrow"),
+    (r"k_xline", "xrow"),
+    (r"k_yline", "yline"),
     (r"k_mass", "mass"),
     (r"k_flux_divergence", "rhs_theta"),
 ]
@@ -86,7 +87,7 @@ def copy_duration_us(d, counter):
 
 
 # kernel classes that make up one iteration of the ADI-Newton step (the ones the records keep)
-STEP_CLASSES = ("relations_y", "solve_y", "relations_x", "solve_x", "chain", "xrow")
+STEP_CLASSES = ("relations_y", "solve_y", "relations_x", "solve_x", "chain", "xrow", "yline")
 
 
 def commands(bench_args):

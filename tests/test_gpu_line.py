@@ -1,0 +1,87 @@
+"""Whole-line sweeps (one to several waves per line, cyclic reduction across the lanes) against the
+oracle at the edges of their geometry: the shortest lines, one below / at / above a lane's 4, 8 and
+16 positions, the lengths where the positions per lane and the waves per line change, the longest
+columns and rows, and column counts that do not fill a workgroup."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1806_10550_amd import synth
+from paper_1806_10550_amd.lib import Ensemble, Grid
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# lengths on both sides of every change of geometry
+EDGES = [4, 5, 7, 8, 9, 255, 256, 257, 263, 511, 512, 513, 527, 1023, 1024, 1025, 1039, 2047, 2048]
+
+
+def one(orc, nx, ny, theta=1.0, model="power"):
+    ds, dt, h0 = {"power": (0.67347, 0.2, 1.0), "nlc": (0.1325, 0.028, 0.5), "polymer": (0.126, 7.1e-4, 3.9),
+                  "linear": (0.5, 0.05, 1.0)}[model]
+    un = synth.noise_film(nx, ny, seed=nx + 3 * ny, h0=h0, amp=0.01 * h0)
+    g = Grid(nx, ny, ds)
+    if model == "power":
+        g.set_model(10.0, 0.1, 3, 2)
+        M = orc.Model(kappa=10.0, b=0.1, n=3.0, m=2.0)
+    else:
+        getattr(g, "set_model_" + model)()
+        M = orc.Model.linear(1.0, 1.0) if model == "linear" else getattr(orc.Model, model)()
+    g.set_scheme(theta=theta)
+    if nx <= 8192:
+        g.set_xsweep("row")
+    u = torch.from_numpy(un).to(DEV)
+    out = torch.empty_like(u)
+    e, r, flags = g.newton_iteration(u, u, out, dt)
+    ref, e_ref, r_ref = orc.adi_iteration(M, un, un, ds, dt, theta)
+    got = out.cpu().numpy()
+    # the parity tests' bound on one iterate: 1e-10 of the update (plus rounding of u itself)
+    assert np.max(np.abs(got - ref)) <= 1e-10 * np.max(np.abs(ref - un)) + 4e-16 * h0
+    assert flags == 0
+    assert e == pytest.approx(e_ref, rel=1e-8)
+    assert r == pytest.approx(r_ref, rel=1e-8)
+    g.close()
+
+
+@pytest.mark.parametrize("n", EDGES)
+def test_columns_match_oracle(orc, n):
+    one(orc, 6, n)
+
+
+@pytest.mark.parametrize("n", EDGES + [3072, 3073, 4096, 5000, 8191, 8192])
+def test_rows_match_oracle(orc, n):
+    one(orc, n, 5)
+
+
+@pytest.mark.parametrize("model,theta", [("nlc", 0.5), ("polymer", 1.0), ("linear", 0.5)])
+@pytest.mark.parametrize("nx,ny", [(67, 130), (300, 517), (1030, 300), (21, 1500)])
+def test_models_match_oracle(orc, model, theta, nx, ny):
+    one(orc, nx, ny, theta, model)
+
+
+def test_ensemble_of_every_line_class_equals_single_films():
+    """One film per geometry class of the columns and rows (and one that takes tiles), bit for bit."""
+    shapes = [(100, 90), (300, 60), (700, 400), (1500, 700), (60, 1300), (2500, 40), (4000, 24), (9, 2100)]
+    nx, ny = [a for a, _ in shapes], [b for _, b in shapes]
+    ds = [0.67347] * len(shapes)
+    kap = [10.0 + i for i in range(len(shapes))]
+    ens = Ensemble(nx, ny, ds, kap)
+    ens.set_scheme(theta=0.5, tol=1e-10)
+    h0 = [synth.noise_film(a, b, seed=i, amp=0.01) for i, (a, b) in enumerate(shapes)]
+    packed = torch.empty(ens.size, dtype=torch.float64, device=DEV)
+    for f, h in enumerate(h0):
+        ens.view(packed, f).copy_(torch.from_numpy(h))
+    ens.bind(packed)
+    st, _, sts, its = ens.step(2, 0.1)
+    assert st == 0 and not any(sts)
+    for f in range(len(shapes)):
+        g = Grid(nx[f], ny[f], ds[f])
+        g.set_model(kap[f], 0.1, 3, 2)
+        g.set_scheme(theta=0.5, tol=1e-10)
+        g.set_xsweep(ens.xsweep(f))
+        h = torch.from_numpy(h0[f]).to(DEV)
+        g.bind(h)
+        _, log = g.advance(2, 0.1, log=True)
+        assert torch.equal(ens.view(packed, f), h), shapes[f]
+        assert its[f] == sum(x["total_iters"] for x in log)
+        g.close()
