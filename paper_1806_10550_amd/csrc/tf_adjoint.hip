@@ -462,52 +462,27 @@ __global__ void __launch_bounds__(PCR_THREADS) k_sb_pcr(SBParams P)
 //   local_c = sum_f omega_f [ f0'_c Lam_f / 2 + f1'_c Gam_f / 2 -+ B_f / ds ]  (- if c = L)
 //   xi_c    = sum_f omega_f A_f (+1 if c = R, -1 if c = L) / ds
 // and L the cell-centred Laplacian (symmetric under the even reflection).
-template <bool P32>
-__device__ __forceinline__ void jdt_cell(int nx, int ny, double ids, double ids2, const Model &M, const double *u,
-                                         const double *mu, int i, int j, double &xi, double &loc)
-{
-    const Cell c = cell_glob<P32>(u, nx, ny, i, j, M, ids2);
-    const double mc = mu[(size_t)j * nx + i];
-    double lo = 0.0, x = 0.0;
-    const int di[4] = {-1, 1, 0, 0}, dj[4] = {0, 0, -1, 1};
-    const bool inside[4] = {i > 0, i < nx - 1, j > 0, j < ny - 1};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        if (!inside[k]) continue;
-        const int ni = i + di[k], nj = j + dj[k];
-        const Cell n = cell_glob<P32>(u, nx, ny, ni, nj, M, ids2);
-        const double mn = mu[(size_t)nj * nx + ni];
-        const bool cIsR = (k == 0 || k == 2); // neighbour is the lower-index cell L
-        const double A = 0.5 * (cIsR ? n.f0 + c.f0 : c.f0 + n.f0);
-        const double B = 0.5 * (cIsR ? n.f1 + c.f1 : c.f1 + n.f1);
-        const double Lam = (cIsR ? c.lap - n.lap : n.lap - c.lap) * ids;
-        const double Gam = (cIsR ? c.u - n.u : n.u - c.u) * ids;
-        const double om = (cIsR ? mn - mc : mc - mn) * ids;
-        lo += om * (c.f0p * Lam + c.f1p * Gam + (cIsR ? B * ids : -B * ids));
-        x += (cIsR ? om * A : -om * A) * ids;
-    }
-    xi = x;
-    loc = lo;
-}
-
-// out = a lam + b mu + g J_D(u)^T mu in one kernel: a workgroup owns a JT_X x JT_Y tile,
-// forms xi on the tile and its one-cell ring (ghost positions take the reflected cell's
-// value) and local on the tile in LDS, then applies the Laplacian to xi from LDS.
+// out = a lam + b mu + g J_D(u)^T mu in one kernel. A wave streams JT_R rows of 64 columns: per row one
+// row of cells, the three products of each face
+//   om Lam, om Gam, om B/ds  (om = (mu_L - mu_R)/ds; Lam, Gam, A, B as in the fluxes)
+// and xi, from which the previous row's Laplacian of xi follows; x neighbours come from whole-wave DPP
+// shifts, so the three outer lanes on each side only feed the others. Ghost rows and columns carry
+// reflected u and mu, which makes om zero on the boundary faces and xi even across them: no masks.
+// Latency bound at the sizes the adjoint runs at (512^2: 13.4 -> 6.1 us; evaluating a cell and its
+// four neighbours from global memory for every element took the 13.4).
 // clr (nullable): two reduction words zeroed for a later kernel of the stream.
 // Richardson iterations enqueued in a batch (ctl non-null): ctl[0] is the stop word. A
 // launch that finds it set does nothing; one that finds the previous iteration's record
 // chk = {max|z|, max|mu|} converged (max|z| <= tol max|mu|) or NaN does nothing either and
 // sets ctl[0] (1: converged, 2: NaN) and ctl[1] = it - 1, the converged iteration. Every
 // workgroup reads the same record, so all take the same decision.
-constexpr int JT_X = 64, JT_Y = 16;
+constexpr int JT_X = 58, JT_R = 8, JT_Y = 4 * JT_R; // a workgroup: four waves, one below the other
 template <bool P32>
 __global__ void __launch_bounds__(256) k_jdt(int nx, int ny, double ids, double ids2, Model M, const double *u,
                                              const double *mu, const double *lam, double a, double b, double g,
                                              double *out, unsigned long long *clr, const unsigned long long *chk,
                                              unsigned long long *ctl, double tol, int it)
 {
-    constexpr int RX = JT_X + 2, RY = JT_Y + 2;
-    __shared__ double sxi[RY * RX], sloc[RY * RX];
     if (ctl != nullptr) {
         if (ctl[0] != 0ull) return;
         if (chk != nullptr) {
@@ -523,28 +498,72 @@ __global__ void __launch_bounds__(256) k_jdt(int nx, int ny, double ids, double 
         }
     }
     if (clr != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 2) clr[threadIdx.x] = 0ull;
-    const int i0 = blockIdx.x * JT_X, j0 = blockIdx.y * JT_Y;
-    for (int e = threadIdx.x; e < RX * RY; e += 256) {
-        const int li = e % RX, lj = e / RX;
-        const int ri = i0 - 1 + li, rj = j0 - 1 + lj; // -1 and nx / ny are the ghost layer
-        if (ri > nx || rj > ny) continue;             // beyond it: never read
-        double x, l;
-        jdt_cell<P32>(nx, ny, ids, ids2, M, u, mu, crefl(ri, nx), crefl(rj, ny), x, l);
-        sxi[e] = x;
-        sloc[e] = l;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < JT_X * JT_Y; e += 256) {
-        const int ti = e % JT_X, tj = e / JT_X;
-        const int i = i0 + ti, j = j0 + tj;
-        if (i >= nx || j >= ny) continue;
-        const int c = (tj + 1) * RX + ti + 1;
-        const double lx = (sxi[c + 1] + sxi[c - 1] + sxi[c + RX] + sxi[c - RX] - 4.0 * sxi[c]) * ids2;
-        const size_t o = (size_t)j * nx + i;
-        double v = g * (sloc[c] + lx);
-        if (b != 0.0) v += b * mu[o];
-        if (a != 0.0) v += a * lam[o];
-        out[o] = v;
+    const int lane = threadIdx.x & 63;
+    const int i = blockIdx.x * JT_X + lane - 3;
+    const int j0 = blockIdx.y * JT_Y + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * JT_R;
+    if (j0 >= ny) return;                          // uniform over the wave
+    const bool own = lane >= 3 && lane < 3 + JT_X && i < nx;
+    const unsigned ic = (unsigned)crefl(i, nx);
+    double vu[JT_R + 6], vm[JT_R + 4], vl[JT_R];   // u from row j0 - 3, mu from j0 - 2, lam from j0
+#pragma unroll
+    for (int r = 0; r < JT_R + 6; ++r) vu[r] = (u + (size_t)crefl(j0 - 3 + r, ny) * nx)[ic];
+#pragma unroll
+    for (int r = 0; r < JT_R + 4; ++r) vm[r] = (mu + (size_t)crefl(j0 - 2 + r, ny) * nx)[ic];
+#pragma unroll
+    for (int r = 0; r < JT_R; ++r) vl[r] = a != 0.0 ? (lam + (size_t)crefl(j0 + r, ny) * nx)[ic] : 0.0;
+    struct JFace {
+        double q, p0, p1, p2; // om A / ds, om Lam, om Gam, om B / ds
+    };
+    auto cell = [&](int r) {                       // row j0 - 2 + r
+        Cell c;
+        c.u = vu[r + 1];
+        c.lap = (lane_next(c.u) + lane_prev(c.u) + vu[r + 2] + vu[r] - 4.0 * c.u) * ids2;
+        model_coefs<P32>(M, c.u, c.f0, c.f1, c.f0p, c.f1p);
+        c.f0p *= 0.5;
+        c.f1p *= 0.5;
+        return c;
+    };
+    auto face = [&](double lu, double ll, double l0, double l1, double lm, double ru, double rl, double r0, double r1,
+                    double rm) {
+        const double om = (lm - rm) * ids;
+        JFace f;
+        f.q = om * (0.5 * (l0 + r0)) * ids;
+        f.p0 = om * ((rl - ll) * ids);
+        f.p1 = om * ((ru - lu) * ids);
+        f.p2 = om * (0.5 * (l1 + r1)) * ids;
+        return f;
+    };
+    Cell c = cell(0);
+    JFace fs{};
+    double xm = 0.0, x0 = 0.0, lo0 = 0.0;          // xi of the two rows before, local part of the last
+#pragma unroll
+    for (int r = 0; r < JT_R + 3; ++r) {           // cell rows r and r + 1; xi of row r; result of row r - 1
+        const Cell n = cell(r + 1);
+        const JFace fn = face(c.u, c.lap, c.f0, c.f1, vm[r], n.u, n.lap, n.f0, n.f1, vm[r + 1]);
+        double xi = 0.0, lo = 0.0;
+        if (r >= 1) {
+            const JFace fe = face(c.u, c.lap, c.f0, c.f1, vm[r], lane_next(c.u), lane_next(c.lap), lane_next(c.f0),
+                                  lane_next(c.f1), lane_next(vm[r]));
+            xi = lane_prev(fe.q) - fe.q + fs.q - fn.q;
+            if (r >= 2 && r < JT_R + 2)
+                lo = c.f0p * (lane_prev(fe.p0) + fe.p0 + fs.p0 + fn.p0) + c.f1p * (lane_prev(fe.p1) + fe.p1 + fs.p1 + fn.p1)
+                     + (lane_prev(fe.p2) - fe.p2 + fs.p2 - fn.p2);
+        }
+        if (r >= 3) {
+            const double lx = (lane_next(x0) + lane_prev(x0) + xi + xm - 4.0 * x0) * ids2;
+            const int j = j0 + r - 3;
+            if (own && j < ny) {
+                double v = g * (lo0 + lx);
+                if (b != 0.0) v += b * vm[r - 1];
+                if (a != 0.0) v += a * vl[r - 3];
+                out[(size_t)j * nx + i] = v;
+            }
+        }
+        xm = x0;
+        x0 = xi;
+        lo0 = lo;
+        c = n;
+        fs = fn;
     }
 }
 

@@ -192,7 +192,7 @@ tf::PassParams base_params(const tf_grid *g, double dt)
 }
 
 // The y sweep takes whole columns wherever tf::yline_geom gives them.
-bool yline(const tf_grid *g) { return tf::yline_geom(g->nx, g->ny).W > 0; }
+bool yline(const tf_grid *g) { return tf::yline_geom(tf::kernel_model(g->M), g->nx, g->ny).W > 0; }
 
 // One ADI-Newton iteration: y sweep (relations, chain, solve) into w, x sweep into
 // u_kp1. The reduction record of slot `slot` receives max|G| (y relations pass) and

@@ -128,18 +128,6 @@ tf_status ensure_graph(tf_ensemble *e)
     return TF_OK;
 }
 
-// Replace every film's model by M (kernel form km) and upload the film table.
-tf_status set_all_models(tf_ensemble *e, const tf::Model &M, int km)
-{
-    for (auto &d : e->desc) d.M = M;
-    TF_EHIP(hipMemcpyAsync(e->d_desc, e->desc.data(), e->nfilms * sizeof(tf::FilmDesc), hipMemcpyHostToDevice,
-                           e->stream));
-    TF_EHIP(hipStreamSynchronize(e->stream));
-    e->km = km;
-    drop_graph(e);
-    return TF_OK;
-}
-
 int line_class(const tf::LineGeom &g, const tf::LineGeom *classes, int n)
 {
     for (int c = 0; c < n; ++c)
@@ -149,24 +137,24 @@ int line_class(const tf::LineGeom &g, const tf::LineGeom *classes, int n)
 
 // Work lists of one iteration: the y sweep of a film is whole-column where tf::yline_geom gives a
 // geometry (as for a single film), its x sweep whole-row when xsweep[f] == 1; the others take tiles
-// and chain blocks. The b^n list covers every film's y tiles.
+// and chain blocks. The b^n list covers every film.
 void build_items(tf_ensemble *e, std::vector<int> &items)
 {
     std::vector<int> ty, tx, cy, cx, bnt, yl[tf::N_YL], xl[tf::N_XL];
     for (int f = 0; f < e->nfilms; ++f) {
         const tf::FilmDesc &d = e->desc[f];
-        const int yc = line_class(tf::yline_geom(d.nx, d.ny), tf::YL_CLASSES, tf::N_YL);
+        const int yc = line_class(tf::yline_geom(e->km, d.nx, d.ny), tf::YL_CLASSES, tf::N_YL);
         const int xc = e->xsweep[f] == 1 ? line_class(tf::xline_geom(d.nx), tf::XL_CLASSES, tf::N_XL) : -1;
         const int tyx = (d.nx + tf::TILE - 1) / tf::TILE, txy = (d.ny + tf::TILE - 1) / tf::TILE;
-        for (int j = 0; j < d.Py; ++j)
-            for (int i = 0; i < tyx; ++i) {
-                bnt.insert(bnt.end(), {f, i, j});
-                if (yc < 0) ty.insert(ty.end(), {f, i, j});
-            }
-        if (yc >= 0)
+        for (int j = 0; j < tf::bn_tiles_y(d.ny); ++j)
+            for (int i = 0; i < tf::bn_tiles_x(d.nx); ++i) bnt.insert(bnt.end(), {f, i, j});
+        if (yc >= 0) {
             for (int b = 0; b < (d.nx + tf::LN_COLS - 1) / tf::LN_COLS; ++b) yl[yc].insert(yl[yc].end(), {f, b});
-        else
+        } else {
+            for (int j = 0; j < d.Py; ++j)
+                for (int i = 0; i < tyx; ++i) ty.insert(ty.end(), {f, i, j});
             for (int b = 0; b < (d.nx + 63) / 64; ++b) cy.insert(cy.end(), {f, b});
+        }
         if (xc >= 0) {
             for (int j = 0; j < d.ny; ++j) xl[xc].insert(xl[xc].end(), {f, j});
         } else {
@@ -190,6 +178,29 @@ void build_items(tf_ensemble *e, std::vector<int> &items)
     for (int c = 0; c < tf::N_XL; ++c) put(e->xl[c], xl[c], 2);
 }
 
+tf_status upload_items(tf_ensemble *e)
+{
+    std::vector<int> items;
+    build_items(e, items);
+    TF_EHIP(hipStreamSynchronize(e->stream));
+    TF_EHIP(hipMemcpyAsync(e->d_items, items.data(), items.size() * sizeof(int), hipMemcpyHostToDevice, e->stream));
+    TF_EHIP(hipStreamSynchronize(e->stream));
+    drop_graph(e);
+    return TF_OK;
+}
+
+// Replace every film's model by M (kernel form km) and upload the film table and
+// the work lists (the whole-column rule depends on the model).
+tf_status set_all_models(tf_ensemble *e, const tf::Model &M, int km)
+{
+    for (auto &d : e->desc) d.M = M;
+    TF_EHIP(hipMemcpyAsync(e->d_desc, e->desc.data(), e->nfilms * sizeof(tf::FilmDesc), hipMemcpyHostToDevice,
+                           e->stream));
+    TF_EHIP(hipStreamSynchronize(e->stream));
+    e->km = km;
+    return upload_items(e);
+}
+
 // Rows of all films: the x sweep of an ensemble is one launch over every film's rows, so the
 // automatic variant choice takes this as its batch.
 int total_rows(const tf_ensemble *e)
@@ -205,7 +216,8 @@ size_t max_items(const tf_ensemble *e)
     size_t n = 0;
     for (const auto &d : e->desc) {
         const size_t yt = (size_t)d.Py * ((d.nx + tf::TILE - 1) / tf::TILE);
-        n += 6 * yt + 2 * (size_t)((d.nx + tf::LN_COLS - 1) / tf::LN_COLS);
+        n += 3 * yt + 3 * (size_t)tf::bn_tiles_x(d.nx) * tf::bn_tiles_y(d.ny);
+        n += 2 * (size_t)((d.nx + 63) / 64) + 2 * (size_t)((d.nx + tf::LN_COLS - 1) / tf::LN_COLS);
         n += 3 * (size_t)((d.ny + tf::TILE - 1) / tf::TILE) * d.Px + 2 * (size_t)((d.ny + 63) / 64) + 2 * (size_t)d.ny;
     }
     return n;
@@ -360,13 +372,7 @@ tf_status tf_ensemble_set_xsweep(tf_ensemble *e, int variant)
         e->xsweep[f] = variant == TF_XSWEEP_AUTO ? tf::xsweep_choice(d.nx, total_rows(e))
                      : (variant == TF_XSWEEP_ROW && row4 ? 1 : 0);
     }
-    std::vector<int> items;
-    build_items(e, items);
-    TF_EHIP(hipStreamSynchronize(e->stream));
-    TF_EHIP(hipMemcpyAsync(e->d_items, items.data(), items.size() * sizeof(int), hipMemcpyHostToDevice, e->stream));
-    TF_EHIP(hipStreamSynchronize(e->stream));
-    drop_graph(e);
-    return TF_OK;
+    return upload_items(e);
 }
 
 int tf_ensemble_xsweep(const tf_ensemble *e, int film)

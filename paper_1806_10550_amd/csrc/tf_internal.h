@@ -166,6 +166,12 @@ struct Model {
     double C8, a2, c2, d;      // polymer
 };
 
+inline int kernel_model(const Model &M)
+{
+    return M.kind == MODEL_LINEAR ? KM_LINEAR : M.kind == MODEL_NLC ? KM_NLC : M.kind == MODEL_POLYMER ? KM_POLYMER
+         : M.p32 ? KM_P32 : KM_POWER;
+}
+
 // Parameters of one sweep pass (K1 relations / K3 solve) over a grid or a packed film.
 struct PassParams {
     int nx, ny;
@@ -250,7 +256,7 @@ struct LineGeom {
     int cpl, W; // positions per lane, waves per line
 };
 LineGeom xline_geom(int nx);
-LineGeom yline_geom(int nx, int ny);
+LineGeom yline_geom(int km, int nx, int ny); // km: KernelModel
 // the classes an ensemble's films fall into (rows of at most XR_ROW4_MAX_NX cells)
 constexpr LineGeom YL_CLASSES[] = {{4, 1}, {8, 1}, {16, 1}, {16, 2}};
 constexpr LineGeom XL_CLASSES[] = {{4, 1}, {8, 1}, {16, 1}, {16, 2}, {16, 3}, {16, 4}};
@@ -280,7 +286,10 @@ hipError_t launch_mass(const double *u, size_t n, double *partials, int nblocks,
 // out = {sum, min}.
 hipError_t launch_mass_tiles(const double *part, int ntiles, double *out, hipStream_t s);
 hipError_t launch_pass_ens(int dir, bool solve, int km, const EnsParams &e, hipStream_t s);
-// b^n of every active film at the first iteration of an attempt (items: the y-sweep tiles)
+// b^n of every active film at the first iteration of an attempt (items: (film, tx, ty) over the
+// bn_tiles_x x bn_tiles_y tiles of each film)
+int bn_tiles_x(int nx);
+int bn_tiles_y(int ny);
 hipError_t launch_bn_ens(const EnsParams &e, hipStream_t s);
 hipError_t launch_chain_ens(const EnsParams &e, int dir, hipStream_t s);
 hipError_t launch_ens_control(FilmState *st, int nfilms, const EnsScheme &S, int *active_count, hipStream_t s);

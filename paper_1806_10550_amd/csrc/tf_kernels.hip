@@ -778,43 +778,65 @@ __global__ void __launch_bounds__(128) k_chain_ens(EnsParams e, int dir)
 // out = alpha * add + beta * D(u) per cell (flux-difference operator; add may be null).
 // Used for b^n = u^n - (1 - theta) dt D(u^n) and for testing D.
 // ------------------------------------------------------------------------------------
-template <bool P32>
-__device__ __forceinline__ void cell_g(const double *u, int nx, int ny, int i, int j, const Model &M,
-                                       double ids2, double &uc, double &lap, double &f0, double &f1)
+//
+// A wave streams FD_R rows of 64 columns through its registers (one u row loaded, one row of cells
+// evaluated and one row of results written per step); x neighbours come from whole-wave DPP shifts,
+// so the two outer lanes on each side only feed the others and 60 columns are owned. No LDS and no
+// barrier; every cell is evaluated 1.2 times instead of five. Bound by HBM for the cheap models
+// (16 B per cell) and by the FP64 rate of the tanh switch for NLC (1637^2: 55 -> 26 us).
+constexpr int FD_X = 60, FD_R = 16, FD_Y = 4 * FD_R; // a workgroup: four waves, one below the other
+
+struct FCell {
+    double u, lap, f0, f1;
+};
+// Flux from L to R, A and B the face means of f0 and f1 (NOF0: the f1 part only).
+template <bool NOF0>
+__device__ __forceinline__ double face_flux(const FCell &L, const FCell &R, double ids)
 {
-    const int im = crefl(i - 1, nx), ip = crefl(i + 1, nx), jm = crefl(j - 1, ny), jp = crefl(j + 1, ny);
-    const int ic = crefl(i, nx), jc = crefl(j, ny);
-    uc = u[(size_t)jc * nx + ic];
-    lap = (u[(size_t)jc * nx + ip] + u[(size_t)jc * nx + im] + u[(size_t)jp * nx + ic]
-           + u[(size_t)jm * nx + ic] - 4.0 * uc) * ids2;
-    double f0p, f1p;
-    model_coefs<P32>(M, uc, f0, f1, f0p, f1p);
+    const double A = NOF0 ? 0.0 : 0.5 * (L.f0 + R.f0), B = 0.5 * (L.f1 + R.f1);
+    return A * ((R.lap - L.lap) * ids) + B * ((R.u - L.u) * ids);
 }
 
-// D(u) at cell (i, j): the flux differences of eq. GovEqnCell2 with zero boundary fluxes
-// (NOF0: the f1 part only).
-template <bool P32, bool NOF0>
-__device__ __forceinline__ double flux_div_at(const double *u, int nx, int ny, int i, int j, double ids, double ids2,
-                                              const Model &M)
+// D(u), the flux differences of eq. GovEqnCell2 with zero boundary fluxes, on the rows j0 .. j0 +
+// FD_R - 1 of the columns i0 .. i0 + FD_X - 1: store(j, i, u, D).
+template <bool P32, bool NOF0, class Store>
+__device__ __forceinline__ void flux_div_rows(const double *u, int nx, int ny, int i0, int j0, double ids, double ids2,
+                                              const Model &M, Store store)
 {
-    double uc, lc, f0c, f1c;
-    cell_g<P32>(u, nx, ny, i, j, M, ids2, uc, lc, f0c, f1c);
-    double F[4];
-    const int di[4] = {-1, 1, 0, 0}, dj[4] = {0, 0, -1, 1};
-    const bool inside[4] = {i > 0, i < nx - 1, j > 0, j < ny - 1};
+    const int lane = threadIdx.x & 63;
+    const int i = i0 + lane - 2;
+    if (j0 >= ny) return;                          // uniform over the wave
+    const bool own = lane >= 2 && lane < 2 + FD_X && i < nx;
+    const double *col = u + (unsigned)crefl(i, nx);
+    double v[FD_R + 4];                            // rows j0 - 2 .. j0 + FD_R + 1
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        double un, ln, f0n, f1n;
-        cell_g<P32>(u, nx, ny, i + di[k], j + dj[k], M, ids2, un, ln, f0n, f1n);
-        // flux through the face towards neighbour k, oriented along +x / +y
-        const bool lower = (k == 0 || k == 2);
-        const double A = NOF0 ? 0.0 : (lower ? 0.5 * (f0n + f0c) : 0.5 * (f0c + f0n));
-        const double B = lower ? 0.5 * (f1n + f1c) : 0.5 * (f1c + f1n);
-        const double dl = lower ? (lc - ln) : (ln - lc);
-        const double du = lower ? (uc - un) : (un - uc);
-        F[k] = inside[k] ? A * (dl * ids) + B * (du * ids) : 0.0;
+    for (int r = 0; r < FD_R + 4; ++r) v[r] = col[(size_t)crefl(j0 - 2 + r, ny) * nx];
+    auto cell = [&](int r) {                       // row j0 - 2 + r
+        FCell c;
+        c.u = v[r];
+        c.lap = (lane_next(c.u) + lane_prev(c.u) + v[r + 1] + v[r - 1] - 4.0 * c.u) * ids2;
+        double f0p, f1p;
+        model_coefs<P32>(M, c.u, c.f0, c.f1, f0p, f1p);
+        return c;
+    };
+    FCell c = cell(2);
+    double Fs = face_flux<NOF0>(cell(1), c, ids);
+    if (j0 == 0) Fs = 0.0;
+#pragma unroll
+    for (int r = 2; r < FD_R + 2; ++r) {
+        const int j = j0 + r - 2;
+        if (j < ny) {
+            const FCell n = cell(r + 1);
+            const double Fn = j < ny - 1 ? face_flux<NOF0>(c, n, ids) : 0.0;
+            const FCell e = {lane_next(c.u), lane_next(c.lap), lane_next(c.f0), lane_next(c.f1)};
+            const double Fx = face_flux<NOF0>(c, e, ids);
+            const double Fe = i >= 0 && i < nx - 1 ? Fx : 0.0;
+            const double Fw = lane_prev(Fe);
+            if (own) store(j, i, c.u, (Fe - Fw + Fn - Fs) * ids);
+            c = n;
+            Fs = Fn;
+        }
     }
-    return (F[1] - F[0] + F[3] - F[2]) * ids;
 }
 
 template <bool P32, bool NOF0>
@@ -822,17 +844,16 @@ __global__ void __launch_bounds__(256) k_flux_divergence(int nx, int ny, double 
                                                          const double *u, double alpha, double beta,
                                                          const double *add, double *out)
 {
-    const int i = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int j = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (i >= nx || j >= ny) return;
-    const double D = flux_div_at<P32, NOF0>(u, nx, ny, i, j, ids, ids2, M);
-    const size_t o = (size_t)j * nx + i;
-    out[o] = (add != nullptr ? alpha * add[o] : 0.0) + beta * D;
+    const int j0 = blockIdx.y * FD_Y + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * FD_R;
+    flux_div_rows<P32, NOF0>(u, nx, ny, blockIdx.x * FD_X, j0, ids, ids2, M, [&](int j, int i, double, double D) {
+        const size_t o = (size_t)j * nx + i;
+        out[o] = (add != nullptr ? alpha * add[o] : 0.0) + beta * D;
+    });
 }
 
-// Ensemble b^n = u^n - (1 - theta) dt D(u^n), block -> one y-sweep tile (TILE columns x one
-// segment of rows) of a film that is active and at the first iteration of its attempt (the
-// same arithmetic as k_flux_divergence with alpha = 1, so the ensemble matches the single film).
+// Ensemble b^n = u^n - (1 - theta) dt D(u^n), block -> one FD_X x FD_Y tile of a film that is active
+// and at the first iteration of its attempt (the same arithmetic as k_flux_divergence with
+// alpha = 1, so the ensemble matches the single film).
 __global__ void __launch_bounds__(256) k_bn_ens(EnsParams e)
 {
     const int t = xcd_tile(blockIdx.x, e.nitems);
@@ -845,17 +866,13 @@ __global__ void __launch_bounds__(256) k_bn_ens(EnsParams e)
     double *bn = e.bn + d.off;
     const double ids = 1.0 / d.ds, ids2 = ids * ids;
     const double beta = -(1.0 - e.theta) * s->dt;
-    const int i0 = tx * TILE, i1 = min(i0 + TILE, d.nx);
-    const int j0 = seg_start(ty, d.ny), j1 = seg_start(ty + 1, d.ny);
-    const int w = i1 - i0;
-    for (int c = threadIdx.x; c < w * (j1 - j0); c += 256) {
-        const int i = i0 + c % w, j = j0 + c / w;
-        const double D = d.M.p32 ? flux_div_at<true, false>(un, d.nx, d.ny, i, j, ids, ids2, d.M)
-                                 : flux_div_at<false, false>(un, d.nx, d.ny, i, j, ids, ids2, d.M);
-        const size_t o = (size_t)j * d.nx + i;
-        bn[o] = un[o] + beta * D; // fma(beta, D, u), as in k_flux_divergence
-    }
+    const int j0 = ty * FD_Y + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * FD_R;
+    auto store = [&](int j, int i, double u, double D) { bn[(size_t)j * d.nx + i] = u + beta * D; };
+    if (d.M.p32) flux_div_rows<true, false>(un, d.nx, d.ny, tx * FD_X, j0, ids, ids2, d.M, store);
+    else flux_div_rows<false, false>(un, d.nx, d.ny, tx * FD_X, j0, ids, ids2, d.M, store);
 }
+int bn_tiles_x(int nx) { return (nx + FD_X - 1) / FD_X; }
+int bn_tiles_y(int ny) { return (ny + FD_Y - 1) / FD_Y; }
 
 // ------------------------------------------------------------------------------------
 // Mass diagnostic: per-block compensated (Neumaier) sum, minimum and NaN flag, reduced
@@ -1093,7 +1110,7 @@ hipError_t launch_chain(const ChainParams &c, hipStream_t s)
 hipError_t launch_flux_divergence(int nx, int ny, double ids, double ids2, const Model &M, const double *u,
                                   double alpha, double beta, const double *add, double *out, hipStream_t s)
 {
-    const dim3 grid((nx + 63) / 64, (ny + 3) / 4), block(256);
+    const dim3 grid(bn_tiles_x(nx), bn_tiles_y(ny)), block(256);
     if (M.p32) k_flux_divergence<true, false><<<grid, block, 0, s>>>(nx, ny, ids, ids2, M, u, alpha, beta, add, out);
     else k_flux_divergence<false, false><<<grid, block, 0, s>>>(nx, ny, ids, ids2, M, u, alpha, beta, add, out);
     return hipGetLastError();
@@ -1123,7 +1140,7 @@ hipError_t launch_model_coeffs(const Model &M, const double *h, int n, double *o
 hipError_t launch_flux_divergence_f1(int nx, int ny, double ids, double ids2, const Model &M, const double *u,
                                      double *out, hipStream_t s)
 {
-    const dim3 grid((nx + 63) / 64, (ny + 3) / 4), block(256);
+    const dim3 grid(bn_tiles_x(nx), bn_tiles_y(ny)), block(256);
     if (M.p32) k_flux_divergence<true, true><<<grid, block, 0, s>>>(nx, ny, ids, ids2, M, u, 0.0, 1.0, nullptr, out);
     else k_flux_divergence<false, true><<<grid, block, 0, s>>>(nx, ny, ids, ids2, M, u, 0.0, 1.0, nullptr, out);
     return hipGetLastError();

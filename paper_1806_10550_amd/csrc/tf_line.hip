@@ -37,10 +37,11 @@ LineGeom xline_geom(int nx)
 }
 // Columns of more than 1024 cells need a workgroup of 8 waves and 135 KB of LDS, one per CU, that
 // overlaps nothing: with many of them the partitioned passes stream better (8192 x 2048: 268 against
-// 251 us; 2048^2: 67 against 92).
-LineGeom yline_geom(int nx, int ny)
+// 251 us; 2048^2: 67 against 92), and the NLC model, whose cells cost most, loses more by evaluating
+// the neighbouring columns' cells than the partition costs (1637^2: 102 against 97 us).
+LineGeom yline_geom(int km, int nx, int ny)
 {
-    if (ny < 4 || ny > 2048 || (ny > 1024 && nx > 4096)) return {0, 0};
+    if (ny < 4 || ny > 2048 || (ny > 1024 && (nx > 4096 || km == KM_NLC))) return {0, 0};
     if (ny <= 256) return {4, 1};
     if (ny <= 512) return {8, 1};
     return {16, (ny + 1023) / 1024};
@@ -359,7 +360,7 @@ template <int KM>
 static hipError_t launch_line_km(int dir, const PassParams &p, hipStream_t s)
 {
     const int nb = (p.nx + LN_COLS - 1) / LN_COLS;
-    const LineGeom g = dir == 0 ? yline_geom(p.nx, p.ny) : xline_geom(p.nx);
+    const LineGeom g = dir == 0 ? yline_geom(KM, p.nx, p.ny) : xline_geom(p.nx);
     const dim3 gx(p.ny), gy(nb), bx(64 * g.W), by(64 * LN_COLS * g.W);
 #define TF_XL(C, V) case 100 * V + C: k_xline<KM, C, V><<<gx, bx, 0, s>>>(p); break
 #define TF_YL(C, V) case 100 * V + C: k_yline<KM, C, V><<<gy, by, 0, s>>>(p, nb); break
