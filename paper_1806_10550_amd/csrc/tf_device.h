@@ -465,45 +465,4 @@ __device__ __forceinline__ FaceQ face_q(const Cell &L, const Cell &R, bool inter
     return f;
 }
 
-// ---- cell quantities of a tile in LDS ---------------------------------------------------------
-// A TX x TY tile with H rings around it: u on all of it, lap, f0 and f1 on all but the outer ring
-// (pitch of every array: TX + 2 H). Element (x, y) of the tile at (y + H) * pitch + x + H. Each cell
-// is evaluated once (a cell and its neighbours' faces evaluated cell by cell take five).
-template <int TX, int TY, int H>
-struct CellTile {
-    static constexpr int RX = TX + 2 * H, RY = TY + 2 * H, N = RX * RY;
-    double u[N], lap[N], f0[N], f1[N];
-    static __device__ __forceinline__ int at(int x, int y) { return (y + H) * RX + x + H; }
-};
-
-// Fill a tile at cell (i0, j0) with NT threads (even reflection outside the grid; positions past the
-// first ghost layers repeat border cells and are not used). Ends with a barrier.
-template <bool P32, int TX, int TY, int H, int NT>
-__device__ __forceinline__ void cell_tile(CellTile<TX, TY, H> &T, const double *u, int nx, int ny, int i0, int j0,
-                                          const Model &M, double ids2)
-{
-    constexpr int RX = TX + 2 * H, RY = TY + 2 * H, N = RX * RY, K = (N + NT - 1) / NT;
-    double v[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int e = threadIdx.x + NT * k;
-        if (e < N) v[k] = u[(size_t)crefl(j0 - H + e / RX, ny) * nx + (unsigned)crefl(i0 - H + e % RX, nx)];
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int e = threadIdx.x + NT * k;
-        if (e < N) T.u[e] = v[k];
-    }
-    __syncthreads();
-    constexpr int CX = RX - 2, C = CX * (RY - 2);
-    for (int c = threadIdx.x; c < C; c += NT) {
-        const int e = (c / CX + 1) * RX + c % CX + 1;
-        const double uc = T.u[e];
-        T.lap[e] = (T.u[e + 1] + T.u[e - 1] + T.u[e + RX] + T.u[e - RX] - 4.0 * uc) * ids2;
-        double f0p, f1p;
-        model_coefs<P32>(M, uc, T.f0[e], T.f1[e], f0p, f1p);
-    }
-    __syncthreads();
-}
-
 } // namespace tf
