@@ -308,9 +308,11 @@ tf_status tf_spectrum_maxima(const double *q, const double *s, int npoints, doub
  * transposed != 0 solves with the transposed matrices. variant: 0 = partitioned
  * (64-cell segments, interface chain), 1 = one lane per line (Thomas), 2 = block cyclic
  * reduction in LDS (one workgroup per line, n <= 2048), 3 = whole lines in one kernel
- * (16-cell sub-segments per lane coupled by a tree of merges in LDS, 4 <= n <= 4096),
+ * (sub-segments of 4 to 16 cells per lane coupled by cyclic reduction across the lanes,
+ * 4 <= n <= 4096),
  * -1 = the autotuned choice. No pivoting: the matrices must be factorable without it.
- * Allocates and frees its own scratch; synchronises `stream`. TF_EINVAL for bad sizes,
+ * Allocates and frees the scratch of the chosen variant (variants 2 and 3 need none);
+ * synchronises `stream`. TF_EINVAL for bad sizes,
  * variant 2 with n > 2048 or variant 3 with n outside 4..4096. */
 tf_status tf_penta_solve(int nlines, int n, const double *bands, const double *rhs, double *x, int transposed,
                          int variant, void *stream);

@@ -695,8 +695,7 @@ constexpr int XSWEEP_KIND = 2;
 
 // choice for a batch of `nl` lines of length `np` (plain or transposed solves): the
 // autotuned entry of the same kind with the nearest (log-distance) shape, else a
-// heuristic (one lane per line only pays when the lines alone fill the GPU). Cyclic
-// reduction is only used for lines that fit in LDS.
+// built-in rule. Cyclic reduction is only used for lines that fit in LDS.
 Choice pick_variant(int np, int nl, bool trans)
 {
     TuneTable &t = tune_table();
@@ -712,7 +711,14 @@ Choice pick_variant(int np, int nl, bool trans)
     if (found && best_d < 0.7 && !(c.variant == V_PCR && np > tf::PCR_MAX)
         && !(c.variant == V_LINE && !tf::sbline_supported(np)))
         return c;
-    c.variant = nl >= 65536 ? V_THOMAS : V_PARTITIONED;
+    // shapes away from every tuned one: the whole-line kernel where it measured fastest (lines of at most
+    // 1024 cells in any number but the shortest by the ten thousand; of 2048 up to a few hundred thousand
+    // cells: 1024 x 512 lines 17 against 28 us partitioned, 2048 x 256 24 against 34, 2048 x 4096 213
+    // against 262, 4096 x 4096 609 against 512)
+    if (np >= 4 && (np <= 1024 || (np <= 2048 && nl <= 4096) || (np <= 4096 && nl <= 512)) && !(np <= 192 && nl >= 32768))
+        c.variant = V_LINE;
+    else
+        c.variant = nl >= 65536 ? V_THOMAS : V_PARTITIONED;
     c.block = 64;
     return c;
 }
@@ -968,6 +974,16 @@ size_t scratch_need(int variant, int n, int nlines)
     if (variant == V_THOMAS) return 3 * (size_t)n * nlines;
     return 0; // cyclic reduction and the whole-line solver work in LDS
 }
+Scratch scratch_at(double *base, int n, int nlines)
+{
+    const size_t recs = (size_t)tf::seg_count(n) * nlines;
+    Scratch S;
+    S.rel = base;
+    S.ext = base + recs * tf::NREL;
+    S.chain = base + recs * (tf::NREL + tf::NEXT);
+    S.work = base;
+    return S;
+}
 } // namespace
 
 extern "C" {
@@ -1137,25 +1153,19 @@ tf_status tf_penta_solve(int nlines, int n, const double *bands, const double *r
     if (variant == V_PCR && n > tf::PCR_MAX) return afail(TF_EINVAL, "cyclic reduction needs n <= 2048");
     if (variant == V_LINE && !tf::sbline_supported(n)) return afail(TF_EINVAL, "the whole-line solver needs 4 <= n <= 4096");
     hipStream_t s = (hipStream_t)stream;
-    const size_t recs = (size_t)tf::seg_count(n) * nlines;
-    Scratch S;
-    bool ok = hipMalloc(&S.rel, recs * tf::NREL * sizeof(double)) == hipSuccess
-              && hipMalloc(&S.ext, recs * tf::NEXT * sizeof(double)) == hipSuccess
-              && hipMalloc(&S.chain, recs * tf::NCHAIN * sizeof(double)) == hipSuccess
-              && hipMalloc(&S.work, 3 * (size_t)n * nlines * sizeof(double)) == hipSuccess;
-    tf_status st = TF_OK;
-    if (!ok) st = afail(TF_ENOMEM, "scratch allocation failed");
-    if (st == TF_OK) {
-        Choice c;
-        if (variant < 0) c = pick_variant(n, nlines, transposed != 0);
-        else c.variant = variant;
-        st = sb_solve(c, transposed != 0, 0, nlines, n, bands, rhs, x, nullptr, S, s);
-        if (st == TF_OK && hipStreamSynchronize(s) != hipSuccess) st = afail(TF_EDEVICE, "synchronize failed");
+    Choice c;
+    if (variant < 0) c = pick_variant(n, nlines, transposed != 0);
+    else c.variant = variant;
+    // scratch of the chosen variant only (the whole-line and cyclic-reduction kernels need none)
+    const size_t need = scratch_need(c.variant, n, nlines);
+    double *base = nullptr;
+    if (need > 0 && hipMalloc(&base, need * sizeof(double)) != hipSuccess) {
+        (void)hipGetLastError();
+        return afail(TF_ENOMEM, "scratch allocation failed");
     }
-    (void)hipFree(S.rel);
-    (void)hipFree(S.ext);
-    (void)hipFree(S.chain);
-    (void)hipFree(S.work);
+    tf_status st = sb_solve(c, transposed != 0, 0, nlines, n, bands, rhs, x, nullptr, scratch_at(base, n, nlines), s);
+    if (hipStreamSynchronize(s) != hipSuccess && st == TF_OK) st = afail(TF_EDEVICE, "synchronize failed");
+    (void)hipFree(base);
     return st;
 }
 
@@ -1184,13 +1194,8 @@ tf_status tf_penta_solve_noalloc(int nlines, int n, const double *bands, const d
     double *base = nullptr;
     tf_status st = noalloc_scratch(&base);
     if (st != TF_OK) return st;
-    const size_t recs = (size_t)tf::seg_count(n) * nlines;
-    Scratch S;
-    S.rel = base;
-    S.ext = base + recs * tf::NREL;
-    S.chain = base + recs * (tf::NREL + tf::NEXT);
-    S.work = base;
-    return sb_solve(c, transposed != 0, 0, nlines, n, bands, rhs, x, nullptr, S, (hipStream_t)stream);
+    return sb_solve(c, transposed != 0, 0, nlines, n, bands, rhs, x, nullptr, scratch_at(base, n, nlines),
+                    (hipStream_t)stream);
 }
 
 tf_status tf_autotune(int length, int batch, int transposed, const char *cache_path)

@@ -54,8 +54,9 @@ __device__ __forceinline__ void fold_right(Band &B, int pos) // pos: n-1 (0) or 
 
 // LU step at position k of a lane's sub-segment with the outer unknowns l1 = x_{p0-2},
 // l2 = x_{p0-1} kept symbolic (z: constant part, ph: coefficient of l1, ps: of l2); the
-// factors of every position stay in the arrays for the back-substitution.
-template <int CPL>
+// factors of every position stay in the arrays for the back-substitution. EXACT: the pivot's
+// reciprocal to the last bits (the stored-band solves, whose result is the answer itself).
+template <int CPL, bool EXACT = false>
 __device__ __forceinline__ void xr_elim(int k, const Band &B, double rhs, double (&fa)[CPL], double (&fb)[CPL],
                                         double (&fz)[CPL], double (&fph)[CPL], double (&fps)[CPL])
 {
@@ -67,7 +68,7 @@ __device__ __forceinline__ void xr_elim(int k, const Band &B, double rhs, double
     const double ps2 = k >= 2 ? fps[k - 2] : (k == 1 ? 1.0 : 0.0), ps1 = k >= 1 ? fps[k - 1] : 1.0;
     const double gam = B.b - B.a * al2;
     const double mu = B.c - B.a * be2 - gam * al1;
-    const double rm = rcp_pivot(mu);
+    const double rm = EXACT ? rcp(mu) : rcp_pivot(mu);
     fa[k] = (B.d - gam * be1) * rm;
     fb[k] = B.e * rm;
     fz[k] = (rhs - B.a * z2 - gam * z1) * rm;

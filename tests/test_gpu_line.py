@@ -59,6 +59,26 @@ def test_models_match_oracle(orc, model, theta, nx, ny):
     one(orc, nx, ny, theta, model)
 
 
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("n", EDGES + [2049, 3072, 3073, 4095, 4096])
+def test_stored_band_lines_match_oracle(orc, n, transposed):
+    """The whole-line stored-band solver with one line, one short of and one past a workgroup's lines
+    (diagonally dominant bands; the bound of the solver tests)."""
+    from paper_1806_10550_amd.lib import penta_solve
+    rng = np.random.default_rng(n)
+    for nl in (1, 3, 5):
+        bands = rng.standard_normal((5, n, nl))
+        bands[2] = 6.0 + rng.random((n, nl))
+        bands[0, :2] = bands[1, :1] = bands[3, n - 1:] = bands[4, n - 2:] = 0.0
+        rhs = rng.standard_normal((n, nl))
+        b, r = torch.from_numpy(bands).to(DEV), torch.from_numpy(rhs).to(DEV)
+        x = penta_solve(b, r, torch.empty_like(r), transposed=transposed, variant="line").cpu().numpy()
+        for l in range(nl):
+            band = np.ascontiguousarray(bands[:, :, l])
+            ref = orc.band_solve(orc.band_transpose(band) if transposed else band, rhs[:, l].copy())
+            assert np.max(np.abs(x[:, l] - ref)) <= 1e-12 * max(1.0, np.max(np.abs(ref))), (n, nl, l)
+
+
 def test_ensemble_of_every_line_class_equals_single_films():
     """One film per geometry class of the columns and rows (and one that takes tiles), bit for bit."""
     shapes = [(100, 90), (300, 60), (700, 400), (1500, 700), (60, 1300), (2500, 40), (4000, 24), (9, 2100)]
