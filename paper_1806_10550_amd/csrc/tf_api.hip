@@ -1,10 +1,11 @@
 // Host runtime and C ABI of libthinfilm (see include/thinfilm.h).
 //
 // The Newton / time-step control of Fig. FlowChartTime (Lam, Cummings & Kondic,
-// arXiv:1806.10550) runs on the host: after every iteration the kernels leave a
-// 64-byte reduction record {max|v/u_k|, max|G|, flags} on the device, which is copied
-// to pinned memory and read after one stream synchronisation (the paper's per-block
-// flag array reduced to a single record).
+// arXiv:1806.10550) runs on the host: after every iteration the kernels leave a reduction
+// record {max|v/u_k|, max|G|, flags} on the device, which a one-wave kernel combines into
+// pinned memory; the host reads it after one stream synchronisation (the paper's per-block
+// flag array reduced to a single record). Whole-line films run several iterations per
+// synchronisation (do_step).
 //
 // Buffer rotation: the accepted state u^n stays untouched while iterates alternate
 // between the two buffers that do not hold u^n (the caller's h is one of the three),
@@ -126,11 +127,14 @@ struct tf_grid {
     double *w = nullptr, *bn = nullptr, *rel = nullptr, *ext = nullptr, *chain = nullptr;
     double *partials = nullptr, *hpart = nullptr;
     double *mpart = nullptr;   // per x-solve tile mass records {s, c, min, -} of the last iterate
-    double *mout = nullptr;    // {sum, min} combined from mpart
+    // reduction slots and, behind them, the two control words of batched iterations; result words and
+    // {mass, min h} in pinned memory that the device writes
     unsigned long long *res = nullptr, *hres = nullptr;
+    unsigned long long epoch = 0;       // attempts so far (stop word of the current one)
+    int last_iters = 0;                 // Newton iterations of the last accepted attempt (batch size)
     int Px = 0, Py = 0;
     int xsweep = TF_XSWEEP_PARTITIONED; // x-sweep variant (TF_XSWEEP_*)
-    long iter = 0;
+    unsigned long long iter = 0;
     int successes = 0;
     double t = 0.0;
     bool state_ok = false;
@@ -194,13 +198,26 @@ tf::PassParams base_params(const tf_grid *g, double dt)
 // The y sweep takes whole columns wherever tf::yline_geom gives them.
 bool yline(const tf_grid *g) { return tf::yline_geom(tf::kernel_model(g->M), g->nx, g->ny).W > 0; }
 
+unsigned long long *control_words(const tf_grid *g) { return g->res + (size_t)RES_SLOTS * RES_STRIDE; }
+
 // One ADI-Newton iteration: y sweep (relations, chain, solve) into w, x sweep into
 // u_kp1. The reduction record of slot `slot` receives max|G| (y relations pass) and
 // max|v/u_k| and flags (x solve pass); slot (slot+2)%RES_SLOTS is cleared for later.
-tf_status enqueue_iteration(tf_grid *g, const double *bnp, const double *uk, double *ukp1, double dt, int slot,
-                            bool diag = false)
+// batch: the iteration may stand down on the device (whole-line sweeps; see PassParams::ctl);
+// check: it tests the previous iteration's record first. Advances g->iter.
+tf_status enqueue_iteration(tf_grid *g, const double *bnp, const double *uk, double *ukp1, double dt, bool diag = false,
+                            bool batch = false, bool check = false)
 {
+    const unsigned long long it = g->iter++;
+    const int slot = (int)(it % RES_SLOTS);
     tf::PassParams P = base_params(g, dt);
+    if (batch) {
+        P.ctl = control_words(g);
+        P.epoch = g->epoch;
+        P.it = it;
+        P.tol = g->S.tol;
+        P.chk = check ? g->res + (size_t)((slot + RES_SLOTS - 1) % RES_SLOTS) * RES_STRIDE : nullptr;
+    }
     P.u = uk;
     P.rel = g->rel;
     P.ext = g->ext;
@@ -247,26 +264,44 @@ tf_status enqueue_iteration(tf_grid *g, const double *bnp, const double *uk, dou
     return TF_OK;
 }
 
-tf_status read_result(tf_grid *g, int slot, double *e, double *r, int *flags)
+int x_tiles(const tf_grid *g) { return g->Px * ((g->ny + tf::TILE - 1) / tf::TILE); }
+// Mass records the x sweep leaves (one per x-solve tile or per wave of the whole-row kernel).
+int mass_records(const tf_grid *g)
 {
-    TF_HIP(hipMemcpyAsync(g->hres, g->res + (size_t)slot * RES_STRIDE, RES_STRIDE * sizeof(unsigned long long),
-                          hipMemcpyDeviceToHost, g->stream));
+    if (g->xsweep == TF_XSWEEP_ROW) return g->ny * tf::xline_geom(g->nx).W;
+    return x_tiles(g);
+}
+
+// Outcome of the iterations enqueued last, after one stream synchronisation: the record of the
+// iteration the device stopped at, else of the last one.
+struct Result {
+    bool stopped;
+    unsigned long long it;
+    double e, r, e_prev;
+    int flags;
+    double mass, hmin; // of that iterate (mass only)
+};
+tf_status read_result(tf_grid *g, bool batch, bool mass, Result *out)
+{
+    double *hm = reinterpret_cast<double *>(g->hres + 8);
+    if (mass) {
+        const tf_status st = timed(g, P_MASS, [&] { return tf::launch_mass_tiles(g->mpart, mass_records(g), hm, g->stream); });
+        if (st != TF_OK) return st;
+    }
+    TF_HIP(tf::launch_result(g->res, RES_SLOTS, batch ? control_words(g) : nullptr, g->epoch, g->iter - 1, g->hres,
+                             g->stream));
     TF_HIP(hipStreamSynchronize(g->stream));
     if (g->prof) prof_flush(g);
-    // combine the copies: maxima of non-negative doubles compare as their bit patterns
-    unsigned long long em = 0, rm = 0, fl = 0;
-    for (int c = 0; c < tf::RES_SPREAD; ++c) {
-        const unsigned long long *w = g->hres + (size_t)c * tf::RES_WORDS;
-        em = std::max(em, w[tf::RES_EMAX]);
-        rm = std::max(rm, w[tf::RES_RMAX]);
-        fl |= w[tf::RES_FLAGS];
-    }
-    double ev, rv;
-    std::memcpy(&ev, &em, sizeof(double));
-    std::memcpy(&rv, &rm, sizeof(double));
-    *e = ev;
-    *r = rv;
-    *flags = (int)fl;
+    const volatile unsigned long long *w = g->hres;
+    const unsigned long long e = w[2], r = w[3], ep = w[5];
+    out->stopped = w[0] != 0;
+    out->it = w[1];
+    std::memcpy(&out->e, &e, sizeof(double));
+    std::memcpy(&out->r, &r, sizeof(double));
+    std::memcpy(&out->e_prev, &ep, sizeof(double));
+    out->flags = (int)w[4];
+    out->mass = mass ? hm[0] : 0.0;
+    out->hmin = mass ? hm[1] : 0.0;
     return TF_OK;
 }
 
@@ -301,28 +336,6 @@ tf_status mass_of(tf_grid *g, const double *u, double *mass, double *hmin, bool 
     *mass = s + c;
     *hmin = m;
     if (nan) *nan = isn;
-    return TF_OK;
-}
-
-int x_tiles(const tf_grid *g) { return g->Px * ((g->ny + tf::TILE - 1) / tf::TILE); }
-// Mass records the x sweep leaves (one per x-solve tile or per wave of the whole-row kernel).
-int mass_records(const tf_grid *g)
-{
-    if (g->xsweep == TF_XSWEEP_ROW) return g->ny * tf::xline_geom(g->nx).W;
-    return x_tiles(g);
-}
-
-// Mass and minimum of the last iterate from the records its x solve left per tile (Sec.
-// "Conservation of Mass"), combined on the device in a fixed order: no extra read of h.
-tf_status fused_mass(tf_grid *g, double *mass, double *hmin)
-{
-    tf_status st = timed(g, P_MASS, [&] { return tf::launch_mass_tiles(g->mpart, mass_records(g), g->mout, g->stream); });
-    if (st != TF_OK) return st;
-    TF_HIP(hipMemcpyAsync(g->hpart, g->mout, 2 * sizeof(double), hipMemcpyDeviceToHost, g->stream));
-    TF_HIP(hipStreamSynchronize(g->stream));
-    if (g->prof) prof_flush(g);
-    *mass = g->hpart[0];
-    *hmin = g->hpart[1];
     return TF_OK;
 }
 
@@ -374,7 +387,7 @@ tf_status do_step(tf_grid *g, double *dt_inout, tf_step_info *info)
     if (st != TF_OK) return st;
     double *un = g->cur;
     int rejections = 0, total = 0, iters = 0;
-    double e = 0.0, r = 0.0;
+    double e = 0.0, r = 0.0, mass = 0.0, hmin = 0.0;
     tf_status status = TF_ENOCONV;
     for (;;) {
         const double *bnp = un;
@@ -384,21 +397,50 @@ tf_status do_step(tf_grid *g, double *dt_inout, tf_step_info *info)
         }
         double *uk = un;
         bool accepted = false;
-        for (iters = 1; iters <= g->S.max_newton; ++iters) {
-            double *dst = pick_buffer(g, un, uk);
-            const int slot = (int)(g->iter % RES_SLOTS);
-            if ((st = enqueue_iteration(g, bnp, uk, dst, dt, slot, info != nullptr && g->diag_mass)) != TF_OK)
-                return st;
-            g->iter++;
-            int flags = 0;
-            if ((st = read_result(g, slot, &e, &r, &flags)) != TF_OK) return st;
-            ++total;
-            if (flags != 0) break; // an iterate left the admissible set (h <= 0 or NaN)
-            uk = dst;
+        const bool diag = info != nullptr && g->diag_mass;
+        // Whole-line sweeps: iterations are enqueued in batches as long as the last attempt was (later
+        // ones as long as the convergence rate predicts) and those past the accepted one stand down
+        // on the device, so the host waits once per batch and not once per iteration (a third of the
+        // time at 128^2); the iterates and decisions are those of a test after every iteration.
+        // Per-launch timing takes one iteration at a time.
+        const bool batch = yline(g) && g->xsweep == TF_XSWEEP_ROW && !g->prof;
+        ++g->epoch;
+        int want = !batch ? 1 : (g->last_iters > 0 ? g->last_iters : 2);
+        iters = 0;
+        int bad = 0;
+        while (iters < g->S.max_newton) {
+            const int n = std::min(want, g->S.max_newton - iters);
+            const unsigned long long first = g->iter;
+            double *prev = uk;
+            for (int k = 0; k < n; ++k) {
+                double *dst = pick_buffer(g, un, uk);
+                if ((st = enqueue_iteration(g, bnp, uk, dst, dt, diag, batch, k > 0)) != TF_OK) return st;
+                prev = uk;
+                uk = dst;
+            }
+            Result R;
+            if ((st = read_result(g, batch, diag, &R)) != TF_OK) return st;
+            const int done = (int)(R.it - first) + 1;   // iterations that ran
+            if (done < n && (n - done) % 2 != 0) uk = prev; // the iterate of iteration R.it
+            g->iter = R.it + 1; // launches that stood down left their slots untouched
+            iters += done;
+            total += done;
+            e = R.e;
+            r = R.r;
+            mass = R.mass;
+            hmin = R.hmin;
+            bad = R.flags;
+            if (R.flags != 0) break; // an iterate left the admissible set (h <= 0 or NaN)
             if (e < g->S.tol) { accepted = true; break; }
+            const double rate = e / R.e_prev;
+            want = 1;
+            if (batch && iters > 1 && rate > 0.0 && rate < 1.0)
+                want = (int)std::min(8.0, std::max(1.0, std::ceil(std::log(g->S.tol / e) / std::log(rate))));
         }
+        if (!accepted && bad == 0) ++iters; // iterations exhausted: reported as one past the limit
         if (accepted) {
             g->cur = uk;
+            g->last_iters = iters;
             status = TF_OK;
             break;
         }
@@ -431,11 +473,9 @@ tf_status do_step(tf_grid *g, double *dt_inout, tf_step_info *info)
     }
     *dt_inout = dt;
     if (info && g->diag_mass) {
-        // the accepted state is the last iterate: its x solve left the mass records
-        double m, hm;
-        if ((st = fused_mass(g, &m, &hm)) != TF_OK) return st;
-        info->mass = m;
-        info->hmin = hm;
+        // the accepted state is the last iterate: its x sweep left the mass records
+        info->mass = mass;
+        info->hmin = hmin;
     }
     return TF_OK;
 }
@@ -491,20 +531,23 @@ tf_status tf_create(int nx, int ny, double ds, void *stream, tf_grid **out)
     }
     const size_t N = (size_t)nx * ny;
     const size_t lines_seg = std::max((size_t)g->Py * nx, (size_t)g->Px * ny);
+    // the small device arrays share one allocation: mass partials, mass records, reduction slots
+    const size_t nmass = (size_t)std::max(x_tiles(g), ny * tf::xline_geom(nx).W), nres = RES_SLOTS * RES_STRIDE + 2;
     bool ok = hipMalloc(&g->buf[0], N * sizeof(double)) == hipSuccess
               && hipMalloc(&g->buf[1], N * sizeof(double)) == hipSuccess
               && hipMalloc(&g->w, N * sizeof(double)) == hipSuccess
               && hipMalloc(&g->rel, lines_seg * tf::NREL * sizeof(double)) == hipSuccess
               && hipMalloc(&g->ext, lines_seg * tf::NEXT * sizeof(double)) == hipSuccess
               && hipMalloc(&g->chain, lines_seg * tf::NCHAIN * sizeof(double)) == hipSuccess
-              && hipMalloc(&g->partials, 4096 * 4 * sizeof(double)) == hipSuccess
-              && hipMalloc(&g->mpart, (size_t)std::max(x_tiles(g), ny * tf::xline_geom(nx).W)
-                                          * 4 * sizeof(double)) == hipSuccess
-              && hipMalloc(&g->mout, 2 * sizeof(double)) == hipSuccess
-              && hipMalloc(&g->res, RES_SLOTS * RES_STRIDE * sizeof(unsigned long long)) == hipSuccess
-              && hipHostMalloc(&g->hres, RES_STRIDE * sizeof(unsigned long long), hipHostMallocDefault) == hipSuccess
+              && hipMalloc(&g->partials, (4096 * 4 + nmass * 4) * sizeof(double) + nres * sizeof(unsigned long long))
+                     == hipSuccess
+              && hipHostMalloc(&g->hres, 16 * sizeof(unsigned long long), hipHostMallocDefault) == hipSuccess
               && hipHostMalloc(&g->hpart, 4096 * 4 * sizeof(double), hipHostMallocDefault) == hipSuccess;
-    if (ok) ok = hipMemsetAsync(g->res, 0, RES_SLOTS * RES_STRIDE * sizeof(unsigned long long), g->stream) == hipSuccess
+    if (ok) {
+        g->mpart = g->partials + 4096 * 4;
+        g->res = reinterpret_cast<unsigned long long *>(g->mpart + nmass * 4);
+    }
+    if (ok) ok = hipMemsetAsync(g->res, 0, nres * sizeof(unsigned long long), g->stream) == hipSuccess
                  && hipStreamSynchronize(g->stream) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
@@ -532,9 +575,6 @@ tf_status tf_destroy(tf_grid *g)
     (void)hipFree(g->ext);
     (void)hipFree(g->chain);
     (void)hipFree(g->partials);
-    (void)hipFree(g->mpart);
-    (void)hipFree(g->mout);
-    (void)hipFree(g->res);
     if (g->hres) (void)hipHostFree(g->hres);
     if (g->hpart) (void)hipHostFree(g->hpart);
     delete g;
@@ -732,10 +772,13 @@ tf_status tf_newton_iteration(tf_grid *g, const double *u_n, const double *u_k, 
         if ((st = rhs_theta(g, u_n, dt)) != TF_OK) return st;
         bnp = g->bn;
     }
-    const int slot = (int)(g->iter % RES_SLOTS);
-    if ((st = enqueue_iteration(g, bnp, u_k, u_kp1, dt, slot)) != TF_OK) return st;
-    g->iter++;
-    return read_result(g, slot, e, r, flags);
+    if ((st = enqueue_iteration(g, bnp, u_k, u_kp1, dt)) != TF_OK) return st;
+    Result R;
+    if ((st = read_result(g, false, false, &R)) != TF_OK) return st;
+    *e = R.e;
+    *r = R.r;
+    *flags = R.flags;
+    return TF_OK;
 }
 
 tf_status tf_flux_divergence(tf_grid *g, const double *u, double *out)

@@ -189,6 +189,15 @@ struct PassParams {
     unsigned long long *res_clear;  // slot zeroed by block 0 (may be null)
     int res_spread;                 // copies of the reduction record in a slot (>= 1)
     int tiles_x, tiles_y;
+    // Iterations enqueued in a batch (whole-line sweeps; ctl nullable): ctl[0] is the stop word. A
+    // launch that finds it equal to epoch does nothing; a y sweep that finds the previous iteration's
+    // record chk (nullable) accepted (max|v/u_k| < tol) or flagged does nothing either and sets
+    // ctl[1] = it - 1, that iteration, and ctl[0] = epoch. Every workgroup reads the same record, so
+    // all take the same decision.
+    const unsigned long long *chk;
+    unsigned long long *ctl;
+    unsigned long long epoch, it;
+    double tol;
     // x solve only, nullable: per tile (ty * tiles_x + tx) the compensated sum {s, c} and the
     // minimum of the u_{k+1} cells it writes (the mass diagnostic of the iterate, 4 doubles)
     double *mass;
@@ -284,6 +293,12 @@ hipError_t launch_flux_divergence(int nx, int ny, double ids, double ids2, const
 hipError_t launch_mass(const double *u, size_t n, double *partials, int nblocks, hipStream_t s);
 // Combine ntiles per-tile mass records {s, c, min, -} (PassParams::mass) in a fixed order into
 // out = {sum, min}.
+// The record of the iteration a batch ended with, combined over its copies, into host-visible memory
+// `out` (8 words): {stopped (ctl[0] == epoch), iteration, max|v/u_k|, max|G|, flags, max|v/u_k| of the
+// iteration before}. res: the slots (`slots` of them, iteration i in slot i % slots); last: the last
+// iteration enqueued, reported when the batch was not stopped.
+hipError_t launch_result(const unsigned long long *res, int slots, const unsigned long long *ctl,
+                         unsigned long long epoch, unsigned long long last, unsigned long long *out, hipStream_t s);
 hipError_t launch_mass_tiles(const double *part, int ntiles, double *out, hipStream_t s);
 hipError_t launch_pass_ens(int dir, bool solve, int km, const EnsParams &e, hipStream_t s);
 // b^n of every active film at the first iteration of an attempt (items: (film, tx, ty) over the

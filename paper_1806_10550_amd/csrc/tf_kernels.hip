@@ -910,6 +910,31 @@ __global__ void __launch_bounds__(256) k_mass(const double *u, size_t n, double 
 }
 
 
+// See launch_result. One wave, a lane per copy of the record.
+__global__ void __launch_bounds__(64) k_result(const unsigned long long *res, int slots, const unsigned long long *ctl,
+                                               unsigned long long epoch, unsigned long long last,
+                                               unsigned long long *out)
+{
+    static_assert(RES_SPREAD == 64, "one copy per lane");
+    const bool stopped = ctl != nullptr && ctl[0] == epoch;
+    const unsigned long long it = stopped ? ctl[1] : last;
+    const unsigned long long *w = res + ((it % slots) * RES_SPREAD + threadIdx.x) * RES_WORDS;
+    const unsigned long long *v = res + (((it + slots - 1) % slots) * RES_SPREAD + threadIdx.x) * RES_WORDS;
+    // the maxima are of non-negative doubles or carry a NaN-free flag beside them
+    const double e = wave_max(__longlong_as_double((long long)w[RES_EMAX]));
+    const double r = wave_max(__longlong_as_double((long long)w[RES_RMAX]));
+    const double ep = wave_max(__longlong_as_double((long long)v[RES_EMAX]));
+    const unsigned f = wave_or((unsigned)w[RES_FLAGS]);
+    if (threadIdx.x == 0) {
+        out[0] = stopped;
+        out[1] = it;
+        out[2] = (unsigned long long)__double_as_longlong(e);
+        out[3] = (unsigned long long)__double_as_longlong(r);
+        out[4] = f;
+        out[5] = (unsigned long long)__double_as_longlong(ep);
+    }
+}
+
 // Per-tile mass records of the x solve combined in a fixed order (strided per thread, then
 // a tree): out = {sum, min}.
 __global__ void __launch_bounds__(256) k_mass_tiles(const double *part, int ntiles, double *out)
@@ -1155,6 +1180,13 @@ int mass_blocks(size_t n)
 hipError_t launch_mass(const double *u, size_t n, double *partials, int nblocks, hipStream_t s)
 {
     k_mass<<<dim3(nblocks), dim3(256), 0, s>>>(u, n, partials);
+    return hipGetLastError();
+}
+
+hipError_t launch_result(const unsigned long long *res, int slots, const unsigned long long *ctl,
+                         unsigned long long epoch, unsigned long long last, unsigned long long *out, hipStream_t s)
+{
+    k_result<<<dim3(1), dim3(64), 0, s>>>(res, slots, ctl, epoch, last, out);
     return hipGetLastError();
 }
 

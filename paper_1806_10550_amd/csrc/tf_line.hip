@@ -47,6 +47,24 @@ LineGeom yline_geom(int km, int nx, int ny)
     return {16, (ny + 1023) / 1024};
 }
 
+// Whether this launch of a batch stands down (PassParams::ctl); the y sweep of an iteration decides
+// from the previous iteration's record, one copy per lane. Uniform over the launch.
+__device__ __forceinline__ bool stands_down(const PassParams &p, bool decide)
+{
+    if (p.ctl == nullptr) return false;
+    if (p.ctl[0] == p.epoch) return true;
+    if (!decide || p.chk == nullptr) return false;
+    const unsigned long long *w = p.chk + (size_t)(threadIdx.x & 63) * RES_WORDS;
+    const double e = wave_max(__longlong_as_double((long long)w[RES_EMAX]));
+    const unsigned f = wave_or((unsigned)w[RES_FLAGS]);
+    if (f == 0u && !(e < p.tol)) return false;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        p.ctl[1] = p.it - 1;
+        p.ctl[0] = p.epoch;
+    }
+    return true;
+}
+
 // ------------------------------------------------------------------------------------
 // x sweep of grid row j. sU, s2: the wave's LDS rows (ln_row, ln_row2 doubles). rec: index of the
 // wave's reduction copy and mass record.
@@ -87,6 +105,7 @@ __device__ __forceinline__ void xline_body(const PassParams &p, int j, int rec, 
             eu = uc[c];
             ex = us[c] + un[c];
         }
+        if (stands_down(p, false)) return;
 #pragma unroll
         for (int k = 0; k < CPL; ++k) s2[ln_at<CPL>(w0 + lane + 64 * k)] = vw[k];
         wave_lds_sync();
@@ -226,6 +245,9 @@ __device__ __forceinline__ void yline_body(const PassParams &p, int i0, int rec,
         }
 #pragma unroll
         for (int k = 0; k < KW; ++k) vb[k] = p.in2[(size_t)max(rb + RW * k - sh, 0) * nx + gb];
+        if (stands_down(p, true)) return;
+        if (p.res_clear != nullptr && blockIdx.x == 0)
+            for (int e = tid; e < p.res_spread * RES_WORDS; e += NT) p.res_clear[e] = 0ull;
 #pragma unroll
         for (int k = 0; k < KW; ++k) sU[cb * RB + ln_at<CPL>(rb + RW * k)] = vb[k];
         __syncthreads();
@@ -350,8 +372,6 @@ __global__ void __launch_bounds__(64 * LN_COLS * W) TF_LINE_ATTR(CPL) k_yline(Pa
 {
     __shared__ __align__(16) double sU[lny_u2(CPL, W)];
     __shared__ double bnd[W > 1 ? LN_COLS * W * LN_BND : 1];
-    if (p.res_clear != nullptr && blockIdx.x == 0)
-        for (int i = threadIdx.x; i < p.res_spread * RES_WORDS; i += 64 * LN_COLS * W) p.res_clear[i] = 0ull;
     const int b = xcd_tile(blockIdx.x, nblocks);
     yline_body<KM, CPL, W>(p, b * LN_COLS, b, sU, bnd);
 }
