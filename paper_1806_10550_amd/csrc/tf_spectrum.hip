@@ -1,15 +1,18 @@
 // Radial Fourier spectrum of a film (App. "Radial Fourier Transform"; see include/thinfilm.h,
 // tf_radial_spectrum and tf_spectrum_maxima).
 //
-// Device part (steps 1-4): the film minus H0 is transformed by an in-place 2D real-to-complex
-// FFT (hipFFT; half spectrum, the other half by conjugate symmetry); the magnitudes are
-// gathered into a window of the wavenumber plane that covers the disk
-// |k|^2 <= M plus the Gaussian's reach (indices taken modulo n, so the smoothing is the
-// periodic convolution over the whole plane); two separable passes smooth the window; one
-// thread per group m = kx^2 + ky^2 (all wavevectors of a group have the same |q|) sums its
-// smoothed values in a fixed order (an index of the window by group, built once per
-// window on the host), so spectra are bit-reproducible. Only the FFT touches all
-// n^2 values; the window holds (2 sqrt(M) + 2 r + 1)^2 values.
+// Device part (steps 1-4): the film minus H0 is transformed by hipFFT, in place and real to complex (half
+// spectrum, the other half by conjugate symmetry): the rows, then only the columns kx that the window
+// below reads, brought together by a transpose (a window of 5 q_m reads a twentieth to an eighth of the
+// columns of the paper's films; the full 2D transform runs when it reads more than half of the half
+// spectrum). The magnitudes are gathered into a window of the wavenumber plane that covers the disk
+// |k|^2 <= M plus the Gaussian's reach (indices taken modulo n, so the smoothing is the periodic
+// convolution over the whole plane); two separable passes smooth the window; the smoothed values of
+// each group m = kx^2 + ky^2 (all its wavevectors have the same |q|) are averaged in a fixed order (an
+// index of the window by group, built once per window on the host), so spectra are bit-reproducible.
+// Only the row transforms touch all n^2 values; the window holds (2 sqrt(M) + 2 r + 1)^2 values. Bound
+// by the row transforms: 2674^2 (a length with a prime factor 191) 173 of 383 us, where transforming every
+// column took another 185 and reading sums and counts of empty groups back to pageable memory 70.
 //
 // Host part (steps 5-7): the fit has about N/10 unknowns, the smoothed curve 400 points: a
 // tridiagonal normal-equation solve and a few passes over 400 doubles, done in plain C++.
@@ -38,11 +41,27 @@ __global__ void __launch_bounds__(256) k_spec_load(const double *__restrict__ h,
     buf[(size_t)j * pitch + i] = h[(size_t)j * n + i] - h0;
 }
 
+// T[c][j] = F[j][c] for the columns c < nc of the half spectrum (rows of pitch2 complex values), through
+// a 32 x 32 LDS tile.
+__global__ void __launch_bounds__(256) k_spec_columns(const hipfftDoubleComplex *__restrict__ F, int n, int pitch2,
+                                                      int nc, hipfftDoubleComplex *__restrict__ T)
+{
+    __shared__ hipfftDoubleComplex t[32][33];
+    const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32, x = threadIdx.x & 31, y = threadIdx.x >> 5;
+#pragma unroll
+    for (int r = y; r < 32; r += 8)
+        if (r0 + r < n && c0 + x < nc) t[r][x] = F[(size_t)(r0 + r) * pitch2 + c0 + x];
+    __syncthreads();
+#pragma unroll
+    for (int c = y; c < 32; c += 8)
+        if (c0 + c < nc && r0 + x < n) T[(size_t)(c0 + c) * n + r0 + x] = t[x][c];
+}
+
 // A[(wy + E) * W + (wx + E)] = |F(wx mod n, wy mod n)| / n^2 for wx, wy in [-E, E], from the
-// half spectrum F[iy][ix], ix <= n/2, of the real transform: the other half follows from
-// F(-k) = conj F(k).
-__global__ void __launch_bounds__(256) k_spec_window(const hipfftDoubleComplex *__restrict__ F, int n, int E,
-                                                     double inv_n2, double *__restrict__ A)
+// half spectrum of the real transform: the other half follows from F(-k) = conj F(k). Element (ix,
+// iy), ix <= n/2, at F[ix * sx + iy * sy].
+__global__ void __launch_bounds__(256) k_spec_window(const hipfftDoubleComplex *__restrict__ F, size_t sx, size_t sy,
+                                                     int n, int E, double inv_n2, double *__restrict__ A)
 {
     const int W = 2 * E + 1;
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
@@ -53,7 +72,7 @@ __global__ void __launch_bounds__(256) k_spec_window(const hipfftDoubleComplex *
         ix = n - ix;
         iy = (n - iy) % n;
     }
-    const hipfftDoubleComplex c = F[(size_t)iy * (n / 2 + 1) + ix];
+    const hipfftDoubleComplex c = F[ix * sx + iy * sy];
     A[t] = sqrt(c.x * c.x + c.y * c.y) * inv_n2;
 }
 
@@ -78,21 +97,22 @@ __global__ void __launch_bounds__(256) k_spec_smooth(const double *__restrict__ 
     out[t] = s;
 }
 
-// Group sums over the disk: S is the smoothed window of side 2R+1 centred on k = 0. One
-// thread per group m = kx^2 + ky^2 (0 <= m <= M) adds its wavevectors' values in the
-// order of the index (window positions sorted by group, then by position), so the sums
-// do not depend on scheduling.
+// Group means over the disk: S is the smoothed window of side 2R+1 centred on k = 0. SG lanes per
+// nonempty group of m = kx^2 + ky^2 (1 <= m <= M; a dozen wavevectors on average): lane i adds the values i,
+// i + SG, ... of the index (window positions sorted by group, then by position) and the lanes' sums are
+// added in a fixed tree, so the means do not depend on scheduling.
+constexpr int SG = 8;
 __global__ void __launch_bounds__(256) k_spec_groups(const double *__restrict__ S, const int *__restrict__ perm,
-                                                     const long long *__restrict__ off, long long M,
-                                                     double *__restrict__ sum, int *__restrict__ cnt)
+                                                     const int *__restrict__ off, int ng, double *__restrict__ mean)
 {
-    const long long m = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (m > M) return;
-    const long long b = off[m], e = off[m + 1];
+    const int t = blockIdx.x * blockDim.x + threadIdx.x, g = t / SG;
+    const bool live = g < ng;
+    const int b = live ? off[g] : 0, e = live ? off[g + 1] : 0;
     double acc = 0.0;
-    for (long long i = b; i < e; ++i) acc += S[perm[i]];
-    sum[m] = acc;
-    cnt[m] = (int)(e - b);
+    for (int i = b + t % SG; i < e; i += SG) acc += S[perm[i]];
+#pragma unroll
+    for (int o = SG / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o);
+    if (live && t % SG == 0) mean[g] = acc / (e - b);
 }
 
 } // namespace tf
@@ -105,20 +125,25 @@ tf_status sfail(tf_status s, const std::string &msg)
     return s;
 }
 
-// Plan and scratch of one (device, n), kept until tf_spectrum_release: the padded real /
+// Plans and scratch of one (device, n), kept until tf_spectrum_release: the padded real /
 // half-complex buffer of the in-place transform and the small window and group arrays
 // (grown on demand).
 struct SpecWork {
-    hipfftHandle plan = 0;
-    bool has_plan = false;
+    hipfftHandle full = 0, rows = 0;                // 2D transform; row transforms
+    bool has_full = false, has_rows = false;
+    std::map<int, hipfftHandle> cols;               // column transforms by batch (64, 128, 256, ...)
     double *buf = nullptr;
-    double *small = nullptr; // A | B | C | weights | sums, doubles
-    int *cnt = nullptr;
-    size_t small_cap = 0, cnt_cap = 0;
-    // index of the window by group for the last (M, R): perm lists window positions sorted
-    // by m = kx^2 + ky^2 (then by position), group m owns perm[off[m] .. off[m+1])
-    int *perm = nullptr;
-    long long *off = nullptr;
+    hipfftDoubleComplex *colbuf = nullptr;          // transposed columns
+    size_t col_cap = 0;
+    double *small = nullptr; // A | B | C | weights | means, doubles
+    size_t small_cap = 0;
+    double *hmean = nullptr; // pinned host copy of the means
+    size_t hmean_cap = 0;
+    // index of the window by group for the last (M, R): the nonempty groups in increasing m
+    // (gm), perm lists window positions sorted by m = kx^2 + ky^2 (then by position), group g owns
+    // perm[off[g] .. off[g+1])
+    int *perm = nullptr, *off = nullptr;
+    std::vector<int> gm, goff;
     long long idx_M = -1;
     int idx_R = -1;
 };
@@ -131,16 +156,19 @@ std::map<WorkKey, SpecWork> g_spec;
 
 void free_work(SpecWork &w)
 {
-    if (w.has_plan) (void)hipfftDestroy(w.plan);
+    if (w.has_full) (void)hipfftDestroy(w.full);
+    if (w.has_rows) (void)hipfftDestroy(w.rows);
+    for (auto &kv : w.cols) (void)hipfftDestroy(kv.second);
     if (w.buf) (void)hipFree(w.buf);
+    if (w.colbuf) (void)hipFree(w.colbuf);
     if (w.small) (void)hipFree(w.small);
-    if (w.cnt) (void)hipFree(w.cnt);
+    if (w.hmean) (void)hipHostFree(w.hmean);
     if (w.perm) (void)hipFree(w.perm);
     if (w.off) (void)hipFree(w.off);
     w = SpecWork{};
 }
 
-// The window index for groups 0..M over a window of half side R (n x n spectrum), built on
+// The window index for the groups 1..M over a window of half side R (n x n spectrum), built on
 // the host by a counting sort over m (positions in increasing order within a group) and kept
 // until the next call with another (M, R). Called with g_spec_mu held.
 tf_status get_index(SpecWork &w, int n, int R, long long M)
@@ -149,23 +177,29 @@ tf_status get_index(SpecWork &w, int n, int R, long long M)
     const int Wr = 2 * R + 1;
     const int lo = -(n / 2), hi = (n - 1) / 2;
     const long long npos = (long long)Wr * Wr;
-    std::vector<long long> off(M + 2, 0);
     auto group = [&](long long t) -> long long {
         const int kx = (int)(t % Wr) - R, ky = (int)(t / Wr) - R;
-        if (kx < lo || kx > hi || ky < lo || ky > hi) return -1;
+        if (kx < lo || kx > hi || ky < lo || ky > hi) return 0;
         const long long m = (long long)kx * kx + (long long)ky * ky;
-        return m <= M ? m : -1;
+        return m <= M ? m : 0;
     };
+    std::vector<int> at(M + 1, 0); // members, then the compact number, of each group
     for (long long t = 0; t < npos; ++t) {
         const long long m = group(t);
-        if (m >= 0) ++off[m + 1];
+        if (m > 0) ++at[m];
     }
-    for (long long m = 0; m <= M; ++m) off[m + 1] += off[m];
-    std::vector<int> perm((size_t)off[M + 1]);
-    std::vector<long long> next(off.begin(), off.end() - 1);
+    w.gm.clear();
+    w.goff.assign(1, 0);
+    for (long long m = 1; m <= M; ++m) {
+        if (at[m] == 0) continue;
+        w.goff.push_back(w.goff.back() + at[m]);
+        at[m] = (int)w.gm.size();
+        w.gm.push_back((int)m);
+    }
+    std::vector<int> perm((size_t)w.goff.back()), next(w.goff.begin(), w.goff.end() - 1);
     for (long long t = 0; t < npos; ++t) {
         const long long m = group(t);
-        if (m >= 0) perm[(size_t)next[m]++] = (int)t;
+        if (m > 0) perm[(size_t)next[at[m]]++] = (int)t;
     }
     if (w.perm) (void)hipFree(w.perm);
     if (w.off) (void)hipFree(w.off);
@@ -173,34 +207,70 @@ tf_status get_index(SpecWork &w, int n, int R, long long M)
     w.off = nullptr;
     w.idx_M = -1;
     if (hipMalloc(&w.perm, std::max<size_t>(perm.size(), 1) * sizeof(int)) != hipSuccess
-        || hipMalloc(&w.off, off.size() * sizeof(long long)) != hipSuccess) {
+        || hipMalloc(&w.off, w.goff.size() * sizeof(int)) != hipSuccess) {
         if (w.perm) (void)hipFree(w.perm);
         w.perm = nullptr;
         w.off = nullptr;
         return sfail(TF_ENOMEM, "spectrum index allocation failed");
     }
     if (hipMemcpy(w.perm, perm.data(), perm.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess
-        || hipMemcpy(w.off, off.data(), off.size() * sizeof(long long), hipMemcpyHostToDevice) != hipSuccess)
+        || hipMemcpy(w.off, w.goff.data(), w.goff.size() * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
         return sfail(TF_EDEVICE, "spectrum index upload failed");
     w.idx_M = M;
     w.idx_R = R;
     return TF_OK;
 }
 
-// Called with g_spec_mu held.
-tf_status get_work(int n, size_t small_doubles, size_t groups, SpecWork **out)
+// Batch of the column plan that covers nc columns.
+int col_batch(int nc)
+{
+    int b = 64;
+    while (b < nc) b *= 2;
+    return b;
+}
+
+// nc: columns of the half spectrum to transform, or 0 for the full 2D transform. Called with g_spec_mu
+// held.
+tf_status get_work(int n, size_t small_doubles, size_t groups, int nc, SpecWork **out)
 {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return sfail(TF_EDEVICE, "hipGetDevice failed");
     SpecWork &w = g_spec[WorkKey{dev, n}];
-    if (!w.has_plan) {
-        if (hipfftPlan2d(&w.plan, n, n, HIPFFT_D2Z) != HIPFFT_SUCCESS) return sfail(TF_EDEVICE, "hipfftPlan2d failed");
-        w.has_plan = true;
+    if (nc == 0 && !w.has_full) {
+        if (hipfftPlan2d(&w.full, n, n, HIPFFT_D2Z) != HIPFFT_SUCCESS) return sfail(TF_EDEVICE, "hipfftPlan2d failed");
+        w.has_full = true;
+    }
+    if (nc > 0 && !w.has_rows) {
+        int len = n, in = 2 * (n / 2 + 1), on = n / 2 + 1;
+        if (hipfftPlanMany(&w.rows, 1, &len, &in, 1, in, &on, 1, on, HIPFFT_D2Z, n) != HIPFFT_SUCCESS)
+            return sfail(TF_EDEVICE, "hipfftPlanMany (rows) failed");
+        w.has_rows = true;
+    }
+    if (nc > 0 && w.cols.find(col_batch(nc)) == w.cols.end()) {
+        int len = n;
+        hipfftHandle h = 0;
+        if (hipfftPlanMany(&h, 1, &len, &len, 1, n, &len, 1, n, HIPFFT_Z2Z, col_batch(nc)) != HIPFFT_SUCCESS)
+            return sfail(TF_EDEVICE, "hipfftPlanMany (columns) failed");
+        w.cols[col_batch(nc)] = h;
     }
     if (w.buf == nullptr
         && hipMalloc(&w.buf, (size_t)n * (n / 2 + 1) * sizeof(hipfftDoubleComplex)) != hipSuccess) {
         w.buf = nullptr;
         return sfail(TF_ENOMEM, "spectrum buffer allocation failed");
+    }
+    const size_t col_need = nc > 0 ? (size_t)col_batch(nc) * n : 0;
+    if (w.col_cap < col_need) {
+        if (w.colbuf) (void)hipFree(w.colbuf);
+        w.colbuf = nullptr;
+        w.col_cap = 0;
+        if (hipMalloc(&w.colbuf, col_need * sizeof(hipfftDoubleComplex)) != hipSuccess) {
+            w.colbuf = nullptr;
+            return sfail(TF_ENOMEM, "spectrum buffer allocation failed");
+        }
+        w.col_cap = col_need;
+        // columns past the ones asked for are transformed with the rest of the batch: finite values
+        if (hipMemset(w.colbuf, 0, col_need * sizeof(hipfftDoubleComplex)) != hipSuccess)
+            return sfail(TF_EDEVICE, "spectrum buffer setup failed");
     }
     if (w.small_cap < small_doubles) {
         if (w.small) (void)hipFree(w.small);
@@ -212,15 +282,15 @@ tf_status get_work(int n, size_t small_doubles, size_t groups, SpecWork **out)
         }
         w.small_cap = small_doubles;
     }
-    if (w.cnt_cap < groups) {
-        if (w.cnt) (void)hipFree(w.cnt);
-        w.cnt = nullptr;
-        w.cnt_cap = 0;
-        if (hipMalloc(&w.cnt, groups * sizeof(int)) != hipSuccess) {
-            w.cnt = nullptr;
-            return sfail(TF_ENOMEM, "spectrum scratch allocation failed");
+    if (w.hmean_cap < groups) {
+        if (w.hmean) (void)hipHostFree(w.hmean);
+        w.hmean = nullptr;
+        w.hmean_cap = 0;
+        if (hipHostMalloc(&w.hmean, groups * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+            w.hmean = nullptr;
+            return sfail(TF_ENOMEM, "spectrum host buffer allocation failed");
         }
-        w.cnt_cap = groups;
+        w.hmean_cap = groups;
     }
     *out = &w;
     return TF_OK;
@@ -264,46 +334,57 @@ tf_status tf_radial_spectrum(const double *h, int n, double ds, double h0, doubl
         for (double &v : w) v /= z;
     }
     hipStream_t s = (hipStream_t)stream;
-    // small scratch: A (W x W) | B (Wr x W) | C (Wr x Wr) | weights | group sums
+    // small scratch: A (W x W) | B (Wr x W) | C (Wr x Wr) | weights | group means
     const size_t oA = 0, oB = oA + (size_t)W * W, oC = oB + (size_t)W * Wr, oW = oC + (size_t)Wr * Wr,
                  oS = oW + w.size(), small = oS + (size_t)(M + 1);
     std::lock_guard<std::mutex> lk(g_spec_mu);
+    // the columns 0 .. E (and their mirror images) are all the window reads
+    const int nc = 2 * (E + 1) <= n / 2 + 1 ? E + 1 : 0;
     SpecWork *wk;
-    tf_status st = get_work(n, small, (size_t)(M + 1), &wk);
+    tf_status st = get_work(n, small, (size_t)(M + 1), nc, &wk);
     if (st != TF_OK) return st;
     if ((st = get_index(*wk, n, R, M)) != TF_OK) return st;
+    const int ng = (int)wk->gm.size();
     StreamDrain drain{s};
     double *A = wk->small + oA, *B = wk->small + oB, *C = wk->small + oC, *wd = wk->small + oW,
-           *sum = wk->small + oS;
+           *mean = wk->small + oS;
     const int pitch = 2 * (n / 2 + 1);
+    if (hipMemcpyAsync(wd, w.data(), w.size() * sizeof(double), hipMemcpyHostToDevice, s) != hipSuccess)
+        return sfail(TF_EDEVICE, "spectrum scratch setup failed");
     tf::k_spec_load<<<dim3((n + 255) / 256, n), 256, 0, s>>>(h, h0, n, pitch, wk->buf);
     if (hipGetLastError() != hipSuccess) return sfail(TF_EDEVICE, "spectrum load launch failed");
     auto *F = (hipfftDoubleComplex *)wk->buf;
-    if (hipfftSetStream(wk->plan, s) != HIPFFT_SUCCESS || hipfftExecD2Z(wk->plan, wk->buf, F) != HIPFFT_SUCCESS)
+    const hipfftHandle first = nc > 0 ? wk->rows : wk->full;
+    if (hipfftSetStream(first, s) != HIPFFT_SUCCESS || hipfftExecD2Z(first, wk->buf, F) != HIPFFT_SUCCESS)
         return sfail(TF_EDEVICE, "hipfftExecD2Z failed");
-    if (hipMemcpyAsync(wd, w.data(), w.size() * sizeof(double), hipMemcpyHostToDevice, s) != hipSuccess)
-        return sfail(TF_EDEVICE, "spectrum scratch setup failed");
+    size_t sx = 1, sy = n / 2 + 1;
+    if (nc > 0) {
+        tf::k_spec_columns<<<dim3((nc + 31) / 32, (n + 31) / 32), 256, 0, s>>>(F, n, n / 2 + 1, nc, wk->colbuf);
+        if (hipGetLastError() != hipSuccess) return sfail(TF_EDEVICE, "spectrum transpose launch failed");
+        const hipfftHandle col = wk->cols[col_batch(nc)];
+        F = wk->colbuf;
+        if (hipfftSetStream(col, s) != HIPFFT_SUCCESS || hipfftExecZ2Z(col, F, F, HIPFFT_FORWARD) != HIPFFT_SUCCESS)
+            return sfail(TF_EDEVICE, "hipfftExecZ2Z failed");
+        sx = n;
+        sy = 1;
+    }
     const double inv_n2 = 1.0 / ((double)n * (double)n);
-    tf::k_spec_window<<<(W * W + 255) / 256, 256, 0, s>>>(F, n, E, inv_n2, A);
+    tf::k_spec_window<<<(W * W + 255) / 256, 256, 0, s>>>(F, sx, sy, n, E, inv_n2, A);
     tf::k_spec_smooth<0><<<(Wr * W + 255) / 256, 256, 0, s>>>(A, W, W, wd, r, B);
     tf::k_spec_smooth<1><<<(Wr * Wr + 255) / 256, 256, 0, s>>>(B, Wr, W, wd, r, C);
-    tf::k_spec_groups<<<(unsigned)((M + 1 + 255) / 256), 256, 0, s>>>(C, wk->perm, wk->off, M, sum, wk->cnt);
+    tf::k_spec_groups<<<(unsigned)(((size_t)ng * tf::SG + 255) / 256), 256, 0, s>>>(C, wk->perm, wk->off, ng, mean);
     if (hipGetLastError() != hipSuccess) return sfail(TF_EDEVICE, "spectrum kernel launch failed");
-    std::vector<double> hs(M + 1);
-    std::vector<int> hc(M + 1);
-    if (hipMemcpyAsync(hs.data(), sum, (M + 1) * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess
-        || hipMemcpyAsync(hc.data(), wk->cnt, (M + 1) * sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess
+    if (hipMemcpyAsync(wk->hmean, mean, ng * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess
         || hipStreamSynchronize(s) != hipSuccess)
         return sfail(TF_EDEVICE, "spectrum readback failed");
     int np = 0;
-    for (long long m = 1; m <= M; ++m) {
-        if (hc[m] == 0) continue;
-        const double q = 2.0 * M_PI * std::sqrt((double)m) / L;
+    for (int g = 0; g < ng; ++g) {
+        const double q = 2.0 * M_PI * std::sqrt((double)wk->gm[g]) / L;
         if (q > qmax) continue;
         if (np < capacity && q_out != nullptr && s_out != nullptr) {
             q_out[np] = q;
-            s_out[np] = hs[m] / hc[m];
-            if (count_out != nullptr) count_out[np] = hc[m];
+            s_out[np] = wk->hmean[g];
+            if (count_out != nullptr) count_out[np] = wk->goff[g + 1] - wk->goff[g];
         }
         ++np;
     }
