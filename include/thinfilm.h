@@ -278,8 +278,8 @@ tf_status tf_jacobian_apply_t(tf_grid *g, const double *u, const double *mu, dou
  * needed) or qmax spans more than 2^26 groups. Each group's sum is formed in a fixed order, so
  * the output is bit-reproducible. Work is enqueued on `stream` (hipStream_t, NULL = default)
  * and the call returns after it has finished. The FFT plan and device scratch (8 n (n + 2)
- * bytes, 16 n bytes per transformed column of the window, the smoothing window, the group sums and an index of the window by group, about
- * 4 pi M bytes) are kept per (device, n) for later calls until tf_spectrum_release; calls are
+ * bytes, 16 n bytes per transformed column of the window, the smoothing window, the group
+ * means and an index of the window by group, about 4 pi M bytes) are kept per (device, n) for later calls until tf_spectrum_release; calls are
  * serialised by a lock. */
 tf_status tf_radial_spectrum(const double *h, int n, double ds, double h0, double sigma, double qmax, void *stream,
                              double *q_out, double *s_out, int *count_out, int capacity, int *npoints);

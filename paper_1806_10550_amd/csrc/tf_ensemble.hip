@@ -44,7 +44,7 @@ struct tf_ensemble {
     long long ncells = 0, nrec = 0;
     // work lists of one iteration (build_items), each a range of d_items
     struct Range { size_t off = 0; int n = 0; };
-    Range ty, tx, cy, cx, bnt, yl[tf::N_YL], xl[tf::N_XL];
+    Range ty, tx, cy, cx, bnt, yl[tf::YL_MAXW], xl[tf::XL_MAXW];
     tf::FilmDesc *d_desc = nullptr;
     tf::FilmState *d_state = nullptr, *h_state = nullptr;
     int *d_items = nullptr;
@@ -90,15 +90,15 @@ tf_status enqueue_iteration(tf_ensemble *e)
         TF_EHIP(tf::launch_chain_ens(params(e, e->cy), 0, e->stream));
         TF_EHIP(tf::launch_pass_ens(0, true, e->km, params(e, e->ty), e->stream));
     }
-    for (int c = 0; c < tf::N_YL; ++c)
-        if (e->yl[c].n > 0) TF_EHIP(tf::launch_line_ens(0, tf::YL_CLASSES[c], e->km, params(e, e->yl[c]), e->stream));
+    for (int W = 1; W <= tf::YL_MAXW; ++W)
+        if (e->yl[W - 1].n > 0) TF_EHIP(tf::launch_line_ens(0, W, e->km, params(e, e->yl[W - 1]), e->stream));
     if (e->tx.n > 0) {
         TF_EHIP(tf::launch_pass_ens(1, false, e->km, params(e, e->tx), e->stream));
         TF_EHIP(tf::launch_chain_ens(params(e, e->cx), 1, e->stream));
         TF_EHIP(tf::launch_pass_ens(1, true, e->km, params(e, e->tx), e->stream));
     }
-    for (int c = 0; c < tf::N_XL; ++c)
-        if (e->xl[c].n > 0) TF_EHIP(tf::launch_line_ens(1, tf::XL_CLASSES[c], e->km, params(e, e->xl[c]), e->stream));
+    for (int W = 1; W <= tf::XL_MAXW; ++W)
+        if (e->xl[W - 1].n > 0) TF_EHIP(tf::launch_line_ens(1, W, e->km, params(e, e->xl[W - 1]), e->stream));
     TF_EHIP(tf::launch_ens_control(e->d_state, e->nfilms, S, e->d_active, e->stream));
     return TF_OK;
 }
@@ -128,11 +128,20 @@ tf_status ensure_graph(tf_ensemble *e)
     return TF_OK;
 }
 
-int line_class(const tf::LineGeom &g, const tf::LineGeom *classes, int n)
+// A line list in launch order: runs of LINE_RUN neighbouring items stay on one XCD (blocks are dispatched
+// round-robin over 8), so that they share halo rows and partly written lines in its L2, and the runs go
+// round the XCDs in turn, the costliest films (sorted first) included. Padded with film -1.
+constexpr size_t LINE_RUN = 16, LINE_XCDS = 8;
+std::vector<int> spread_lines(const std::vector<int> &v)
 {
-    for (int c = 0; c < n; ++c)
-        if (classes[c].cpl == g.cpl && classes[c].W == g.W) return c;
-    return -1;
+    const size_t n = v.size() / 3, group = LINE_RUN * LINE_XCDS, padded = (n + group - 1) / group * group;
+    std::vector<int> out(3 * padded, -1);
+    for (size_t i = 0; i < n; ++i) {
+        const size_t run = i / LINE_RUN, k = i % LINE_RUN;
+        const size_t at = run / LINE_XCDS * group + k * LINE_XCDS + run % LINE_XCDS;
+        std::copy(v.begin() + 3 * i, v.begin() + 3 * i + 3, out.begin() + 3 * at);
+    }
+    return out;
 }
 
 // Work lists of one iteration: the y sweep of a film is whole-column where tf::yline_geom gives a
@@ -140,23 +149,24 @@ int line_class(const tf::LineGeom &g, const tf::LineGeom *classes, int n)
 // and chain blocks. The b^n list covers every film.
 void build_items(tf_ensemble *e, std::vector<int> &items)
 {
-    std::vector<int> ty, tx, cy, cx, bnt, yl[tf::N_YL], xl[tf::N_XL];
+    std::vector<int> ty, tx, cy, cx, bnt, yl[tf::YL_MAXW], xl[tf::XL_MAXW];
     for (int f = 0; f < e->nfilms; ++f) {
         const tf::FilmDesc &d = e->desc[f];
-        const int yc = line_class(tf::yline_geom(e->km, d.nx, d.ny), tf::YL_CLASSES, tf::N_YL);
-        const int xc = e->xsweep[f] == 1 ? line_class(tf::xline_geom(d.nx), tf::XL_CLASSES, tf::N_XL) : -1;
+        const tf::LineGeom yg = tf::yline_geom(e->km, d.nx, d.ny), xg = e->xsweep[f] == 1 ? tf::xline_geom(d.nx)
+                                                                                         : tf::LineGeom{0, 0};
         const int tyx = (d.nx + tf::TILE - 1) / tf::TILE, txy = (d.ny + tf::TILE - 1) / tf::TILE;
         for (int j = 0; j < tf::bn_tiles_y(d.ny); ++j)
             for (int i = 0; i < tf::bn_tiles_x(d.nx); ++i) bnt.insert(bnt.end(), {f, i, j});
-        if (yc >= 0) {
-            for (int b = 0; b < (d.nx + tf::LN_COLS - 1) / tf::LN_COLS; ++b) yl[yc].insert(yl[yc].end(), {f, b});
+        if (yg.W > 0) {
+            for (int b = 0; b < (d.nx + tf::LN_COLS - 1) / tf::LN_COLS; ++b)
+                yl[yg.W - 1].insert(yl[yg.W - 1].end(), {f, b, yg.cpl});
         } else {
             for (int j = 0; j < d.Py; ++j)
                 for (int i = 0; i < tyx; ++i) ty.insert(ty.end(), {f, i, j});
             for (int b = 0; b < (d.nx + 63) / 64; ++b) cy.insert(cy.end(), {f, b});
         }
-        if (xc >= 0) {
-            for (int j = 0; j < d.ny; ++j) xl[xc].insert(xl[xc].end(), {f, j});
+        if (xg.W > 0) {
+            for (int j = 0; j < d.ny; ++j) xl[xg.W - 1].insert(xl[xg.W - 1].end(), {f, j, xg.cpl});
         } else {
             for (int j = 0; j < txy; ++j)
                 for (int i = 0; i < d.Px; ++i) tx.insert(tx.end(), {f, i, j});
@@ -169,13 +179,21 @@ void build_items(tf_ensemble *e, std::vector<int> &items)
         r.n = (int)(v.size() / per);
         items.insert(items.end(), v.begin(), v.end());
     };
+    // line items: the films with most positions per lane first (stable: a film's items stay in order)
+    auto put_lines = [&](tf_ensemble::Range &r, std::vector<int> &v) {
+        std::vector<int> w;
+        for (int cpl = 16; cpl >= 4; cpl -= 2)
+            for (size_t i = 0; i < v.size(); i += 3)
+                if (v[i + 2] == cpl) w.insert(w.end(), v.begin() + i, v.begin() + i + 3);
+        put(r, spread_lines(w), 3);
+    };
     put(e->ty, ty, 3);
     put(e->tx, tx, 3);
     put(e->bnt, bnt, 3);
     put(e->cy, cy, 2);
     put(e->cx, cx, 2);
-    for (int c = 0; c < tf::N_YL; ++c) put(e->yl[c], yl[c], 2);
-    for (int c = 0; c < tf::N_XL; ++c) put(e->xl[c], xl[c], 2);
+    for (auto W = 0; W < tf::YL_MAXW; ++W) put_lines(e->yl[W], yl[W]);
+    for (auto W = 0; W < tf::XL_MAXW; ++W) put_lines(e->xl[W], xl[W]);
 }
 
 tf_status upload_items(tf_ensemble *e)
@@ -217,9 +235,10 @@ size_t max_items(const tf_ensemble *e)
     for (const auto &d : e->desc) {
         const size_t yt = (size_t)d.Py * ((d.nx + tf::TILE - 1) / tf::TILE);
         n += 3 * yt + 3 * (size_t)tf::bn_tiles_x(d.nx) * tf::bn_tiles_y(d.ny);
-        n += 2 * (size_t)((d.nx + 63) / 64) + 2 * (size_t)((d.nx + tf::LN_COLS - 1) / tf::LN_COLS);
-        n += 3 * (size_t)((d.ny + tf::TILE - 1) / tf::TILE) * d.Px + 2 * (size_t)((d.ny + 63) / 64) + 2 * (size_t)d.ny;
+        n += 2 * (size_t)((d.nx + 63) / 64) + 3 * (size_t)((d.nx + tf::LN_COLS - 1) / tf::LN_COLS);
+        n += 3 * (size_t)((d.ny + tf::TILE - 1) / tf::TILE) * d.Px + 2 * (size_t)((d.ny + 63) / 64) + 3 * (size_t)d.ny;
     }
+    n += 3 * LINE_RUN * LINE_XCDS * (tf::YL_MAXW + tf::XL_MAXW); // padding of the line lists
     return n;
 }
 

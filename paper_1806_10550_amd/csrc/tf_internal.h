@@ -75,8 +75,8 @@ __host__ __device__ inline XRowGeom xrow_geom(int nx)
     return g;
 }
 
-// Whole lines across the lanes of one or several waves (tf_line.hip): LN_CPL consecutive positions
-// per lane (4, 8 or 16), W waves per line, right-aligned: slot s (64 wave + lane) owns the
+// Whole lines across the lanes of one or several waves (tf_line.hip): CPL consecutive positions
+// per lane (an even number, 4 to 16), W waves per line, right-aligned: slot s (64 wave + lane) owns the
 // positions w = CPL s + k, cell q = w - sh with sh = 64 W CPL - n < 64 CPL; positions before the
 // line (w < sh, in the first wave) hold copies of its first cells and are decoupled from it.
 constexpr int LN_MAXW = 8;                    // waves of the longest line
@@ -266,10 +266,8 @@ struct LineGeom {
 };
 LineGeom xline_geom(int nx);
 LineGeom yline_geom(int km, int nx, int ny); // km: KernelModel
-// the classes an ensemble's films fall into (rows of at most XR_ROW4_MAX_NX cells)
-constexpr LineGeom YL_CLASSES[] = {{4, 1}, {8, 1}, {16, 1}, {16, 2}};
-constexpr LineGeom XL_CLASSES[] = {{4, 1}, {8, 1}, {16, 1}, {16, 2}, {16, 3}, {16, 4}};
-constexpr int N_YL = 4, N_XL = 6;
+// an ensemble's films share one launch per number of waves per line (rows of at most XR_ROW4_MAX_NX cells)
+constexpr int YL_MAXW = 2, XL_MAXW = 4;
 hipError_t launch_line(int dir, const PassParams &p, hipStream_t s);
 // Stored-band solves of whole lines (4 ..= XR_ROW4_MAX_NX cells) in one kernel: pm true
 // position-major (plain or transposed; mode 0 out = x, mode 1 out += x with the maxima in
@@ -282,9 +280,9 @@ hipError_t launch_sbline(bool trans, bool pm, int mode, int nl, int np, const do
 // x-sweep variant for a film of nx x ny cells (0: partitioned, 1: whole-row): the autotuned
 // choice for the nearest shape, else the built-in rule (tf_adjoint.hip).
 int xsweep_choice(int nx, int ny);
-// The same over an ensemble's films of one geometry class (items: (film, block): four columns or
-// one row); km: the KernelModel every film shares.
-hipError_t launch_line_ens(int dir, const LineGeom &g, int km, const EnsParams &e, hipStream_t s);
+// The same over an ensemble's films with W waves per line (items: (film, block of four columns or row,
+// positions per lane), film -1: none); km: the KernelModel every film shares.
+hipError_t launch_line_ens(int dir, int W, int km, const EnsParams &e, hipStream_t s);
 hipError_t launch_model_coeffs(const Model &M, const double *h, int n, double *out, hipStream_t s);
 hipError_t launch_chain(const ChainParams &c, hipStream_t s);
 hipError_t launch_flux_divergence(int nx, int ny, double ids, double ids2, const Model &M,

@@ -1,39 +1,25 @@
-// Whole-line sweeps of the ADI-Newton iteration (gfx950, FP64;
-// Lam, Cummings & Kondic, arXiv:1806.10550, eqs. JacobianSystem1-3, NewtonError): one kernel per
-// sweep, one wave per line (core and layout: tf_line.h, tf_internal.h).
-//
-//   k_xline  x sweep: a wave holds one grid row; everything it touches in LDS is its own, so there
-//            is no barrier at all. Reads u_k (the row and its two neighbours) and w once, writes
-//            u_{k+1} once.
-//   k_yline  y sweep: a workgroup holds four neighbouring columns, one per wave, and stages their
-//            u tile (two columns more on each side) and b^n with coalesced loads; each wave forms
-//            the residual and the bands of its column and solves it; w goes out through LDS in
-//            32-byte row pieces. Reads u_k and b^n, writes w.
-//
-// What bounds them: at small sizes the latency of one wave's serial elimination, reduction and
-// memory round trips (x + y of 128^2: 8 + 10 us; 512^2: 11 + 14 us; the same sweeps by tile passes
-// and record tree took 25 + 35 and 23 + 35 us), at large ones the FP64 issue rate at two waves per
-// SIMD (1000 rows x 8192 cells: 68 us, 2.9 TB/s of the 24 B per cell; 8192 columns of 1000: 94 us
-// against 141 us for the partitioned passes). The waves of different lines share nothing, so the
-// loads of one line overlap the arithmetic of others.
-#include "tf_line.h"
+// Whole-line sweep kernels of one film (bodies: tf_line_body.h) and the geometry rules they share with the
+// ensemble's (tf_line_ens.hip).
+#include "tf_line_body.h"
 
 namespace tf {
 
 bool xrow_supported(int nx) { return nx >= 4 && nx <= XR_MAX_NX; }
 
-// Positions per lane and waves per line. Short lines take few positions per lane: the elimination
-// is a serial chain over them and these launches do not fill the GPU (128^2 and 512^2: 8 and 11 us a
-// sweep, where 16 positions per lane took 29 and 23). Longer ones take 16, whose cyclic reduction
-// costs half as much per cell as with 8 (rows of 1000 cells, 8192 of them: 68 against 89 us; 4096^2:
-// 164 against 263). The partitioned x sweep takes longer at every length and number of rows
-// (2048^2: 87 against 52 us, 8192 rows of 4096: 485 against 344).
+// Positions per lane and waves per line: as few waves as hold the line with 16 positions per lane, then the
+// fewest positions (an even number) that hold it with those. Few positions make short lines fast: the
+// elimination is a serial chain over them and small launches do not fill the GPU (128^2 and 512^2: 8 and
+// 11 us a sweep with 4 and 8, where 16 took 29 and 23). For long lines 16 positions in few waves beat 8 in
+// twice as many, whose cyclic reduction costs twice as much per cell (rows of 1000 cells, 8192 of them: 68
+// against 89 us; 4096^2: 164 against 263). Lengths between the powers of two leave no lanes
+// idle (600^2: 35 -> 27 us for both sweeps, 3001 x 700 polymer 74 -> 60). The partitioned x sweep takes longer at every length and number of rows (2048^2: 87
+// against 52 us, 8192 rows of 4096: 485 against 344).
+static int line_positions(int n, int W) { return W > 4 ? 16 : (n <= 256 ? 4 : 2 * ((n + 128 * W - 1) / (128 * W))); }
 LineGeom xline_geom(int nx)
 {
     if (!xrow_supported(nx)) return {0, 0};
-    if (nx <= 256) return {4, 1};
-    if (nx <= 512) return {8, 1};
-    return {16, (nx + 1023) / 1024};
+    const int W = (nx + 1023) / 1024;
+    return {line_positions(nx, W), W};
 }
 // Columns of more than 1024 cells need a workgroup of 8 waves and 135 KB of LDS, one per CU, that
 // overlaps nothing: with many of them the partitioned passes stream better (8192 x 2048: 268 against
@@ -42,320 +28,14 @@ LineGeom xline_geom(int nx)
 LineGeom yline_geom(int km, int nx, int ny)
 {
     if (ny < 4 || ny > 2048 || (ny > 1024 && (nx > 4096 || km == KM_NLC))) return {0, 0};
-    if (ny <= 256) return {4, 1};
-    if (ny <= 512) return {8, 1};
-    return {16, (ny + 1023) / 1024};
+    const int W = (ny + 1023) / 1024;
+    return {line_positions(ny, W), W};
 }
 
-// Whether this launch of a batch stands down (PassParams::ctl); the y sweep of an iteration decides
-// from the previous iteration's record, one copy per lane. Uniform over the launch.
-__device__ __forceinline__ bool stands_down(const PassParams &p, bool decide)
-{
-    if (p.ctl == nullptr) return false;
-    if (p.ctl[0] == p.epoch) return true;
-    if (!decide || p.chk == nullptr) return false;
-    const unsigned long long *w = p.chk + (size_t)(threadIdx.x & 63) * RES_WORDS;
-    const double e = wave_max(__longlong_as_double((long long)w[RES_EMAX]));
-    const unsigned f = wave_or((unsigned)w[RES_FLAGS]);
-    if (f == 0u && !(e < p.tol)) return false;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        p.ctl[1] = p.it - 1;
-        p.ctl[0] = p.epoch;
-    }
-    return true;
-}
-
-// ------------------------------------------------------------------------------------
-// x sweep of grid row j. sU, s2: the wave's LDS rows (ln_row, ln_row2 doubles). rec: index of the
-// wave's reduction copy and mass record.
-// ------------------------------------------------------------------------------------
-template <int KM, int CPL, bool MW>
-__device__ __forceinline__ void xline_body(const PassParams &p, int j, int rec, int W, double *sU, double *s2,
-                                           double *bnd)
-{
-    const int nx = p.nx, ny = p.ny;
-    const int lane = threadIdx.x & 63;
-    const int wv = MW ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0; // wave of the line
-    const int w0 = 64 * CPL * wv;                                             // its first position
-    const int sh = 64 * CPL * W - nx;
-    double *const priv = s2 + (size_t)wv * ln_priv(CPL);
-    const double ka = p.ka;
-    const double *uc = p.u + (size_t)j * nx;
-    const double *un = p.u + (size_t)crefl(j - 1, ny) * nx;
-    const double *us = p.u + (size_t)crefl(j + 1, ny) * nx;
-    const double *wrow = p.in2 + (size_t)j * nx;
-    // stage w through the second row (each lane then takes its own CPL positions), u(j) and
-    // u(j-1) + u(j+1); positions before the line repeat its first cells
-    double wr[CPL];
-    {
-        double vu[CPL], vx[CPL], vw[CPL], eu = 0.0, ex = 0.0;
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) {
-            const int q = w0 + lane + 64 * k - sh;
-            vw[k] = wrow[max(q, 0)];
-            const int c = q >= 0 ? q : -1 - max(q, -2);
-            vu[k] = uc[c];
-            vx[k] = us[c] + un[c];
-        }
-        // the two positions on each side of the line's span: w = -2, -1 and 64 W CPL + 0, 1
-        const int we = lane < 2 ? lane - 2 : 64 * CPL * W + lane - 2;
-        const bool ends = wv == 0 && lane < 4;
-        if (ends) {
-            const int c = crefl(max(we - sh, -2), nx);
-            eu = uc[c];
-            ex = us[c] + un[c];
-        }
-        if (stands_down(p, false)) return;
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) s2[ln_at<CPL>(w0 + lane + 64 * k)] = vw[k];
-        wave_lds_sync();
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) wr[k] = s2[ln_at<CPL>(w0 + CPL * lane) + k];
-        wave_lds_sync();
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) {
-            sU[ln_at<CPL>(w0 + lane + 64 * k)] = vu[k];
-            s2[ln_at<CPL>(w0 + lane + 64 * k)] = vx[k];
-        }
-        if (ends) {
-            sU[ln_at<CPL>(we)] = eu;
-            s2[ln_at<CPL>(we)] = ex;
-        }
-        if (MW) __syncthreads();
-        else wave_lds_sync();
-    }
-    double fa[CPL], fb[CPL], fz[CPL], fph[CPL], fps[CPL];
-    {
-        const double *bu = sU + ln_at<CPL>(w0 + CPL * lane), *bx = s2 + ln_at<CPL>(w0 + CPL * lane);
-        auto cell = [&](int t) {
-            const double uq = bu[ln_off<CPL>(t)];
-            return cell_core<KM>(p, uq, __builtin_fma(-4.0, uq, (bu[ln_off<CPL>(t + 1)] + bu[ln_off<CPL>(t - 1)])
-                                                                    + bx[ln_off<CPL>(t)]));
-        };
-        // slot and position of the line's first cell; the last slot holds its end at k = CPL-2, CPL-1
-        const int lz = sh / CPL, kz = sh % CPL, slot = 64 * wv + lane;
-        const bool re = slot == 64 * W - 1;
-        CellS c0 = cell(0);
-        FaceS fm = face_s<false>(cell(-1), c0, true, ka);
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) {
-            const CellS cp = cell(k + 1);
-            const FaceS fp = face_s<false>(c0, cp, !(k == CPL - 1 && re), ka);
-            if (k == kz && slot == lz) fm = FaceS{0.0, 0.0, 0.0, 0.0}; // no flux through x = 0
-            Band B = xr_band(fm, fp);
-            if (k >= CPL - 2 && re) fold_right(B, CPL - 1 - k);
-            if (k == kz && slot == lz) fold_left(B, 0);
-            if (k == (kz + 1) % CPL && slot == lz + (kz == CPL - 1 ? 1 : 0)) fold_left(B, 1);
-            xr_elim<CPL>(k, B, wr[k], fa, fb, fz, fph, fps);
-            c0 = cp;
-            fm = fp;
-        }
-    }
-    double B0, B1, l1, l2;
-    if (MW) ln_pairs_mw<CPL>(reinterpret_cast<double2 *>(priv), bnd, lane, wv, W, fa, fb, fz, fph, fps, B0, B1, l1, l2);
-    else ln_pairs<CPL>(reinterpret_cast<double2 *>(priv), lane, (nx + CPL - 1) / CPL, fa, fb, fz, fph, fps, B0, B1, l1, l2);
-    {
-        // back-substitution from the lane's pair and its left neighbour's; v goes to the wave's space
-        double *v2 = priv + (CPL + 1) * lane;
-        __asm__ volatile("" ::: "memory");
-        double x1 = B0, x2 = B1;
-        v2[CPL - 1] = B1;
-        v2[CPL - 2] = B0;
-#pragma unroll
-        for (int k = CPL - 3; k >= 0; --k) {
-            const double v = fz[k] + fph[k] * l1 + fps[k] * l2 - fa[k] * x1 - fb[k] * x2;
-            v2[k] = v;
-            x2 = x1;
-            x1 = v;
-        }
-        wave_lds_sync();
-    }
-    // output: u_{k+1} = u_k + v, update ratio, flags, mass diagnostic (coalesced)
-    double emax = 0.0;
-    unsigned flags = 0;
-    const bool diag = p.mass != nullptr;
-    double ms = 0.0, mc = 0.0, mmin = __builtin_inf();
-    double *orow = p.out + (size_t)j * nx;
-#pragma unroll
-    for (int k = 0; k < CPL; ++k) {
-        const int i = lane + 64 * k, q = w0 + i - sh;
-        if (q >= 0) {
-            const double v = priv[i + i / CPL], uk = sU[ln_at<CPL>(w0 + i)];
-            const double u1 = uk + v;
-            emax = fmax(emax, fabs(v) * rcp(fabs(uk)));
-            if (!(u1 > 0.0)) flags |= (u1 != u1 || v != v) ? FLAG_NAN : FLAG_NONPOS;
-            orow[q] = u1;
-            if (diag) {
-                two_sum_acc(ms, mc, u1);
-                mmin = fmin(mmin, u1);
-            }
-        }
-    }
-    const double wm = wave_max(emax);
-    const unsigned wf = wave_or(flags);
-    if (lane == 0 && p.res != nullptr) {
-        unsigned long long *rs = p.res + (size_t)((unsigned)(rec * W + wv) % (unsigned)p.res_spread) * RES_WORDS;
-        atomicMax(&rs[RES_EMAX], (unsigned long long)__double_as_longlong(wm));
-        if (wf) atomicOr(&rs[RES_FLAGS], (unsigned long long)wf);
-    }
-    if (diag) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) { // fixed-order butterfly
-            comp_add(ms, mc, __shfl_xor(ms, o), __shfl_xor(mc, o));
-            mmin = fmin(mmin, __shfl_xor(mmin, o));
-        }
-        if (lane == 0) {
-            double *o = p.mass + 4 * ((size_t)rec * W + wv);
-            o[0] = ms;
-            o[1] = mc;
-            o[2] = mmin;
-            o[3] = 0.0;
-        }
-    }
-}
-
-// ------------------------------------------------------------------------------------
-// y sweep of the columns i0 .. i0 + LN_COLS - 1 (W waves each). sU: LDS of lny_u2 doubles that holds
-// b^n on its way to the lanes, then the u tile, then the waves' exchange records and solutions:
-// with a single region the workgroups of a CU fill its registers (8 waves of 16 positions per lane).
-// ------------------------------------------------------------------------------------
-template <int KM, int CPL, int W>
-__device__ __forceinline__ void yline_body(const PassParams &p, int i0, int rec, double *sU, double *bnd)
-{
-    constexpr bool MW = W > 1;
-    constexpr int RB = ln_row(CPL, W), NT = 64 * LN_COLS * W, NP = 64 * CPL * W;
-    const int nx = p.nx, ny = p.ny;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int col = MW ? wave / W : wave, wv = MW ? wave % W : 0; // column and wave of its line
-    const int sh = NP - ny, slot = 64 * wv + lane;
-    const double ka = p.ka;
-    double br[CPL]; // b^n of this lane's positions
-    {
-        // u: LN_UC columns x (NP + 4) positions, NT / LN_UC positions per round; b^n: LN_COLS
-        // columns. All loads of a thread are issued before its first LDS store.
-        constexpr int RU = NT / LN_UC, KU = (NP + 4 + RU - 1) / RU, RW = NT / LN_COLS, KW = NP / RW;
-        const int cu = tid % LN_UC, ru = tid / LN_UC, cb = tid % LN_COLS, rb = tid / LN_COLS;
-        const unsigned gu = (unsigned)crefl(i0 - 2 + cu, nx), gb = (unsigned)min(i0 + cb, nx - 1);
-        double vu[KU], vb[KW];
-#pragma unroll
-        for (int k = 0; k < KU; ++k) {
-            const int w = ru + RU * k - 2;
-            if (w < NP + 2) vu[k] = p.u[(size_t)crefl(max(w - sh, -2), ny) * nx + gu];
-        }
-#pragma unroll
-        for (int k = 0; k < KW; ++k) vb[k] = p.in2[(size_t)max(rb + RW * k - sh, 0) * nx + gb];
-        if (stands_down(p, true)) return;
-        if (p.res_clear != nullptr && blockIdx.x == 0)
-            for (int e = tid; e < p.res_spread * RES_WORDS; e += NT) p.res_clear[e] = 0ull;
-#pragma unroll
-        for (int k = 0; k < KW; ++k) sU[cb * RB + ln_at<CPL>(rb + RW * k)] = vb[k];
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) br[k] = sU[col * RB + ln_at<CPL>(CPL * slot) + k];
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < KU; ++k) {
-            const int w = ru + RU * k - 2;
-            if (w < NP + 2) sU[lny_at<CPL>(w) + cu] = vu[k];
-        }
-    }
-    __syncthreads();
-    const int gl = i0 + col; // grid column of this wave
-    double fa[CPL], fb[CPL], fz[CPL], fph[CPL], fps[CPL];
-    double rmax = 0.0;
-    unsigned flags = 0;
-    {
-        const double *bu = sU + lny_at<CPL>(CPL * slot) + 2 + col;
-        // cell quantities at column offset dc, position t; the neighbouring columns' cells enter the
-        // residual's x faces only (their derivatives are not formed)
-        auto cell = [&](int dc, int t) {
-            const double *b = bu + dc;
-            const double uq = b[lny_off<CPL>(t)];
-            return cell_core<KM>(p, uq, __builtin_fma(-4.0, uq, (b[lny_off<CPL>(t) + 1] + b[lny_off<CPL>(t) - 1])
-                                                                    + (b[lny_off<CPL>(t + 1)] + b[lny_off<CPL>(t - 1)])));
-        };
-        auto flux = [&](const CellS &L, const CellS &R) {
-            return __builtin_fma(L.f0 + R.f0, R.lap - L.lap, (L.f1 + R.f1) * (R.u - L.u));
-        };
-        const int lz = sh / CPL, kz = sh % CPL;
-        const bool re = slot == 64 * W - 1;
-        CellS c0 = cell(0, 0);
-        FaceS fm = face_s<true>(cell(0, -1), c0, true, ka);
-#pragma unroll
-        for (int k = 0; k < CPL; ++k) {
-            const CellS cp = cell(0, k + 1);
-            const FaceS fp = face_s<true>(c0, cp, !(k == CPL - 1 && re), ka);
-            if (k == kz && slot == lz) fm = FaceS{0.0, 0.0, 0.0, 0.0};
-            const double Fe = gl < nx - 1 ? flux(c0, cell(1, k)) : 0.0;
-            const double Fw = gl > 0 ? flux(cell(-1, k), c0) : 0.0;
-            const double D = (Fe - Fw) + (fp.F - fm.F);
-            const double G = __builtin_fma(ka, D, c0.u - br[k]);
-            if (CPL * slot + k >= sh) {
-                rmax = fmax(rmax, fabs(G));
-                if (G != G) flags |= FLAG_NAN;
-            }
-            Band B = xr_band(fm, fp);
-            if (k >= CPL - 2 && re) fold_right(B, CPL - 1 - k);
-            if (k == kz && slot == lz) fold_left(B, 0);
-            if (k == (kz + 1) % CPL && slot == lz + (kz == CPL - 1 ? 1 : 0)) fold_left(B, 1);
-            xr_elim<CPL>(k, B, -G, fa, fb, fz, fph, fps);
-            c0 = cp;
-            fm = fp;
-        }
-    }
-    if (p.res != nullptr) {
-        const double wm = wave_max(gl < nx ? rmax : 0.0);
-        const unsigned wf = wave_or(gl < nx ? flags : 0u);
-        if (lane == 0) {
-            unsigned long long *rs = p.res + (size_t)((unsigned)(rec * LN_COLS * W + wave) % (unsigned)p.res_spread) * RES_WORDS;
-            atomicMax(&rs[RES_RMAX], (unsigned long long)__double_as_longlong(wm));
-            if (wf) atomicOr(&rs[RES_FLAGS], (unsigned long long)wf);
-        }
-    }
-    // the u tile is consumed (after a barrier): its space holds the waves' exchange records
-    // and then their solutions
-    double *const priv = sU + wave * ln_priv(CPL);
-    double2 *const xch = reinterpret_cast<double2 *>(priv);
-    double B0, B1, l1, l2;
-    if constexpr (MW) {
-        ln_pairs_mw<CPL>(xch, bnd + col * W * LN_BND, lane, wv, W, fa, fb, fz, fph, fps, B0, B1, l1, l2);
-    } else {
-        __syncthreads();
-        ln_pairs<CPL>(xch, lane, (ny + CPL - 1) / CPL, fa, fb, fz, fph, fps, B0, B1, l1, l2);
-    }
-    {
-        double *v2 = priv + (CPL + 1) * lane;
-        __asm__ volatile("" ::: "memory");
-        double x1 = B0, x2 = B1;
-        v2[CPL - 1] = B1;
-        v2[CPL - 2] = B0;
-#pragma unroll
-        for (int k = CPL - 3; k >= 0; --k) {
-            const double v = fz[k] + fph[k] * l1 + fps[k] * l2 - fa[k] * x1 - fb[k] * x2;
-            v2[k] = v;
-            x2 = x1;
-            x1 = v;
-        }
-    }
-    __syncthreads();
-    {
-        constexpr int RW = NT / LN_COLS, KW = NP / RW;
-        const int cb = tid % LN_COLS, rb = tid / LN_COLS;
-        if (i0 + cb < nx) {
-#pragma unroll
-            for (int k = 0; k < KW; ++k) {
-                const int w = rb + RW * k, q = w - sh, i = w % (64 * CPL);
-                if (q >= 0) p.out[(size_t)q * nx + i0 + cb] = sU[(cb * W + w / (64 * CPL)) * ln_priv(CPL) + i + i / CPL];
-            }
-        }
-    }
-}
-
-// Waves per SIMD the line kernels are compiled for: 16 positions per lane hold 80 factors (2 waves),
-// 8 hold 40 (3 waves).
-#define TF_LINE_ATTR(CPL) \
-    __attribute__((amdgpu_waves_per_eu(CPL == 16 ? 2 : (CPL == 8 ? 3 : 4), CPL == 16 ? 2 : (CPL == 8 ? 3 : 4))))
+// Waves per SIMD the line kernels are compiled for: with 10 and more positions a lane holds 50 to 80
+// factors (2 waves), with 6 and 8 up to 40 (3 waves).
+constexpr int line_waves(int cpl) { return cpl >= 10 ? 2 : (cpl >= 6 ? 3 : 4); }
+#define TF_LINE_ATTR(CPL) __attribute__((amdgpu_waves_per_eu(line_waves(CPL), line_waves(CPL))))
 
 template <int KM, int CPL, int W>
 __global__ void __launch_bounds__(64 * W) TF_LINE_ATTR(CPL) k_xline(PassParams p)
@@ -386,13 +66,15 @@ static hipError_t launch_line_km(int dir, const PassParams &p, hipStream_t s)
 #define TF_YL(C, V) case 100 * V + C: k_yline<KM, C, V><<<gy, by, 0, s>>>(p, nb); break
     if (dir == 0) {
         switch (100 * g.W + g.cpl) {
-        TF_YL(4, 1); TF_YL(8, 1); TF_YL(16, 1); TF_YL(16, 2);
+        TF_YL(4, 1); TF_YL(6, 1); TF_YL(8, 1); TF_YL(10, 1); TF_YL(12, 1); TF_YL(14, 1); TF_YL(16, 1);
+        TF_YL(10, 2); TF_YL(12, 2); TF_YL(14, 2); TF_YL(16, 2);
         default: return hipErrorInvalidValue;
         }
     } else {
         switch (100 * g.W + g.cpl) {
-        TF_XL(4, 1); TF_XL(8, 1); TF_XL(16, 1); TF_XL(16, 2); TF_XL(16, 3); TF_XL(16, 4);
-        TF_XL(16, 5); TF_XL(16, 6); TF_XL(16, 7); TF_XL(16, 8);
+        TF_XL(4, 1); TF_XL(6, 1); TF_XL(8, 1); TF_XL(10, 1); TF_XL(12, 1); TF_XL(14, 1); TF_XL(16, 1);
+        TF_XL(10, 2); TF_XL(12, 2); TF_XL(14, 2); TF_XL(16, 2);
+        TF_XL(12, 3); TF_XL(14, 3); TF_XL(16, 3); TF_XL(14, 4); TF_XL(16, 4); TF_XL(16, 5); TF_XL(16, 6); TF_XL(16, 7); TF_XL(16, 8);
         default: return hipErrorInvalidValue;
         }
     }
@@ -407,67 +89,6 @@ hipError_t launch_line(int dir, const PassParams &p, hipStream_t s)
     case MODEL_POLYMER: return launch_line_km<KM_POLYMER>(dir, p, s);
     default:
         return p.M.p32 ? launch_line_km<KM_P32>(dir, p, s) : launch_line_km<KM_POWER>(dir, p, s);
-    }
-}
-
-// Ensemble versions: block -> (film, four columns / one row) from the work list of one geometry
-// class; films that are not iterating exit at once (before any barrier: the test is uniform over
-// the block).
-template <int KM, int CPL, int W>
-__global__ void __launch_bounds__(64 * W) TF_LINE_ATTR(CPL) k_xline_ens(EnsParams e)
-{
-    __shared__ __align__(16) double s2[ln_row2(CPL, W)];
-    __shared__ double sU[ln_row(CPL, W)];
-    __shared__ double bnd[W > 1 ? W * LN_BND : 1];
-    const int t = xcd_tile(blockIdx.x, e.nitems);
-    const int f = e.items[2 * t], j = e.items[2 * t + 1];
-    FilmState *st = e.state + f;
-    if (!st->active) return;
-    const PassParams p = ens_pass_params(e, e.desc[f], st, 1);
-    xline_body<KM, CPL, (W > 1)>(p, j, j, W, sU, s2, bnd);
-}
-
-template <int KM, int CPL, int W>
-__global__ void __launch_bounds__(64 * LN_COLS * W) TF_LINE_ATTR(CPL) k_yline_ens(EnsParams e)
-{
-    __shared__ __align__(16) double sU[lny_u2(CPL, W)];
-    __shared__ double bnd[W > 1 ? LN_COLS * W * LN_BND : 1];
-    const int t = xcd_tile(blockIdx.x, e.nitems);
-    const int f = e.items[2 * t], b = e.items[2 * t + 1];
-    FilmState *st = e.state + f;
-    if (!st->active) return;
-    const PassParams p = ens_pass_params(e, e.desc[f], st, 0);
-    yline_body<KM, CPL, W>(p, b * LN_COLS, b, sU, bnd);
-}
-
-template <int KM>
-static hipError_t launch_line_ens_km(int dir, const LineGeom &g, const EnsParams &e, hipStream_t s)
-{
-    const dim3 grid(e.nitems), bx(64 * g.W), by(64 * LN_COLS * g.W);
-#define TF_XLE(C, V) case 100 * V + C: k_xline_ens<KM, C, V><<<grid, bx, 0, s>>>(e); break
-#define TF_YLE(C, V) case 100 * V + C: k_yline_ens<KM, C, V><<<grid, by, 0, s>>>(e); break
-    if (dir == 0) {
-        switch (100 * g.W + g.cpl) {
-        TF_YLE(4, 1); TF_YLE(8, 1); TF_YLE(16, 1); TF_YLE(16, 2);
-        default: return hipErrorInvalidValue;
-        }
-    } else {
-        switch (100 * g.W + g.cpl) {
-        TF_XLE(4, 1); TF_XLE(8, 1); TF_XLE(16, 1); TF_XLE(16, 2); TF_XLE(16, 3); TF_XLE(16, 4);
-        default: return hipErrorInvalidValue;
-        }
-    }
-    return hipGetLastError();
-}
-
-hipError_t launch_line_ens(int dir, const LineGeom &g, int km, const EnsParams &e, hipStream_t s)
-{
-    switch (km) {
-    case KM_P32: return launch_line_ens_km<KM_P32>(dir, g, e, s);
-    case KM_POWER: return launch_line_ens_km<KM_POWER>(dir, g, e, s);
-    case KM_LINEAR: return launch_line_ens_km<KM_LINEAR>(dir, g, e, s);
-    case KM_NLC: return launch_line_ens_km<KM_NLC>(dir, g, e, s);
-    default: return launch_line_ens_km<KM_POLYMER>(dir, g, e, s);
     }
 }
 

@@ -174,7 +174,8 @@ template <bool TRANS, bool PM, int MODE>
 static hipError_t launch_sb(int nl, int np, const double *bands, const double *rhs, double *out,
                             unsigned long long *red, hipStream_t s, const unsigned long long *stop)
 {
-    const LineGeom g = xline_geom(np);
+    // (not the forward sweeps' finer choice: these kernels are latency bound)
+    const LineGeom g = {np <= 256 ? 4 : (np <= 512 ? 8 : 16), (np + 1023) / 1024};
     const bool many = (long long)nl * g.W > 1024;
     const int L = sb_lines(g.W, many), nb = (nl + L - 1) / L;
     const dim3 grid(nb), block(64 * L * g.W);

@@ -13,7 +13,8 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 # lengths on both sides of every change of geometry
-EDGES = [4, 5, 7, 8, 9, 255, 256, 257, 263, 511, 512, 513, 527, 1023, 1024, 1025, 1039, 2047, 2048]
+EDGES = [4, 5, 7, 8, 9, 255, 256, 257, 263, 384, 385, 511, 512, 513, 527, 640, 641, 768, 769, 895, 897, 1023, 1024, 1025,
+         1039, 1280, 1281, 1536, 1537, 1792, 1793, 2047, 2048]
 
 
 def one(orc, nx, ny, theta=1.0, model="power"):
@@ -48,7 +49,7 @@ def test_columns_match_oracle(orc, n):
     one(orc, 6, n)
 
 
-@pytest.mark.parametrize("n", EDGES + [3072, 3073, 4096, 5000, 8191, 8192])
+@pytest.mark.parametrize("n", EDGES + [2304, 2305, 2688, 2689, 3072, 3073, 3584, 3585, 4096, 5000, 8191, 8192])
 def test_rows_match_oracle(orc, n):
     one(orc, n, 5)
 
@@ -81,7 +82,9 @@ def test_stored_band_lines_match_oracle(orc, n, transposed):
 
 def test_ensemble_of_every_line_class_equals_single_films():
     """One film per geometry class of the columns and rows (and one that takes tiles), bit for bit."""
-    shapes = [(100, 90), (300, 60), (700, 400), (1500, 700), (60, 1300), (2500, 40), (4000, 24), (9, 2100)]
+    shapes = [(100, 90), (300, 60), (500, 300), (600, 500), (700, 600), (800, 700), (1000, 800), (1200, 900), (30, 1200),
+              (1500, 40), (40, 1500), (1700, 20), (20, 1700), (2000, 10), (10, 2000), (2200, 8), (2500, 40), (3000, 9),
+              (3500, 8), (4000, 24), (9, 2100)]
     nx, ny = [a for a, _ in shapes], [b for _, b in shapes]
     ds = [0.67347] * len(shapes)
     kap = [10.0 + i for i in range(len(shapes))]
