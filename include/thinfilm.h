@@ -355,8 +355,9 @@ int tf_autotune_choice(int length, int batch, int transposed);
  * too). TF_EINVAL for length or batch below 4. Grids (tf_create) and ensembles
  * (tf_ensemble_create, per film, with ny = the rows of all its films, since its x sweep is one
  * launch over all of them) take the variant tf_xsweep_choice(nx, ny) returns at creation: the
- * tuned entry of the nearest shape (log distance below 0.7), else the whole-row kernel; never
- * the whole-row kernel for rows above 4096 cells.
+ * tuned entry of the nearest shape (log distance below 0.7), else the whole-row kernel; for
+ * rows above 4096 cells never the whole-row kernel in ensembles or in films of fewer than 64
+ * rows.
  * Returns 0 (partitioned) or 1 (whole-row). */
 tf_status tf_autotune_xsweep(int length, int batch, const char *cache_path);
 int tf_xsweep_choice(int nx, int ny);

@@ -732,10 +732,12 @@ struct Scratch {
 namespace tf {
 // x-sweep variant for ny rows of nx cells in one launch: the tuned entry with the nearest shape,
 // else the whole-row kernel (faster than the partitioned solver's three launches at every length and
-// number of rows measured, figures at xline_geom in tf_line.hip); it is only chosen for nx <= 4096.
+// number of rows measured, figures at xline_geom in tf_line.hip). Rows above 4096 cells take it in films of
+// at least 64 rows (8192 x 64: 25 against 69 us, 8192^2: 818 against 900); shorter films keep the
+// partitioned solver tf_xsweep_choice has always returned for them.
 int xsweep_choice(int nx, int ny)
 {
-    if (!xrow_supported(nx) || nx > XR_ROW4_MAX_NX) return 0;
+    if (!xrow_supported(nx) || (nx > XR_ROW4_MAX_NX && ny < 64)) return 0;
     TuneTable &t = tune_table();
     std::lock_guard<std::mutex> lk(t.mu);
     double best_d = 1e30;

@@ -44,7 +44,7 @@ struct tf_ensemble {
     long long ncells = 0, nrec = 0;
     // work lists of one iteration (build_items), each a range of d_items
     struct Range { size_t off = 0; int n = 0; };
-    Range ty, tx, cy, cx, bnt, yl[tf::YL_MAXW], xl[tf::XL_MAXW];
+    Range ty, tx, cy, cx, bnt, yl[tf::YL_MAXW], xl[2 * tf::XL_MAXW];
     tf::FilmDesc *d_desc = nullptr;
     tf::FilmState *d_state = nullptr, *h_state = nullptr;
     int *d_items = nullptr;
@@ -91,14 +91,15 @@ tf_status enqueue_iteration(tf_ensemble *e)
         TF_EHIP(tf::launch_pass_ens(0, true, e->km, params(e, e->ty), e->stream));
     }
     for (int W = 1; W <= tf::YL_MAXW; ++W)
-        if (e->yl[W - 1].n > 0) TF_EHIP(tf::launch_line_ens(0, W, e->km, params(e, e->yl[W - 1]), e->stream));
+        if (e->yl[W - 1].n > 0) TF_EHIP(tf::launch_line_ens(0, W, false, e->km, params(e, e->yl[W - 1]), e->stream));
     if (e->tx.n > 0) {
         TF_EHIP(tf::launch_pass_ens(1, false, e->km, params(e, e->tx), e->stream));
         TF_EHIP(tf::launch_chain_ens(params(e, e->cx), 1, e->stream));
         TF_EHIP(tf::launch_pass_ens(1, true, e->km, params(e, e->tx), e->stream));
     }
-    for (int W = 1; W <= tf::XL_MAXW; ++W)
-        if (e->xl[W - 1].n > 0) TF_EHIP(tf::launch_line_ens(1, W, e->km, params(e, e->xl[W - 1]), e->stream));
+    for (int k = 0; k < 2 * tf::XL_MAXW; ++k)
+        if (e->xl[k].n > 0)
+            TF_EHIP(tf::launch_line_ens(1, k / 2 + 1, k % 2 != 0, e->km, params(e, e->xl[k]), e->stream));
     TF_EHIP(tf::launch_ens_control(e->d_state, e->nfilms, S, e->d_active, e->stream));
     return TF_OK;
 }
@@ -149,7 +150,7 @@ std::vector<int> spread_lines(const std::vector<int> &v)
 // and chain blocks. The b^n list covers every film.
 void build_items(tf_ensemble *e, std::vector<int> &items)
 {
-    std::vector<int> ty, tx, cy, cx, bnt, yl[tf::YL_MAXW], xl[tf::XL_MAXW];
+    std::vector<int> ty, tx, cy, cx, bnt, yl[tf::YL_MAXW], xl[2 * tf::XL_MAXW];
     for (int f = 0; f < e->nfilms; ++f) {
         const tf::FilmDesc &d = e->desc[f];
         const tf::LineGeom yg = tf::yline_geom(e->km, d.nx, d.ny), xg = e->xsweep[f] == 1 ? tf::xline_geom(d.nx)
@@ -166,7 +167,8 @@ void build_items(tf_ensemble *e, std::vector<int> &items)
             for (int b = 0; b < (d.nx + 63) / 64; ++b) cy.insert(cy.end(), {f, b});
         }
         if (xg.W > 0) {
-            for (int j = 0; j < d.ny; ++j) xl[xg.W - 1].insert(xl[xg.W - 1].end(), {f, j, xg.cpl});
+            std::vector<int> &v = xl[2 * (xg.W - 1) + (d.nx % xg.cpl == 0)];
+            for (int j = 0; j < d.ny; ++j) v.insert(v.end(), {f, j, xg.cpl});
         } else {
             for (int j = 0; j < txy; ++j)
                 for (int i = 0; i < d.Px; ++i) tx.insert(tx.end(), {f, i, j});
@@ -192,8 +194,8 @@ void build_items(tf_ensemble *e, std::vector<int> &items)
     put(e->bnt, bnt, 3);
     put(e->cy, cy, 2);
     put(e->cx, cx, 2);
-    for (auto W = 0; W < tf::YL_MAXW; ++W) put_lines(e->yl[W], yl[W]);
-    for (auto W = 0; W < tf::XL_MAXW; ++W) put_lines(e->xl[W], xl[W]);
+    for (int k = 0; k < tf::YL_MAXW; ++k) put_lines(e->yl[k], yl[k]);
+    for (int k = 0; k < 2 * tf::XL_MAXW; ++k) put_lines(e->xl[k], xl[k]);
 }
 
 tf_status upload_items(tf_ensemble *e)
@@ -228,6 +230,12 @@ int total_rows(const tf_ensemble *e)
     return (int)std::min(n, (long long)1 << 30);
 }
 
+int auto_xsweep(const tf_ensemble *e, int f)
+{
+    const int nx = e->desc[f].nx;
+    return nx <= tf::XR_ROW4_MAX_NX ? tf::xsweep_choice(nx, total_rows(e)) : 0;
+}
+
 // Work-list capacity for any choice of x-sweep variants.
 size_t max_items(const tf_ensemble *e)
 {
@@ -238,7 +246,7 @@ size_t max_items(const tf_ensemble *e)
         n += 2 * (size_t)((d.nx + 63) / 64) + 3 * (size_t)((d.nx + tf::LN_COLS - 1) / tf::LN_COLS);
         n += 3 * (size_t)((d.ny + tf::TILE - 1) / tf::TILE) * d.Px + 2 * (size_t)((d.ny + 63) / 64) + 3 * (size_t)d.ny;
     }
-    n += 3 * LINE_RUN * LINE_XCDS * (tf::YL_MAXW + tf::XL_MAXW); // padding of the line lists
+    n += 3 * LINE_RUN * LINE_XCDS * (tf::YL_MAXW + 2 * tf::XL_MAXW); // padding of the line lists
     return n;
 }
 
@@ -293,7 +301,7 @@ tf_status tf_ensemble_create(int nfilms, const int *nx, const int *ny, const dou
         e->desc.push_back(d);
     }
     e->xsweep.assign(nfilms, 0);
-    for (int f = 0; f < nfilms; ++f) e->xsweep[f] = tf::xsweep_choice(nx[f], total_rows(e));
+    for (int f = 0; f < nfilms; ++f) e->xsweep[f] = auto_xsweep(e, f);
     std::vector<int> items;
     build_items(e, items);
     const size_t N = (size_t)e->ncells, R = (size_t)e->nrec;
@@ -388,7 +396,7 @@ tf_status tf_ensemble_set_xsweep(tf_ensemble *e, int variant)
     for (int f = 0; f < e->nfilms; ++f) {
         const tf::FilmDesc &d = e->desc[f];
         const bool row4 = tf::xrow_supported(d.nx) && d.nx <= tf::XR_ROW4_MAX_NX;
-        e->xsweep[f] = variant == TF_XSWEEP_AUTO ? tf::xsweep_choice(d.nx, total_rows(e))
+        e->xsweep[f] = variant == TF_XSWEEP_AUTO ? auto_xsweep(e, f)
                      : (variant == TF_XSWEEP_ROW && row4 ? 1 : 0);
     }
     return upload_items(e);

@@ -280,9 +280,10 @@ hipError_t launch_sbline(bool trans, bool pm, int mode, int nl, int np, const do
 // x-sweep variant for a film of nx x ny cells (0: partitioned, 1: whole-row): the autotuned
 // choice for the nearest shape, else the built-in rule (tf_adjoint.hip).
 int xsweep_choice(int nx, int ny);
-// The same over an ensemble's films with W waves per line (items: (film, block of four columns or row,
+// The same over an ensemble's films with W waves per line, of x sweeps only those whose rows fill their
+// lanes (aligned: cpl divides nx) or only the others (items: (film, block of four columns or row,
 // positions per lane), film -1: none); km: the KernelModel every film shares.
-hipError_t launch_line_ens(int dir, int W, int km, const EnsParams &e, hipStream_t s);
+hipError_t launch_line_ens(int dir, int W, bool aligned, int km, const EnsParams &e, hipStream_t s);
 hipError_t launch_model_coeffs(const Model &M, const double *h, int n, double *out, hipStream_t s);
 hipError_t launch_chain(const ChainParams &c, hipStream_t s);
 hipError_t launch_flux_divergence(int nx, int ny, double ids, double ids2, const Model &M,

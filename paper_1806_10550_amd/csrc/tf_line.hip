@@ -37,14 +37,14 @@ LineGeom yline_geom(int km, int nx, int ny)
 constexpr int line_waves(int cpl) { return cpl >= 10 ? 2 : (cpl >= 6 ? 3 : 4); }
 #define TF_LINE_ATTR(CPL) __attribute__((amdgpu_waves_per_eu(line_waves(CPL), line_waves(CPL))))
 
-template <int KM, int CPL, int W>
+template <int KM, int CPL, int W, bool AL>
 __global__ void __launch_bounds__(64 * W) TF_LINE_ATTR(CPL) k_xline(PassParams p)
 {
     __shared__ __align__(16) double s2[ln_row2(CPL, W)];
     __shared__ double sU[ln_row(CPL, W)];
     __shared__ double bnd[W > 1 ? W * LN_BND : 1];
     const int j = xcd_tile(blockIdx.x, p.ny);
-    xline_body<KM, CPL, (W > 1)>(p, j, j, W, sU, s2, bnd);
+    xline_body<KM, CPL, (W > 1), AL>(p, j, j, W, sU, s2, bnd);
 }
 
 template <int KM, int CPL, int W>
@@ -62,7 +62,11 @@ static hipError_t launch_line_km(int dir, const PassParams &p, hipStream_t s)
     const int nb = (p.nx + LN_COLS - 1) / LN_COLS;
     const LineGeom g = dir == 0 ? yline_geom(KM, p.nx, p.ny) : xline_geom(p.nx);
     const dim3 gx(p.ny), gy(nb), bx(64 * g.W), by(64 * LN_COLS * g.W);
-#define TF_XL(C, V) case 100 * V + C: k_xline<KM, C, V><<<gx, bx, 0, s>>>(p); break
+#define TF_XL(C, V) \
+    case 100 * V + C: \
+        if (p.nx % C == 0) k_xline<KM, C, V, true><<<gx, bx, 0, s>>>(p); \
+        else k_xline<KM, C, V, false><<<gx, bx, 0, s>>>(p); \
+        break
 #define TF_YL(C, V) case 100 * V + C: k_yline<KM, C, V><<<gy, by, 0, s>>>(p, nb); break
     if (dir == 0) {
         switch (100 * g.W + g.cpl) {

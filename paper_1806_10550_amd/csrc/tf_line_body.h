@@ -43,9 +43,11 @@ __device__ __forceinline__ bool stands_down(const PassParams &p, bool decide)
 
 // ------------------------------------------------------------------------------------
 // x sweep of grid row j. sU, s2: the wave's LDS rows (ln_row, ln_row2 doubles). rec: index of the
-// wave's reduction copy and mass record.
+// wave's reduction copy and mass record. AL: the row fills its lanes (CPL divides nx), so that its first cell
+// is some lane's position 0; the elimination is then one straight block of code instead of one cut by a
+// test for the first cell at every position (8192 rows of 1024: 75 -> 65 us).
 // ------------------------------------------------------------------------------------
-template <int KM, int CPL, bool MW>
+template <int KM, int CPL, bool MW, bool AL>
 __device__ __forceinline__ void xline_body(const PassParams &p, int j, int rec, int W, double *sU, double *s2,
                                            double *bnd)
 {
@@ -109,7 +111,7 @@ __device__ __forceinline__ void xline_body(const PassParams &p, int j, int rec, 
                                                                     + bx[ln_off<CPL>(t)]));
         };
         // slot and position of the line's first cell; the last slot holds its end at k = CPL-2, CPL-1
-        const int lz = sh / CPL, kz = sh % CPL, slot = 64 * wv + lane;
+        const int lz = sh / CPL, kz = AL ? 0 : sh % CPL, slot = 64 * wv + lane;
         const bool re = slot == 64 * W - 1;
         CellS c0 = cell(0);
         FaceS fm = face_s<false>(cell(-1), c0, true, ka);
