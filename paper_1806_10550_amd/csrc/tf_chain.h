@@ -1,0 +1,155 @@
+// Interface systems of the partitioned line solvers by cyclic reduction.
+//
+// The P segments of a line satisfy (T, B: a segment's first and last pair)
+//   T_q = t_q + Tl_q B_{q-1} + Tr_q T_{q+1},   B_q = b_q + Bl_q B_{q-1} + Br_q T_{q+1}
+// with nothing beyond the line's ends. The unknowns of the junction q | q+1 are x_q = (B_q, T_{q+1});
+// eliminating each from the other's equation gives
+//   x_q = R_q + A_q B_{q-1} + C_q T_{q+2}       (A, C: 4 x 2),
+// which couples x_q to the B half of its left and the T half of its right neighbour: log2(P - 1) steps of
+// cyclic reduction, each a 4 x 4 solve in 2 x 2 blocks, leave x_q alone. One lane per junction; a workgroup
+// holds CH_LINES lines so that records move in 64-byte pieces.
+#pragma once
+
+#include "tf_line.h"
+
+namespace tf {
+
+constexpr int CH_LINES = 4;
+constexpr int CH_MAXP = 129;                                 // junctions of two waves
+__host__ __device__ constexpr int ch_pitch(int WJ) { return 64 * WJ + 1; }
+__host__ __device__ constexpr int ch_lds(int WJ) { return CH_LINES * (NREL / 2) * ch_pitch(WJ); } // double2
+
+// Equation of a junction: B half (rb, Ab, Cb), T half (rt, At, Ct).
+struct Junction {
+    double rb0, rb1, rt0, rt1;
+    M2 Ab, Cb, At, Ct;
+};
+
+__device__ __forceinline__ void ch_mv(const M2 &x, double v0, double v1, double &o0, double &o1) // o += x v
+{
+    o0 = __builtin_fma(x.a, v0, __builtin_fma(x.b, v1, o0));
+    o1 = __builtin_fma(x.c, v0, __builtin_fma(x.d, v1, o1));
+}
+__device__ __forceinline__ M2 m2_neg(const M2 &x) { return {-x.a, -x.b, -x.c, -x.d}; }
+
+// Lines l0 .. l0 + CH_LINES - 1, WJ waves per line (P - 1 <= 64 WJ); buf: ch_lds(WJ) double2 of LDS.
+template <int WJ>
+__device__ __forceinline__ void chain_reduce(const ChainParams &c, int l0, double2 *buf)
+{
+    constexpr int PP = ch_pitch(WJ), NT = 64 * WJ * CH_LINES, NP = NREL / 2;
+    const size_t NL = (size_t)c.nlines;
+    const int P = c.P, tid = threadIdx.x;
+    // records: pair f of segment q of line l at buf[(l NP + f) PP + q]
+    for (int e = tid; e < CH_LINES * NP * P; e += NT) {
+        const int l = e % CH_LINES, f = (e / CH_LINES) % NP, q = e / (CH_LINES * NP);
+        if (l0 + l < c.nlines)
+            buf[(l * NP + f) * PP + q] = rec_get2(c.rel + (size_t)q * NREL * NL + 2 * (size_t)(l0 + l), NL, f);
+    }
+    __syncthreads();
+    const int ln = tid / (64 * WJ), q = tid % (64 * WJ), nj = P - 1; // junction q of line ln
+    const int qc = min(q, max(nj - 1, 0));
+    double2 *const rec = buf + ln * NP * PP;
+    Junction J;
+    {
+        // B half of segment q (fields 10..19), T half of segment q + 1 (fields 0..9)
+        double B[10], T[10];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            const double2 v = rec[(5 + k) * PP + qc], w = rec[k * PP + min(qc + 1, P - 1)];
+            B[2 * k] = v.x; B[2 * k + 1] = v.y;
+            T[2 * k] = w.x; T[2 * k + 1] = w.y;
+        }
+        const M2 Bl = {B[1], B[2], B[6], B[7]}, Br = {B[3], B[4], B[8], B[9]};
+        const M2 Tl = {T[1], T[2], T[6], T[7]};
+        M2 Tr = {T[3], T[4], T[8], T[9]};
+        if (qc == nj - 1) Tr = {0.0, 0.0, 0.0, 0.0};
+        const M2 K = inv_i_minus(mul(Br, Tl));
+        double s0 = B[0], s1 = B[5];
+        ch_mv(Br, T[0], T[5], s0, s1);
+        J.rb0 = K.a * s0 + K.b * s1;
+        J.rb1 = K.c * s0 + K.d * s1;
+        J.Ab = qc == 0 ? M2{0.0, 0.0, 0.0, 0.0} : mul(K, Bl);
+        J.Cb = mul(K, mul(Br, Tr));
+        J.rt0 = T[0];
+        J.rt1 = T[5];
+        ch_mv(Tl, J.rb0, J.rb1, J.rt0, J.rt1);
+        J.At = mul(Tl, J.Ab);
+        J.Ct = m2_ma(Tl, J.Cb, Tr);
+    }
+    auto sync = [&] {
+        if (WJ > 1) __syncthreads();
+        else wave_lds_sync();
+    };
+    // junction q's B half at pairs 0..4, its T half at pairs 5..9 of column q
+    for (int d = 1; d < nj; d <<= 1) {
+        if (WJ > 1) __syncthreads(); // the records / the last step's halves have been read
+        __asm__ volatile("" ::: "memory");
+        rec[0 * PP + q] = make_double2(J.rb0, J.rb1);
+        rec[1 * PP + q] = make_double2(J.Ab.a, J.Ab.b);
+        rec[2 * PP + q] = make_double2(J.Ab.c, J.Ab.d);
+        rec[3 * PP + q] = make_double2(J.Cb.a, J.Cb.b);
+        rec[4 * PP + q] = make_double2(J.Cb.c, J.Cb.d);
+        rec[5 * PP + q] = make_double2(J.rt0, J.rt1);
+        rec[6 * PP + q] = make_double2(J.At.a, J.At.b);
+        rec[7 * PP + q] = make_double2(J.At.c, J.At.d);
+        rec[8 * PP + q] = make_double2(J.Ct.a, J.Ct.b);
+        rec[9 * PP + q] = make_double2(J.Ct.c, J.Ct.d);
+        sync();
+        // past the line's ends A or C is zero and any junction's halves will do
+        const double2 *L = rec + max(qc - d, 0), *R = rec + min(qc + d, nj - 1);
+        const double2 l0v = L[0], l1 = L[PP], l2 = L[2 * PP], l3 = L[3 * PP], l4 = L[4 * PP];
+        const M2 lA = {l1.x, l1.y, l2.x, l2.y}, lC = {l3.x, l3.y, l4.x, l4.y};
+        const double2 r0v = R[5 * PP], r1 = R[6 * PP], r2 = R[7 * PP], r3 = R[8 * PP], r4 = R[9 * PP];
+        const M2 rA = {r1.x, r1.y, r2.x, r2.y}, rC = {r3.x, r3.y, r4.x, r4.y};
+        // [M_BB M_BT; M_TB M_TT] x = f + F B'' + G T''
+        const M2 Mbt = m2_neg(mul(J.Ab, lC)), Mtb = m2_neg(mul(J.Ct, rA));
+        const M2 Pb = inv_i_minus(mul(J.Cb, rA));
+        const M2 U = mul(Pb, Mbt);
+        // S = M_TT - M_TB U = I - (A_T lC + M_TB U)
+        const M2 Si = inv_i_minus(m2_ma(Mtb, U, mul(J.At, lC)));
+        double fb0 = J.rb0, fb1 = J.rb1, ft0 = J.rt0, ft1 = J.rt1;
+        ch_mv(J.Ab, l0v.x, l0v.y, fb0, fb1);
+        ch_mv(J.Cb, r0v.x, r0v.y, fb0, fb1);
+        ch_mv(J.At, l0v.x, l0v.y, ft0, ft1);
+        ch_mv(J.Ct, r0v.x, r0v.y, ft0, ft1);
+        {
+            const double g0 = Pb.a * fb0 + Pb.b * fb1, g1 = Pb.c * fb0 + Pb.d * fb1;
+            const double h0 = ft0 - (Mtb.a * g0 + Mtb.b * g1), h1 = ft1 - (Mtb.c * g0 + Mtb.d * g1);
+            J.rt0 = Si.a * h0 + Si.b * h1;
+            J.rt1 = Si.c * h0 + Si.d * h1;
+            J.rb0 = g0 - (U.a * J.rt0 + U.b * J.rt1);
+            J.rb1 = g1 - (U.c * J.rt0 + U.d * J.rt1);
+        }
+        auto solve = [&](const M2 &Fb, const M2 &Ft, M2 &Xb, M2 &Xt) {
+            const M2 G = mul(Pb, Fb);
+            Xt = mul(Si, m2_ma(m2_neg(Mtb), G, Ft));
+            Xb = m2_ma(m2_neg(U), Xt, G);
+        };
+        const M2 Fb = mul(J.Ab, lA), Ft = mul(J.At, lA), Gb = mul(J.Cb, rC), Gt = mul(J.Ct, rC);
+        solve(Fb, Ft, J.Ab, J.At);
+        solve(Gb, Gt, J.Cb, J.Ct);
+    }
+    // boundary records: segment s takes l = B_{s-1} and r = T_{s+1}; through LDS so that a position's lines
+    // are stored together
+    __syncthreads();
+    double *const eo = reinterpret_cast<double *>(buf); // [segment][field][line]
+    if (q < nj) {
+        eo[((q + 1) * NEXT + 0) * CH_LINES + ln] = J.rb0;
+        eo[((q + 1) * NEXT + 1) * CH_LINES + ln] = J.rb1;
+        eo[(q * NEXT + 2) * CH_LINES + ln] = J.rt0;
+        eo[(q * NEXT + 3) * CH_LINES + ln] = J.rt1;
+    }
+    if (q == 0) {
+        eo[0 * CH_LINES + ln] = 0.0;
+        eo[1 * CH_LINES + ln] = 0.0;
+        eo[((P - 1) * NEXT + 2) * CH_LINES + ln] = 0.0;
+        eo[((P - 1) * NEXT + 3) * CH_LINES + ln] = 0.0;
+    }
+    __syncthreads();
+    for (int e = tid; e < CH_LINES * NEXT * P; e += NT) {
+        const int l = e % CH_LINES;
+        if (l0 + l < c.nlines) c.ext[(size_t)(e / CH_LINES) * NL + l0 + l] = eo[e];
+    }
+}
+
+} // namespace tf

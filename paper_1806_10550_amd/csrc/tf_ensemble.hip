@@ -44,7 +44,7 @@ struct tf_ensemble {
     long long ncells = 0, nrec = 0;
     // work lists of one iteration (build_items), each a range of d_items
     struct Range { size_t off = 0; int n = 0; };
-    Range ty, tx, cy, cx, bnt, yl[tf::YL_MAXW], xl[2 * tf::XL_MAXW];
+    Range ty, tx, cy[2], cx[2], bnt, yl[tf::YL_MAXW], xl[2 * tf::XL_MAXW];
     tf::FilmDesc *d_desc = nullptr;
     tf::FilmState *d_state = nullptr, *h_state = nullptr;
     int *d_items = nullptr;
@@ -87,14 +87,16 @@ tf_status enqueue_iteration(tf_ensemble *e)
     if (e->S.theta < 1.0) TF_EHIP(tf::launch_bn_ens(params(e, e->bnt), e->stream));
     if (e->ty.n > 0) {
         TF_EHIP(tf::launch_pass_ens(0, false, e->km, params(e, e->ty), e->stream));
-        TF_EHIP(tf::launch_chain_ens(params(e, e->cy), 0, e->stream));
+        for (int k = 0; k < 2; ++k)
+            if (e->cy[k].n > 0) TF_EHIP(tf::launch_chain_ens(params(e, e->cy[k]), 0, k != 0, e->stream));
         TF_EHIP(tf::launch_pass_ens(0, true, e->km, params(e, e->ty), e->stream));
     }
     for (int W = 1; W <= tf::YL_MAXW; ++W)
         if (e->yl[W - 1].n > 0) TF_EHIP(tf::launch_line_ens(0, W, false, e->km, params(e, e->yl[W - 1]), e->stream));
     if (e->tx.n > 0) {
         TF_EHIP(tf::launch_pass_ens(1, false, e->km, params(e, e->tx), e->stream));
-        TF_EHIP(tf::launch_chain_ens(params(e, e->cx), 1, e->stream));
+        for (int k = 0; k < 2; ++k)
+            if (e->cx[k].n > 0) TF_EHIP(tf::launch_chain_ens(params(e, e->cx[k]), 1, k != 0, e->stream));
         TF_EHIP(tf::launch_pass_ens(1, true, e->km, params(e, e->tx), e->stream));
     }
     for (int k = 0; k < 2 * tf::XL_MAXW; ++k)
@@ -150,7 +152,13 @@ std::vector<int> spread_lines(const std::vector<int> &v)
 // and chain blocks. The b^n list covers every film.
 void build_items(tf_ensemble *e, std::vector<int> &items)
 {
-    std::vector<int> ty, tx, cy, cx, bnt, yl[tf::YL_MAXW], xl[2 * tf::XL_MAXW];
+    std::vector<int> ty, tx, cy[2], cx[2], bnt, yl[tf::YL_MAXW], xl[2 * tf::XL_MAXW];
+    // chain blocks of one film's lines: serial chains in list 0, reduced ones in list 1
+    auto chains = [](std::vector<int> (&v)[2], int f, int P, int nlines) {
+        const int per = tf::chain_lines(P, nlines);
+        std::vector<int> &w = v[tf::chain_reduced(P, nlines)];
+        for (int b = 0; b < (nlines + per - 1) / per; ++b) w.insert(w.end(), {f, b});
+    };
     for (int f = 0; f < e->nfilms; ++f) {
         const tf::FilmDesc &d = e->desc[f];
         const tf::LineGeom yg = tf::yline_geom(e->km, d.nx, d.ny), xg = e->xsweep[f] == 1 ? tf::xline_geom(d.nx)
@@ -164,7 +172,7 @@ void build_items(tf_ensemble *e, std::vector<int> &items)
         } else {
             for (int j = 0; j < d.Py; ++j)
                 for (int i = 0; i < tyx; ++i) ty.insert(ty.end(), {f, i, j});
-            for (int b = 0; b < (d.nx + 63) / 64; ++b) cy.insert(cy.end(), {f, b});
+            chains(cy, f, d.Py, d.nx);
         }
         if (xg.W > 0) {
             std::vector<int> &v = xl[2 * (xg.W - 1) + (d.nx % xg.cpl == 0)];
@@ -172,7 +180,7 @@ void build_items(tf_ensemble *e, std::vector<int> &items)
         } else {
             for (int j = 0; j < txy; ++j)
                 for (int i = 0; i < d.Px; ++i) tx.insert(tx.end(), {f, i, j});
-            for (int b = 0; b < (d.ny + 63) / 64; ++b) cx.insert(cx.end(), {f, b});
+            chains(cx, f, d.Px, d.ny);
         }
     }
     items.clear();
@@ -192,8 +200,10 @@ void build_items(tf_ensemble *e, std::vector<int> &items)
     put(e->ty, ty, 3);
     put(e->tx, tx, 3);
     put(e->bnt, bnt, 3);
-    put(e->cy, cy, 2);
-    put(e->cx, cx, 2);
+    for (int k = 0; k < 2; ++k) {
+        put(e->cy[k], cy[k], 2);
+        put(e->cx[k], cx[k], 2);
+    }
     for (int k = 0; k < tf::YL_MAXW; ++k) put_lines(e->yl[k], yl[k]);
     for (int k = 0; k < 2 * tf::XL_MAXW; ++k) put_lines(e->xl[k], xl[k]);
 }
@@ -243,8 +253,8 @@ size_t max_items(const tf_ensemble *e)
     for (const auto &d : e->desc) {
         const size_t yt = (size_t)d.Py * ((d.nx + tf::TILE - 1) / tf::TILE);
         n += 3 * yt + 3 * (size_t)tf::bn_tiles_x(d.nx) * tf::bn_tiles_y(d.ny);
-        n += 2 * (size_t)((d.nx + 63) / 64) + 3 * (size_t)((d.nx + tf::LN_COLS - 1) / tf::LN_COLS);
-        n += 3 * (size_t)((d.ny + tf::TILE - 1) / tf::TILE) * d.Px + 2 * (size_t)((d.ny + 63) / 64) + 3 * (size_t)d.ny;
+        n += 2 * (size_t)d.nx + 3 * (size_t)((d.nx + tf::LN_COLS - 1) / tf::LN_COLS); // (chain blocks: at most one per line)
+        n += 3 * (size_t)((d.ny + tf::TILE - 1) / tf::TILE) * d.Px + 5 * (size_t)d.ny;
     }
     n += 3 * LINE_RUN * LINE_XCDS * (tf::YL_MAXW + 2 * tf::XL_MAXW); // padding of the line lists
     return n;

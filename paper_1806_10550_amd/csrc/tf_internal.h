@@ -285,6 +285,10 @@ int xsweep_choice(int nx, int ny);
 // positions per lane), film -1: none); km: the KernelModel every film shares.
 hipError_t launch_line_ens(int dir, int W, bool aligned, int km, const EnsParams &e, hipStream_t s);
 hipError_t launch_model_coeffs(const Model &M, const double *h, int n, double *out, hipStream_t s);
+// Interface systems of all lines: by cyclic reduction (chain_reduced) or the serial two-ended chain;
+// chain_lines: lines per workgroup.
+bool chain_reduced(int P, int nlines);
+int chain_lines(int P, int nlines);
 hipError_t launch_chain(const ChainParams &c, hipStream_t s);
 hipError_t launch_flux_divergence(int nx, int ny, double ids, double ids2, const Model &M,
                                   const double *u, double alpha, double beta, const double *add,
@@ -305,7 +309,8 @@ hipError_t launch_pass_ens(int dir, bool solve, int km, const EnsParams &e, hipS
 int bn_tiles_x(int nx);
 int bn_tiles_y(int ny);
 hipError_t launch_bn_ens(const EnsParams &e, hipStream_t s);
-hipError_t launch_chain_ens(const EnsParams &e, int dir, hipStream_t s);
+// items: (film, block of chain_lines lines) of the films whose chains are reduced, or of the others
+hipError_t launch_chain_ens(const EnsParams &e, int dir, bool reduced, hipStream_t s);
 hipError_t launch_ens_control(FilmState *st, int nfilms, const EnsScheme &S, int *active_count, hipStream_t s);
 hipError_t launch_ens_begin(FilmState *st, int nfilms, hipStream_t s);
 hipError_t launch_ens_commit(const FilmDesc *desc, FilmState *st, int nfilms, double *buf0, double *buf1,

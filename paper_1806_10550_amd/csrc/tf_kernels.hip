@@ -16,7 +16,7 @@
 //                            registers, plug in the segment's outer unknowns and
 //                            back-substitute; write w (y sweep) or u_{k+1} (x sweep).
 // No band matrix is ever stored: coefficients are recomputed from the u tile.
-#include "tf_sweep.h"
+#include "tf_chain.h"
 
 namespace tf {
 
@@ -753,6 +753,18 @@ __device__ __forceinline__ void chain_line(const ChainParams &c, int line, int w
     }
 }
 
+// At most CH_MAX_LINES lines of at most CH_MAXP segments: cyclic reduction (tf_chain.h). The two-ended chain
+// below is bound by its P / 2 dependent steps (0.4 us a segment) whatever the number of lines, the reduction by
+// its arithmetic once its waves fill the GPU: 128 segments of 700 lines 49 -> 20 us, 64 of 4096 32 -> 28, but
+// 128 of 8192 77 against 155, so longer batches and longer lines keep the chain.
+constexpr int CH_MAX_LINES = 4096;
+template <int WJ>
+__global__ void __launch_bounds__(64 * WJ * CH_LINES) k_chain_reduce(ChainParams c, int nblocks)
+{
+    __shared__ __align__(16) double2 buf[ch_lds(WJ)];
+    chain_reduce<WJ>(c, xcd_tile(blockIdx.x, nblocks) * CH_LINES, buf);
+}
+
 __global__ void __launch_bounds__(128) k_chain(ChainParams c)
 {
     __shared__ ChainMeet mt;
@@ -760,18 +772,26 @@ __global__ void __launch_bounds__(128) k_chain(ChainParams c)
     chain_line(c, blockIdx.x * 64 + lane, wave, lane, mt);
 }
 
-// Ensemble version: block -> (film, block of 64 lines); dir 0 chains the y sweep.
+// Ensemble versions: block -> (film, block of CH_LINES or 64 lines); dir 0 chains the y sweep.
+__device__ __forceinline__ ChainParams ens_chain_params(const EnsParams &e, const FilmDesc &d, int dir)
+{
+    return ChainParams{dir == 0 ? d.nx : d.ny, dir == 0 ? d.Py : d.Px, e.rel + d.roff * NREL, e.chain + d.roff * NCHAIN,
+                       e.ext + d.roff * NEXT};
+}
+__global__ void __launch_bounds__(64 * 2 * CH_LINES) k_chain_reduce_ens(EnsParams e, int dir)
+{
+    __shared__ __align__(16) double2 buf[ch_lds(2)];
+    const int f = e.items[2 * blockIdx.x], lb = e.items[2 * blockIdx.x + 1];
+    if (!e.state[f].active) return;
+    chain_reduce<2>(ens_chain_params(e, e.desc[f], dir), lb * CH_LINES, buf);
+}
 __global__ void __launch_bounds__(128) k_chain_ens(EnsParams e, int dir)
 {
     __shared__ ChainMeet mt;
     const int f = e.items[2 * blockIdx.x], lb = e.items[2 * blockIdx.x + 1];
-    const FilmState *s = e.state + f;
-    if (!s->active) return;
-    const FilmDesc d = e.desc[f];
-    ChainParams c{dir == 0 ? d.nx : d.ny, dir == 0 ? d.Py : d.Px, e.rel + d.roff * NREL, e.chain + d.roff * NCHAIN,
-                  e.ext + d.roff * NEXT};
+    if (!e.state[f].active) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    chain_line(c, lb * 64 + lane, wave, lane, mt);
+    chain_line(ens_chain_params(e, e.desc[f], dir), lb * 64 + lane, wave, lane, mt);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1124,9 +1144,15 @@ hipError_t launch_pass(int dir, bool solve, const PassParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
+bool chain_reduced(int P, int nlines) { return P <= CH_MAXP && nlines <= CH_MAX_LINES; }
+int chain_lines(int P, int nlines) { return chain_reduced(P, nlines) ? CH_LINES : 64; }
+
 hipError_t launch_chain(const ChainParams &c, hipStream_t s)
 {
-    k_chain<<<dim3((c.nlines + 63) / 64), dim3(128), 0, s>>>(c);
+    const int nb = (c.nlines + CH_LINES - 1) / CH_LINES;
+    if (!chain_reduced(c.P, c.nlines)) k_chain<<<dim3((c.nlines + 63) / 64), dim3(128), 0, s>>>(c);
+    else if (c.P <= 65) k_chain_reduce<1><<<dim3(nb), dim3(64 * CH_LINES), 0, s>>>(c, nb);
+    else k_chain_reduce<2><<<dim3(nb), dim3(128 * CH_LINES), 0, s>>>(c, nb);
     return hipGetLastError();
 }
 
@@ -1229,9 +1255,10 @@ hipError_t launch_bn_ens(const EnsParams &e, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_chain_ens(const EnsParams &e, int dir, hipStream_t s)
+hipError_t launch_chain_ens(const EnsParams &e, int dir, bool reduced, hipStream_t s)
 {
-    k_chain_ens<<<dim3(e.nitems), dim3(128), 0, s>>>(e, dir);
+    if (reduced) k_chain_reduce_ens<<<dim3(e.nitems), dim3(128 * CH_LINES), 0, s>>>(e, dir);
+    else k_chain_ens<<<dim3(e.nitems), dim3(128), 0, s>>>(e, dir);
     return hipGetLastError();
 }
 

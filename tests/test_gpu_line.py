@@ -80,6 +80,26 @@ def test_stored_band_lines_match_oracle(orc, n, transposed):
             assert np.max(np.abs(x[:, l] - ref)) <= 1e-12 * max(1.0, np.max(np.abs(ref))), (n, nl, l)
 
 
+@pytest.mark.parametrize("nx,ny", [(4097, 129), (4200, 70), (9, 2049), (66, 4160), (5, 4161), (3, 8256), (3, 8257),
+                                   (130, 2304)])
+def test_partitioned_chains_match_oracle(orc, nx, ny):
+    """Interface systems on both sides of the rules between cyclic reduction (one and two waves per line)
+    and the serial chain: 2, 64, 65, 66, 129 and 130 segments, 4096 and more lines."""
+    ds, dt = 0.67347, 0.2
+    nx = max(nx, 4)
+    un = synth.noise_film(nx, ny, seed=nx + ny, amp=0.01)
+    g = Grid(nx, ny, ds)
+    g.set_model(10.0, 0.1, 3, 2)
+    g.set_xsweep("partitioned")
+    u = torch.from_numpy(un).to(DEV)
+    out = torch.empty_like(u)
+    e, r, flags = g.newton_iteration(u, u, out, dt)
+    ref, e_ref, _ = orc.adi_iteration(orc.Model(kappa=10.0, b=0.1, n=3.0, m=2.0), un, un, ds, dt, 1.0)
+    assert np.max(np.abs(out.cpu().numpy() - ref)) <= 1e-10 * np.max(np.abs(ref - un)) + 4e-16
+    assert flags == 0 and e == pytest.approx(e_ref, rel=1e-8)
+    g.close()
+
+
 def test_ensemble_of_every_line_class_equals_single_films():
     """One film per geometry class of the columns and rows (and one that takes tiles), bit for bit."""
     shapes = [(100, 90), (300, 60), (500, 300), (600, 500), (700, 600), (800, 700), (1000, 800), (1200, 900), (30, 1200),
