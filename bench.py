@@ -37,7 +37,9 @@ ALGO_BYTES_PER_CELL = {"relations_y": 16, "solve_y": 24, "relations_x": 16, "sol
 KERNEL_SOURCES = ["paper_1806_10550_amd/csrc/tf_kernels.hip", "paper_1806_10550_amd/csrc/tf_internal.h",
                   "paper_1806_10550_amd/csrc/tf_device.h", "paper_1806_10550_amd/csrc/tf_sweep.h",
                   "paper_1806_10550_amd/csrc/tf_xrow.hip", "paper_1806_10550_amd/csrc/tf_line.h",
-                  "paper_1806_10550_amd/csrc/tf_line_body.h", "paper_1806_10550_amd/csrc/tf_line.hip"]
+                  "paper_1806_10550_amd/csrc/tf_line_body.h", "paper_1806_10550_amd/csrc/tf_line.hip",
+                  "paper_1806_10550_amd/csrc/tf_chain.h"]
+
 def traffic_file(config="large8192"):
     return os.path.join(ROOT, "profiles", f"traffic_{config}.json")
 

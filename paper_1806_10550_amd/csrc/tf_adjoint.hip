@@ -711,14 +711,7 @@ Choice pick_variant(int np, int nl, bool trans)
     if (found && best_d < 0.7 && !(c.variant == V_PCR && np > tf::PCR_MAX)
         && !(c.variant == V_LINE && !tf::sbline_supported(np)))
         return c;
-    // shapes away from every tuned one: the whole-line kernel where it measured fastest (lines of at most
-    // 1024 cells in any number but the shortest by the ten thousand; of 2048 up to a few hundred thousand
-    // cells: 1024 x 512 lines 17 against 28 us partitioned, 2048 x 256 24 against 34, 2048 x 4096 213
-    // against 262, 4096 x 4096 609 against 512)
-    if (np >= 4 && (np <= 1024 || (np <= 2048 && nl <= 4096) || (np <= 4096 && nl <= 512)) && !(np <= 192 && nl >= 32768))
-        c.variant = V_LINE;
-    else
-        c.variant = nl >= 65536 ? V_THOMAS : V_PARTITIONED;
+    c.variant = nl >= 65536 ? V_THOMAS : V_PARTITIONED;
     c.block = 64;
     return c;
 }

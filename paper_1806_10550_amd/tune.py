@@ -5,7 +5,9 @@
                                         [--xs-lengths ...] [--xs-batches ...]
 
 Each shape is timed by tf_autotune for plain and for transposed solves (partitioned,
-Thomas with 64/128/256 lines per workgroup, block cyclic reduction for lengths <= 2048),
+Thomas with 64/128/256 lines per workgroup, block cyclic reduction for lengths <= 2048,
+whole lines for lengths <= 4096; lengths and batches by twos, so that every shape between
+them is within the distance at which an entry counts),
 and each x-sweep shape (row length, number of rows) by tf_autotune_xsweep (partitioned
 against whole-row), and appended as one JSON line to
 FILE (default: autotune_<arch>.jsonl beside this module). tf_autotune_load (or
@@ -22,8 +24,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 def main(argv=None):
     ap = argparse.ArgumentParser()
     ap.add_argument("--out")
-    ap.add_argument("--lengths", default="128,256,512,1024,2048,4096,8192")
-    ap.add_argument("--batches", default="16,256,512,4096,65536")
+    ap.add_argument("--lengths", default="64,128,256,512,1024,2048,4096,8192")
+    ap.add_argument("--batches", default="16,32,64,128,256,512,1024,2048,4096,8192,16384,65536")
     ap.add_argument("--max-cells", type=int, default=1 << 27, help="skip shapes with more cells")
     ap.add_argument("--xs-lengths", default="64,128,256,384,512,768,1024,1536,2048,3072,4096,8192")
     ap.add_argument("--xs-batches", default="64,256,1024,2048,4096,8192")
