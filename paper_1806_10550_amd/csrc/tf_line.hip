@@ -11,9 +11,9 @@ bool xrow_supported(int nx) { return nx >= 4 && nx <= XR_MAX_NX; }
 // elimination is a serial chain over them and small launches do not fill the GPU (128^2 and 512^2: 8 and
 // 11 us a sweep with 4 and 8, where 16 took 29 and 23). For long lines 16 positions in few waves beat 8 in
 // twice as many, whose cyclic reduction costs twice as much per cell (rows of 1000 cells, 8192 of them: 68
-// against 89 us; 4096^2: 164 against 263). Lengths between the powers of two leave no lanes
-// idle (600^2: 35 -> 27 us for both sweeps, 3001 x 700 polymer 74 -> 60). The partitioned x sweep takes longer at every length and number of rows (2048^2: 87
-// against 52 us, 8192 rows of 4096: 485 against 344).
+// against 89 us; 4096^2: 164 against 263). Lengths between the powers of two leave no lanes idle (600^2:
+// 35 -> 27 us for both sweeps, 3001 x 700 polymer 74 -> 60). The partitioned x sweep takes longer at every
+// length and number of rows (2048^2: 87 against 52 us, 8192 rows of 4096: 485 against 344).
 static int line_positions(int n, int W) { return W > 4 ? 16 : (n <= 256 ? 4 : 2 * ((n + 128 * W - 1) / (128 * W))); }
 LineGeom xline_geom(int nx)
 {
@@ -21,13 +21,22 @@ LineGeom xline_geom(int nx)
     const int W = (nx + 1023) / 1024;
     return {line_positions(nx, W), W};
 }
-// Columns of more than 1024 cells need a workgroup of 8 waves and 135 KB of LDS, one per CU, that
+// Columns of more than 1024 cells need a workgroup of 8 waves and up to 135 KB of LDS, one per CU, that
 // overlaps nothing: with many of them the partitioned passes stream better (8192 x 2048: 268 against
-// 251 us; 2048^2: 67 against 92), and the NLC model, whose cells cost most, loses more by evaluating
-// the neighbouring columns' cells than the partition costs (1637^2: 102 against 97 us).
+// 251 us; 4096 x 2048: 127 against 142; 2048^2: 65 against 86). The NLC model, whose cells cost most, also evaluates its neighbouring
+// columns' cells, and its time goes by rounds of one workgroup per CU (1300 rows: 68 us from 1100 to 1450
+// columns, 100 from 2200 to 3072): whole columns gain where the last round leaves the GPU well filled
+// (700 x 1300: 37 against 53 us partitioned, 1637^2 79 against 91, 2700 x 1637 114 against 124, 4000 x 1500
+// 135 against 151; 1100 x 1300 70 against 69, 2200 x 1300 100 against 95) and, with 16 positions per lane,
+// in at most two rounds (2048^2 108 against 114, 3000 x 2000 157 against 145).
 LineGeom yline_geom(int km, int nx, int ny)
 {
-    if (ny < 4 || ny > 2048 || (ny > 1024 && (nx > 4096 || km == KM_NLC))) return {0, 0};
+    if (ny < 4 || ny > 2048 || (ny > 1024 && nx > 4096)) return {0, 0};
+    if (km == KM_NLC && ny > 1024) {
+        constexpr int round = 256 * LN_COLS; // columns
+        const int n = (nx + round - 1) / round;
+        if (n > 1 && (4 * nx < 3 * round * n || (ny > 1792 && n > 2))) return {0, 0};
+    }
     const int W = (ny + 1023) / 1024;
     return {line_positions(ny, W), W};
 }

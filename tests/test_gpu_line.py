@@ -60,6 +60,11 @@ def test_models_match_oracle(orc, model, theta, nx, ny):
     one(orc, nx, ny, theta, model)
 
 
+@pytest.mark.parametrize("ny", [1025, 1280, 1281, 1536, 1537, 1792, 1793, 2048, 2049])
+def test_nlc_long_columns_match_oracle(orc, ny):
+    one(orc, 9, ny, 0.5, "nlc")
+
+
 @pytest.mark.parametrize("transposed", [False, True])
 @pytest.mark.parametrize("n", EDGES + [2049, 3072, 3073, 4095, 4096])
 def test_stored_band_lines_match_oracle(orc, n, transposed):
