@@ -140,6 +140,18 @@ __device__ __forceinline__ void ln_step(M2 &A, M2 &C, double &r0, double &r1, co
     r1 = K.c * s0 + K.d * s1;
 }
 
+// Whether no entry of A (if a) and C (if c) of any lane of the wave reaches 2^-100. The couplings square
+// with every step of the reduction (for I + c J they fall like exp(-distance / (4 c)^(1/4)), distance in
+// cells), and an update is compared with u > 0 only in the sum u + v: below 2^-100 of the largest one
+// nothing of the rest of the line reaches it. NaN and infinity count as coupled. Tests on high words.
+__device__ __forceinline__ bool ln_decoupled(const M2 &A, const M2 &C, bool a, bool c)
+{
+    auto hi = [](double x) { return (unsigned)__double2hiint(x) & 0x7fffffffu; };
+    const unsigned ma = max(max(hi(A.a), hi(A.b)), max(hi(A.c), hi(A.d)));
+    const unsigned mc = max(max(hi(C.a), hi(C.b)), max(hi(C.c), hi(C.d)));
+    return __all(max(a ? ma : 0u, c ? mc : 0u) < (unsigned)(1023 - 100) << 20);
+}
+
 // Top pair record of a lane: x_0 = sum g_k Z_k, x_1 = sum h_k Z_k over the interior (g, h: the
 // first two rows of the inverse of the unit upper factor), minus the coupling of the last interior
 // rows to the lane's own pair.
@@ -187,7 +199,11 @@ __device__ __forceinline__ void ln_equation(const double (&fa)[CPL], const doubl
 
 // The separator pair (B0, B1) of every lane and its left neighbour's (l1, l2) for a line held by
 // one wave. nsub: lanes that hold part of the line (the last nsub of the wave). Every lane calls it.
-template <int CPL>
+// FULL: all steps of the reduction (the stored-band solves, whose results are the answer at every
+// magnitude); else it ends when the lanes are decoupled, of an ordinary film after three of the six steps at
+// 16 positions per lane (x sweep of 8192^2 771 -> 705 us, x + y of 2048^2 111 -> 102). Lanes of four cells
+// decouple a step early at best, which the test costs: they take all steps (128^2: 29.0 against 29.4 us).
+template <int CPL, bool FULL = false>
 __device__ __forceinline__ void ln_pairs(double2 *xch, int lane, int nsub, const double (&fa)[CPL],
                                          const double (&fb)[CPL], const double (&fz)[CPL], const double (&fph)[CPL],
                                          const double (&fps)[CPL], double &B0, double &B1, double &l1, double &l2)
@@ -207,6 +223,7 @@ __device__ __forceinline__ void ln_pairs(double2 *xch, int lane, int nsub, const
         wave_lds_sync();
         // past the wave's ends A or C is zero
         ln_step(A, C, r0, r1, xch, max(lane - d, 0), min(lane + d, 63));
+        if (!FULL && CPL > 4 && ln_decoupled(A, C, true, true)) break;
     }
     B0 = r0;
     B1 = r1;
@@ -221,7 +238,7 @@ __device__ __forceinline__ void ln_pairs(double2 *xch, int lane, int nsub, const
 // one beyond lane 62 likewise (C = I). Each wave then solves the W equations of the G's in its
 // first lanes. Every thread of the workgroup calls it; on entry the factors of every lane are
 // done and xch is still in use by other waves (the first barrier below frees it).
-template <int CPL>
+template <int CPL, bool FULL = false>
 __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane, int wv, int W, const double (&fa)[CPL],
                                             const double (&fb)[CPL], const double (&fz)[CPL], const double (&fph)[CPL],
                                             const double (&fps)[CPL], double &B0, double &B1, double &l1, double &l2)
@@ -249,6 +266,13 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
         ln_put(xch, lane, A, C, r0, r1);
         wave_lds_sync();
         ln_step(A, C, r0, r1, xch, lane >= d ? lane - d : 64, lane + d < 63 ? lane + d : 65);
+        // lanes whose A or C reaches a lane of the wave (the others hold G's)
+        const bool a = lane >= 2 * d && lane < 63, c = lane + 2 * d < 63;
+        if (!FULL && ln_decoupled(A, C, a, c)) {
+            if (a) A = {0.0, 0.0, 0.0, 0.0};
+            if (c) C = {0.0, 0.0, 0.0, 0.0};
+            break;
+        }
     }
     if (lane == 0) ln_put1(mb + 10, A, C, r0, r1);
     if (lane == 62) ln_put1(mb + 20, A, C, r0, r1);
@@ -277,6 +301,7 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
         g1 = K.c * s0 + K.d * s1;
 #pragma unroll 1
         for (int d = 1; d < W; d <<= 1) {
+            if (!FULL && ln_decoupled(gA, gC, true, true)) break;
             __asm__ volatile("" ::: "memory");
             ln_put(xch, lane, gA, gC, g0, g1);
             wave_lds_sync();

@@ -23,9 +23,9 @@ LineGeom xline_geom(int nx)
 }
 // Columns of more than 1024 cells need a workgroup of 8 waves and up to 135 KB of LDS, one per CU, that
 // overlaps nothing: with many of them the partitioned passes stream better (8192 x 2048: 268 against
-// 251 us; 4096 x 2048: 127 against 142; 2048^2: 65 against 86). The NLC model, whose cells cost most, also evaluates its neighbouring
-// columns' cells, and its time goes by rounds of one workgroup per CU (1300 rows: 68 us from 1100 to 1450
-// columns, 100 from 2200 to 3072): whole columns gain where the last round leaves the GPU well filled
+// 251 us; 4096 x 2048: 127 against 142; 2048^2: 65 against 86). The NLC model, whose cells cost most, also
+// evaluates its neighbouring columns' cells, and its time goes by rounds of one workgroup per CU (1300 rows:
+// 68 us from 1100 to 1450 columns, 100 from 2200 to 3072): whole columns gain where the last round leaves the GPU well filled
 // (700 x 1300: 37 against 53 us partitioned, 1637^2 79 against 91, 2700 x 1637 114 against 124, 4000 x 1500
 // 135 against 151; 1100 x 1300 70 against 69, 2200 x 1300 100 against 95) and, with 16 positions per lane,
 // in at most two rounds (2048^2 108 against 114, 3000 x 2000 157 against 145).

@@ -116,10 +116,10 @@ k_sbline(int nl, int np, const double *bands, const double *rhs, double *out, un
     double2 *const xch = reinterpret_cast<double2 *>(priv);
     double B0, B1, l1, l2;
     if constexpr (W > 1) {
-        ln_pairs_mw<CPL>(xch, bnd + ln * W * LN_BND, lane, wv, W, fa, fb, fz, fph, fps, B0, B1, l1, l2);
+        ln_pairs_mw<CPL, true>(xch, bnd + ln * W * LN_BND, lane, wv, W, fa, fb, fz, fph, fps, B0, B1, l1, l2);
     } else {
         __syncthreads();
-        ln_pairs<CPL>(xch, lane, (np + CPL - 1) / CPL, fa, fb, fz, fph, fps, B0, B1, l1, l2);
+        ln_pairs<CPL, true>(xch, lane, (np + CPL - 1) / CPL, fa, fb, fz, fph, fps, B0, B1, l1, l2);
     }
     {
         double *v2 = priv + (CPL + 1) * lane;
