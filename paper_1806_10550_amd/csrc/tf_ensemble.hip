@@ -192,7 +192,7 @@ void build_items(tf_ensemble *e, std::vector<int> &items)
     // line items: the films with most positions per lane first (stable: a film's items stay in order)
     auto put_lines = [&](tf_ensemble::Range &r, std::vector<int> &v) {
         std::vector<int> w;
-        for (int cpl = 16; cpl >= 4; cpl -= 2)
+        for (int cpl = 16; cpl >= 2; cpl -= 2)
             for (size_t i = 0; i < v.size(); i += 3)
                 if (v[i + 2] == cpl) w.insert(w.end(), v.begin() + i, v.begin() + i + 3);
         put(r, spread_lines(w), 3);

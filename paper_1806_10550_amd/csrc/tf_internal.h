@@ -76,7 +76,7 @@ __host__ __device__ inline XRowGeom xrow_geom(int nx)
 }
 
 // Whole lines across the lanes of one or several waves (tf_line.hip): CPL consecutive positions
-// per lane (an even number, 4 to 16), W waves per line, right-aligned: slot s (64 wave + lane) owns the
+// per lane (an even number, 2 to 16), W waves per line, right-aligned: slot s (64 wave + lane) owns the
 // positions w = CPL s + k, cell q = w - sh with sh = 64 W CPL - n < 64 CPL; positions before the
 // line (w < sh, in the first wave) hold copies of its first cells and are decoupled from it.
 constexpr int LN_MAXW = 8;                    // waves of the longest line

@@ -176,6 +176,20 @@ __device__ __forceinline__ void ln_top(const double (&fa)[CPL], const double (&f
     Tb = {-g2 * fb[E - 1] - g1 * fa[E], -g1 * fb[E], -h2 * fb[E - 1] - h1 * fa[E], -h1 * fb[E]};
 }
 
+// Bottom pair of a lane, B_s = b + Bl B_{s-1} + Br T_{s+1}; last: no right neighbour.
+template <int CPL>
+__device__ __forceinline__ void ln_bottom(const double (&fa)[CPL], const double (&fb)[CPL], const double (&fz)[CPL],
+                                          const double (&fph)[CPL], const double (&fps)[CPL], bool last, M2 &Bl, M2 &Br,
+                                          double &b0, double &b1)
+{
+    constexpr int L = CPL - 1;
+    Bl = {fph[L - 1] - fa[L - 1] * fph[L], fps[L - 1] - fa[L - 1] * fps[L], fph[L], fps[L]};
+    Br = {last ? 0.0 : -fb[L - 1] + fa[L - 1] * fa[L], last ? 0.0 : fa[L - 1] * fb[L], last ? 0.0 : -fa[L],
+          last ? 0.0 : -fb[L]};
+    b0 = fz[L - 1] - fa[L - 1] * fz[L];
+    b1 = fz[L];
+}
+
 // Equation of a lane's pair, B_s = r + A B_{s-1} + C B_{s+1}, from its factors and the right
 // neighbour's top pair record (nTl, nTb, n0, n1); last: no right neighbour.
 template <int CPL>
@@ -183,12 +197,10 @@ __device__ __forceinline__ void ln_equation(const double (&fa)[CPL], const doubl
                                             const double (&fph)[CPL], const double (&fps)[CPL], bool last, const M2 &nTl,
                                             const M2 &nTb, double n0, double n1, M2 &A, M2 &C, double &r0, double &r1)
 {
-    constexpr int L = CPL - 1;
-    const M2 Bl = {fph[L - 1] - fa[L - 1] * fph[L], fps[L - 1] - fa[L - 1] * fps[L], fph[L], fps[L]};
-    const M2 Br = {last ? 0.0 : -fb[L - 1] + fa[L - 1] * fa[L], last ? 0.0 : fa[L - 1] * fb[L], last ? 0.0 : -fa[L],
-                   last ? 0.0 : -fb[L]};
+    M2 Bl, Br;
+    double b0, b1;
+    ln_bottom<CPL>(fa, fb, fz, fph, fps, last, Bl, Br, b0, b1);
     const M2 K = inv_i_minus(mul(Br, nTl));
-    const double b0 = fz[L - 1] - fa[L - 1] * fz[L], b1 = fz[L];
     const double s0 = __builtin_fma(Br.a, n0, __builtin_fma(Br.b, n1, b0));
     const double s1 = __builtin_fma(Br.c, n0, __builtin_fma(Br.d, n1, b1));
     r0 = K.a * s0 + K.b * s1;
@@ -208,14 +220,21 @@ __device__ __forceinline__ void ln_pairs(double2 *xch, int lane, int nsub, const
                                          const double (&fb)[CPL], const double (&fz)[CPL], const double (&fph)[CPL],
                                          const double (&fps)[CPL], double &B0, double &B1, double &l1, double &l2)
 {
-    M2 A, C, Tl, Tb;
-    double r0, r1, n0, n1;
-    ln_top<CPL>(fa, fb, fz, fph, fps, Tl, Tb, n0, n1);
-    __asm__ volatile("" ::: "memory"); // earlier reads of this LDS space stay before the writes
-    ln_put(xch, lane, Tl, Tb, n0, n1);
-    wave_lds_sync();
-    ln_get(xch, min(lane + 1, 63), Tl, Tb, n0, n1);
-    ln_equation<CPL>(fa, fb, fz, fph, fps, lane == 63, Tl, Tb, n0, n1, A, C, r0, r1);
+    M2 A, C;
+    double r0, r1;
+    if constexpr (CPL == 2) {
+        // the pair is the whole lane: its two relations are the equation (T_{s+1} = B_{s+1})
+        ln_bottom<CPL>(fa, fb, fz, fph, fps, lane == 63, A, C, r0, r1);
+    } else {
+        M2 Tl, Tb;
+        double n0, n1;
+        ln_top<CPL>(fa, fb, fz, fph, fps, Tl, Tb, n0, n1);
+        __asm__ volatile("" ::: "memory"); // earlier reads of this LDS space stay before the writes
+        ln_put(xch, lane, Tl, Tb, n0, n1);
+        wave_lds_sync();
+        ln_get(xch, min(lane + 1, 63), Tl, Tb, n0, n1);
+        ln_equation<CPL>(fa, fb, fz, fph, fps, lane == 63, Tl, Tb, n0, n1, A, C, r0, r1);
+    }
     if (lane == 0) A = {0.0, 0.0, 0.0, 0.0};
     for (int d = 1; d < nsub; d <<= 1) {
         __asm__ volatile("" ::: "memory");

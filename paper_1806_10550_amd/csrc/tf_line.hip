@@ -9,12 +9,13 @@ bool xrow_supported(int nx) { return nx >= 4 && nx <= XR_MAX_NX; }
 // Positions per lane and waves per line: as few waves as hold the line with 16 positions per lane, then the
 // fewest positions (an even number) that hold it with those. Few positions make short lines fast: the
 // elimination is a serial chain over them and small launches do not fill the GPU (128^2 and 512^2: 8 and
-// 11 us a sweep with 4 and 8, where 16 took 29 and 23). For long lines 16 positions in few waves beat 8 in
+// 11 us a sweep with 4 and 8, where 16 took 29 and 23); two leave nothing to eliminate, the pair being the
+// whole lane (128^2: x + y 18.3 -> 16.4 us). For long lines 16 positions in few waves beat 8 in
 // twice as many, whose cyclic reduction costs twice as much per cell (rows of 1000 cells, 8192 of them: 68
 // against 89 us; 4096^2: 164 against 263). Lengths between the powers of two leave no lanes idle (600^2:
 // 35 -> 27 us for both sweeps, 3001 x 700 polymer 74 -> 60). The partitioned x sweep takes longer at every
 // length and number of rows (2048^2: 87 against 52 us, 8192 rows of 4096: 485 against 344).
-static int line_positions(int n, int W) { return W > 4 ? 16 : (n <= 256 ? 4 : 2 * ((n + 128 * W - 1) / (128 * W))); }
+static int line_positions(int n, int W) { return W > 4 ? 16 : (n <= 128 ? 2 : n <= 256 ? 4 : 2 * ((n + 128 * W - 1) / (128 * W))); }
 LineGeom xline_geom(int nx)
 {
     if (!xrow_supported(nx)) return {0, 0};
@@ -79,13 +80,13 @@ static hipError_t launch_line_km(int dir, const PassParams &p, hipStream_t s)
 #define TF_YL(C, V) case 100 * V + C: k_yline<KM, C, V><<<gy, by, 0, s>>>(p, nb); break
     if (dir == 0) {
         switch (100 * g.W + g.cpl) {
-        TF_YL(4, 1); TF_YL(6, 1); TF_YL(8, 1); TF_YL(10, 1); TF_YL(12, 1); TF_YL(14, 1); TF_YL(16, 1);
+        TF_YL(2, 1); TF_YL(4, 1); TF_YL(6, 1); TF_YL(8, 1); TF_YL(10, 1); TF_YL(12, 1); TF_YL(14, 1); TF_YL(16, 1);
         TF_YL(10, 2); TF_YL(12, 2); TF_YL(14, 2); TF_YL(16, 2);
         default: return hipErrorInvalidValue;
         }
     } else {
         switch (100 * g.W + g.cpl) {
-        TF_XL(4, 1); TF_XL(6, 1); TF_XL(8, 1); TF_XL(10, 1); TF_XL(12, 1); TF_XL(14, 1); TF_XL(16, 1);
+        TF_XL(2, 1); TF_XL(4, 1); TF_XL(6, 1); TF_XL(8, 1); TF_XL(10, 1); TF_XL(12, 1); TF_XL(14, 1); TF_XL(16, 1);
         TF_XL(10, 2); TF_XL(12, 2); TF_XL(14, 2); TF_XL(16, 2);
         TF_XL(12, 3); TF_XL(14, 3); TF_XL(16, 3); TF_XL(14, 4); TF_XL(16, 4); TF_XL(16, 5); TF_XL(16, 6); TF_XL(16, 7); TF_XL(16, 8);
         default: return hipErrorInvalidValue;

@@ -20,7 +20,7 @@ __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 
     const PassParams p = ens_pass_params(e, e.desc[f], st, 1);
 #define TF_XC(C) case C: xline_body<KM, C, (W > 1), AL>(p, j, j, W, sU, s2, bnd); break
     if constexpr (W == 1) {
-        switch (cpl) { TF_XC(4); TF_XC(6); TF_XC(8); TF_XC(10); TF_XC(12); TF_XC(14); default: TF_XC(16); }
+        switch (cpl) { TF_XC(2); TF_XC(4); TF_XC(6); TF_XC(8); TF_XC(10); TF_XC(12); TF_XC(14); default: TF_XC(16); }
     } else if constexpr (W == 2) {
         switch (cpl) { TF_XC(10); TF_XC(12); TF_XC(14); default: TF_XC(16); }
     } else if constexpr (W == 3) {
@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(64 * LN_COLS * W) __attribute__((amdgpu_waves_
     const PassParams p = ens_pass_params(e, e.desc[f], st, 0);
 #define TF_YC(C) case C: yline_body<KM, C, W>(p, b * LN_COLS, b, sU, bnd); break
     if constexpr (W == 1) {
-        switch (cpl) { TF_YC(4); TF_YC(6); TF_YC(8); TF_YC(10); TF_YC(12); TF_YC(14); default: TF_YC(16); }
+        switch (cpl) { TF_YC(2); TF_YC(4); TF_YC(6); TF_YC(8); TF_YC(10); TF_YC(12); TF_YC(14); default: TF_YC(16); }
     } else {
         switch (cpl) { TF_YC(10); TF_YC(12); TF_YC(14); default: TF_YC(16); }
     }
