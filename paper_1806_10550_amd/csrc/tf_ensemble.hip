@@ -131,20 +131,29 @@ tf_status ensure_graph(tf_ensemble *e)
     return TF_OK;
 }
 
-// A line list in launch order: runs of LINE_RUN neighbouring items stay on one XCD (blocks are dispatched
-// round-robin over 8), so that they share halo rows and partly written lines in its L2, and the runs go
-// round the XCDs in turn, the costliest films (sorted first) included. Padded with film -1.
+// A line list in launch order, the films with most positions per lane first: runs of LINE_RUN neighbouring
+// items stay on one XCD (blocks are dispatched round-robin over 8), so that they share halo rows and partly
+// written lines in its L2, and the runs go round the XCDs in turn, the costliest films included. Padded with
+// film -1.
 constexpr size_t LINE_RUN = 16, LINE_XCDS = 8;
-std::vector<int> spread_lines(const std::vector<int> &v)
+struct LineFilm {
+    int f, n, cpl; // n items of film f, cpl positions per lane
+};
+void spread_lines(std::vector<LineFilm> films, std::vector<int> &items)
 {
-    const size_t n = v.size() / 3, group = LINE_RUN * LINE_XCDS, padded = (n + group - 1) / group * group;
-    std::vector<int> out(3 * padded, -1);
-    for (size_t i = 0; i < n; ++i) {
-        const size_t run = i / LINE_RUN, k = i % LINE_RUN;
-        const size_t at = run / LINE_XCDS * group + k * LINE_XCDS + run % LINE_XCDS;
-        std::copy(v.begin() + 3 * i, v.begin() + 3 * i + 3, out.begin() + 3 * at);
-    }
-    return out;
+    std::stable_sort(films.begin(), films.end(), [](const LineFilm &x, const LineFilm &y) { return x.cpl > y.cpl; });
+    size_t n = 0, i = 0;
+    for (const LineFilm &l : films) n += l.n;
+    const size_t group = LINE_RUN * LINE_XCDS, off = items.size();
+    items.resize(off + 3 * ((n + group - 1) / group * group), -1);
+    for (const LineFilm &l : films)
+        for (int b = 0; b < l.n; ++b, ++i) {
+            const size_t run = i / LINE_RUN, k = i % LINE_RUN;
+            int *at = items.data() + off + 3 * (run / LINE_XCDS * group + k * LINE_XCDS + run % LINE_XCDS);
+            at[0] = l.f;
+            at[1] = b;
+            at[2] = l.cpl;
+        }
 }
 
 // Work lists of one iteration: the y sweep of a film is whole-column where tf::yline_geom gives a
@@ -152,7 +161,8 @@ std::vector<int> spread_lines(const std::vector<int> &v)
 // and chain blocks. The b^n list covers every film.
 void build_items(tf_ensemble *e, std::vector<int> &items)
 {
-    std::vector<int> ty, tx, cy[2], cx[2], bnt, yl[tf::YL_MAXW], xl[2 * tf::XL_MAXW];
+    std::vector<int> ty, tx, cy[2], cx[2], bnt;
+    std::vector<LineFilm> yl[tf::YL_MAXW], xl[2 * tf::XL_MAXW];
     // chain blocks of one film's lines: serial chains in list 0, reduced ones in list 1
     auto chains = [](std::vector<int> (&v)[2], int f, int P, int nlines) {
         const int per = tf::chain_lines(P, nlines);
@@ -167,16 +177,14 @@ void build_items(tf_ensemble *e, std::vector<int> &items)
         for (int j = 0; j < tf::bn_tiles_y(d.ny); ++j)
             for (int i = 0; i < tf::bn_tiles_x(d.nx); ++i) bnt.insert(bnt.end(), {f, i, j});
         if (yg.W > 0) {
-            for (int b = 0; b < (d.nx + tf::LN_COLS - 1) / tf::LN_COLS; ++b)
-                yl[yg.W - 1].insert(yl[yg.W - 1].end(), {f, b, yg.cpl});
+            yl[yg.W - 1].push_back({f, (d.nx + tf::LN_COLS - 1) / tf::LN_COLS, yg.cpl});
         } else {
             for (int j = 0; j < d.Py; ++j)
                 for (int i = 0; i < tyx; ++i) ty.insert(ty.end(), {f, i, j});
             chains(cy, f, d.Py, d.nx);
         }
         if (xg.W > 0) {
-            std::vector<int> &v = xl[2 * (xg.W - 1) + (d.nx % xg.cpl == 0)];
-            for (int j = 0; j < d.ny; ++j) v.insert(v.end(), {f, j, xg.cpl});
+            xl[2 * (xg.W - 1) + (d.nx % xg.cpl == 0)].push_back({f, d.ny, xg.cpl});
         } else {
             for (int j = 0; j < txy; ++j)
                 for (int i = 0; i < d.Px; ++i) tx.insert(tx.end(), {f, i, j});
@@ -189,13 +197,10 @@ void build_items(tf_ensemble *e, std::vector<int> &items)
         r.n = (int)(v.size() / per);
         items.insert(items.end(), v.begin(), v.end());
     };
-    // line items: the films with most positions per lane first (stable: a film's items stay in order)
-    auto put_lines = [&](tf_ensemble::Range &r, std::vector<int> &v) {
-        std::vector<int> w;
-        for (int cpl = 16; cpl >= 2; cpl -= 2)
-            for (size_t i = 0; i < v.size(); i += 3)
-                if (v[i + 2] == cpl) w.insert(w.end(), v.begin() + i, v.begin() + i + 3);
-        put(r, spread_lines(w), 3);
+    auto put_lines = [&](tf_ensemble::Range &r, const std::vector<LineFilm> &v) {
+        r.off = items.size();
+        spread_lines(v, items);
+        r.n = (int)((items.size() - r.off) / 3);
     };
     put(e->ty, ty, 3);
     put(e->tx, tx, 3);
