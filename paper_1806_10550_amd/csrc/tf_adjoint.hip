@@ -788,7 +788,7 @@ tf_status sb_solve(Choice ch, bool trans, int mode, int nl, int np, const double
     else if (trans) tf::k_sb_pass<false, true, 0><<<g, b, 0, s>>>(P);
     else tf::k_sb_pass<false, false, 0><<<g, b, 0, s>>>(P);
     TF_AHIP(hipGetLastError());
-    tf::ChainParams C{nl, tf::seg_count(np), S.rel, S.chain, S.ext};
+    tf::ChainParams C{nl, tf::seg_count(np), S.rel, S.chain, S.ext, true};
     TF_AHIP(tf::launch_chain(C, s));
     if (rowio) tf::k_sb_pass<true, true, 0, true><<<g, b, 0, s>>>(P);
     else if (trans && mode == 0) tf::k_sb_pass<true, true, 0><<<g, b, 0, s>>>(P);
@@ -1321,7 +1321,7 @@ tf_status tf_autotune_xsweep(int length, int batch, const char *cache_path)
     P.u = u; P.in2 = w; P.out = out; P.rel = rel; P.ext = ext; P.res = res;
     P.tiles_x = tf::seg_count(length);
     P.tiles_y = (batch + tf::TILE - 1) / tf::TILE;
-    const tf::ChainParams C{batch, tf::seg_count(length), rel, chain, ext};
+    const tf::ChainParams C{batch, tf::seg_count(length), rel, chain, ext, false};
     auto run = [&](int v) -> hipError_t {
         if (v == 1) return tf::launch_line(1, P, s);
         tf::PassParams Q = P;

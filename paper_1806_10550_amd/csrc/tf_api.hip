@@ -236,7 +236,7 @@ tf_status enqueue_iteration(tf_grid *g, const double *bnp, const double *uk, dou
         if ((st = timed(g, P_YLINE, [&] { return tf::launch_line(0, P, g->stream); })) != TF_OK) return st;
     } else {
         if ((st = timed(g, P_REL_Y, [&] { return tf::launch_pass(0, false, P, g->stream); })) != TF_OK) return st;
-        tf::ChainParams C{g->nx, g->Py, g->rel, g->chain, g->ext};
+        tf::ChainParams C{g->nx, g->Py, g->rel, g->chain, g->ext, false};
         if ((st = timed(g, P_CHAIN_Y, [&] { return tf::launch_chain(C, g->stream); })) != TF_OK) return st;
         P.res = nullptr;
         P.res_clear = nullptr;
@@ -256,7 +256,7 @@ tf_status enqueue_iteration(tf_grid *g, const double *bnp, const double *uk, dou
         return timed(g, P_XROW, [&] { return tf::launch_line(1, P, g->stream); });
     }
     if ((st = timed(g, P_REL_X, [&] { return tf::launch_pass(1, false, P, g->stream); })) != TF_OK) return st;
-    tf::ChainParams Cx{g->ny, g->Px, g->rel, g->chain, g->ext};
+    tf::ChainParams Cx{g->ny, g->Px, g->rel, g->chain, g->ext, false};
     if ((st = timed(g, P_CHAIN_X, [&] { return tf::launch_chain(Cx, g->stream); })) != TF_OK) return st;
     P.res = res;
     P.mass = diag ? g->mpart : nullptr; // mass diagnostic of u_{k+1}, formed as it is stored

@@ -6,8 +6,9 @@
 // eliminating each from the other's equation gives
 //   x_q = R_q + A_q B_{q-1} + C_q T_{q+2}       (A, C: 4 x 2),
 // which couples x_q to the B half of its left and the T half of its right neighbour: log2(P - 1) steps of
-// cyclic reduction, each a 4 x 4 solve in 2 x 2 blocks, leave x_q alone. One lane per junction; a workgroup
-// holds CH_LINES lines so that records move in 64-byte pieces.
+// cyclic reduction, each a 4 x 4 solve in 2 x 2 blocks, leave x_q alone. The couplings of an ordinary film span
+// 64 cells and vanish after one or two steps; a line then takes no more (stored-band solves take all). One lane
+// per junction; a workgroup holds CH_LINES lines so that records move in 64-byte pieces.
 #pragma once
 
 #include "tf_line.h"
@@ -32,9 +33,9 @@ __device__ __forceinline__ void ch_mv(const M2 &x, double v0, double v1, double 
 }
 __device__ __forceinline__ M2 m2_neg(const M2 &x) { return {-x.a, -x.b, -x.c, -x.d}; }
 
-// Lines l0 .. l0 + CH_LINES - 1, WJ waves per line (P - 1 <= 64 WJ); buf: ch_lds(WJ) double2 of LDS.
+// Lines l0 .. l0 + CH_LINES - 1, WJ waves per line (P - 1 <= 64 WJ); buf: ch_lds(WJ) double2, flag: WJ CH_LINES words of LDS.
 template <int WJ>
-__device__ __forceinline__ void chain_reduce(const ChainParams &c, int l0, double2 *buf)
+__device__ __forceinline__ void chain_reduce(const ChainParams &c, int l0, double2 *buf, int *flag)
 {
     constexpr int PP = ch_pitch(WJ), NT = 64 * WJ * CH_LINES, NP = NREL / 2;
     const size_t NL = (size_t)c.nlines;
@@ -82,7 +83,22 @@ __device__ __forceinline__ void chain_reduce(const ChainParams &c, int l0, doubl
     };
     // junction q's B half at pairs 0..4, its T half at pairs 5..9 of column q
     for (int d = 1; d < nj; d <<= 1) {
-        if (WJ > 1) __syncthreads(); // the records / the last step's halves have been read
+        // a line takes steps until its junctions are decoupled (ln_decoupled); which it is depends on the line alone
+        const bool in = q < nj && !c.full;
+        bool go = c.full || !(ln_decoupled(J.Ab, J.Cb, in, in) && ln_decoupled(J.At, J.Ct, in, in));
+        if (WJ > 1) {
+            if ((tid & 63) == 0) flag[tid / 64] = go;
+            __syncthreads(); // (also: the records / the last step's halves have been read)
+            bool any = false;
+            go = false;
+            for (int w = 0; w < WJ * CH_LINES; ++w) {
+                any |= flag[w] != 0;
+                go |= w / WJ == ln && flag[w] != 0;
+            }
+            if (!any) break;
+        } else if (!go) {
+            break;
+        }
         __asm__ volatile("" ::: "memory");
         rec[0 * PP + q] = make_double2(J.rb0, J.rb1);
         rec[1 * PP + q] = make_double2(J.Ab.a, J.Ab.b);
@@ -95,6 +111,7 @@ __device__ __forceinline__ void chain_reduce(const ChainParams &c, int l0, doubl
         rec[8 * PP + q] = make_double2(J.Ct.a, J.Ct.b);
         rec[9 * PP + q] = make_double2(J.Ct.c, J.Ct.d);
         sync();
+        if (!go) continue;
         // past the line's ends A or C is zero and any junction's halves will do
         const double2 *L = rec + max(qc - d, 0), *R = rec + min(qc + d, nj - 1);
         const double2 l0v = L[0], l1 = L[PP], l2 = L[2 * PP], l3 = L[3 * PP], l4 = L[4 * PP];

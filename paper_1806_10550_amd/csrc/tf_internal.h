@@ -208,6 +208,7 @@ struct ChainParams {
     const double *rel;
     double *chain;
     double *ext;
+    bool full; // all steps of a cyclic reduction (stored-band solves)
 };
 
 enum ResultWord { RES_EMAX = 0, RES_RMAX = 1, RES_FLAGS = 2, RES_WORDS = 8 };

@@ -755,14 +755,16 @@ __device__ __forceinline__ void chain_line(const ChainParams &c, int line, int w
 
 // At most CH_MAX_LINES lines of at most CH_MAXP segments: cyclic reduction (tf_chain.h). The two-ended chain
 // below is bound by its P / 2 dependent steps (0.4 us a segment) whatever the number of lines, the reduction by
-// its arithmetic once its waves fill the GPU: 128 segments of 700 lines 49 -> 20 us, 64 of 4096 32 -> 28, but
-// 128 of 8192 77 against 155, so longer batches and longer lines keep the chain.
+// reading the records and, with all its steps, by its arithmetic. 128 segments of 700 lines: chain 49 us,
+// reduction 20, ended when the junctions are decoupled 13; 64 of 4096 lines 32, 28, 21; but 128 of 8192 lines
+// 77, 155, 97, so longer batches and longer lines keep the chain.
 constexpr int CH_MAX_LINES = 4096;
 template <int WJ>
 __global__ void __launch_bounds__(64 * WJ * CH_LINES) k_chain_reduce(ChainParams c, int nblocks)
 {
     __shared__ __align__(16) double2 buf[ch_lds(WJ)];
-    chain_reduce<WJ>(c, xcd_tile(blockIdx.x, nblocks) * CH_LINES, buf);
+    __shared__ int flag[WJ * CH_LINES];
+    chain_reduce<WJ>(c, xcd_tile(blockIdx.x, nblocks) * CH_LINES, buf, flag);
 }
 
 __global__ void __launch_bounds__(128) k_chain(ChainParams c)
@@ -776,14 +778,15 @@ __global__ void __launch_bounds__(128) k_chain(ChainParams c)
 __device__ __forceinline__ ChainParams ens_chain_params(const EnsParams &e, const FilmDesc &d, int dir)
 {
     return ChainParams{dir == 0 ? d.nx : d.ny, dir == 0 ? d.Py : d.Px, e.rel + d.roff * NREL, e.chain + d.roff * NCHAIN,
-                       e.ext + d.roff * NEXT};
+                       e.ext + d.roff * NEXT, false};
 }
 __global__ void __launch_bounds__(64 * 2 * CH_LINES) k_chain_reduce_ens(EnsParams e, int dir)
 {
     __shared__ __align__(16) double2 buf[ch_lds(2)];
+    __shared__ int flag[2 * CH_LINES];
     const int f = e.items[2 * blockIdx.x], lb = e.items[2 * blockIdx.x + 1];
     if (!e.state[f].active) return;
-    chain_reduce<2>(ens_chain_params(e, e.desc[f], dir), lb * CH_LINES, buf);
+    chain_reduce<2>(ens_chain_params(e, e.desc[f], dir), lb * CH_LINES, buf, flag);
 }
 __global__ void __launch_bounds__(128) k_chain_ens(EnsParams e, int dir)
 {

@@ -130,8 +130,9 @@ __device__ __forceinline__ void xline_body(const PassParams &p, int j, int rec, 
         }
     }
     double B0, B1, l1, l2;
-    if (MW) ln_pairs_mw<CPL>(reinterpret_cast<double2 *>(priv), bnd, lane, wv, W, fa, fb, fz, fph, fps, B0, B1, l1, l2);
-    else ln_pairs<CPL>(reinterpret_cast<double2 *>(priv), lane, (nx + CPL - 1) / CPL, fa, fb, fz, fph, fps, B0, B1, l1, l2);
+    double2 *const xch = reinterpret_cast<double2 *>(priv);
+    if constexpr (MW) ln_pairs_mw<CPL>(xch, bnd, lane, wv, W, fa, fb, fz, fph, fps, B0, B1, l1, l2);
+    else ln_pairs<CPL>(xch, lane, (nx + CPL - 1) / CPL, fa, fb, fz, fph, fps, B0, B1, l1, l2);
     {
         // back-substitution from the lane's pair and its left neighbour's; v goes to the wave's space
         double *v2 = priv + (CPL + 1) * lane;
