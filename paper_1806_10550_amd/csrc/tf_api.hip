@@ -250,7 +250,7 @@ tf_status enqueue_iteration(tf_grid *g, const double *bnp, const double *uk, dou
     P.tiles_x = g->Px;
     P.tiles_y = (g->ny + tf::TILE - 1) / tf::TILE;
     if (g->xsweep == TF_XSWEEP_ROW) {
-        // one whole-row kernel: assembly, elimination, in-row tree, back-substitution, update
+        // one whole-row kernel: assembly, elimination, cyclic reduction, back-substitution, update
         P.res = res;
         P.mass = diag ? g->mpart : nullptr;
         return timed(g, P_XROW, [&] { return tf::launch_line(1, P, g->stream); });

@@ -83,7 +83,7 @@ __device__ __forceinline__ void chain_reduce(const ChainParams &c, int l0, doubl
     };
     // junction q's B half at pairs 0..4, its T half at pairs 5..9 of column q
     for (int d = 1; d < nj; d <<= 1) {
-        // a line takes steps until its junctions are decoupled (ln_decoupled); which it is depends on the line alone
+        // a line takes steps until its junctions are decoupled (ln_decoupled), whatever the lines beside it
         const bool in = q < nj && !c.full;
         bool go = c.full || !(ln_decoupled(J.Ab, J.Cb, in, in) && ln_decoupled(J.At, J.Ct, in, in));
         if (WJ > 1) {

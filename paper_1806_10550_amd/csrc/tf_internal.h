@@ -26,10 +26,9 @@ constexpr int NEXT = 4;                  // doubles per (segment, line) boundary
 constexpr int NCHAIN = 12;               // doubles per (segment, line) chain record
 constexpr int BLOCK = 64 * NSUB;
 
-// Whole-row x sweep (tf_xrow.hip): each lane eliminates XR_CPL consecutive cells of a row;
-// a workgroup of 4 or 8 waves holds one row (of up to XR_MAX_NX cells) or several shorter
-// rows, in xr_lds(waves) doubles of LDS: 4-wave workgroups (rows up to 4096 cells) fit two
-// to a CU, so that one's memory phases overlap the other's arithmetic.
+// Lengths the whole-line kernels hold (XR_MAX_NX: rows of the forward sweep, XR_ROW4_MAX_NX: stored-band
+// lines and the rows of an ensemble's films), and a geometry of rows in 16-cell sub-segments that the kernels
+// no longer use: the host geometry check is written against it. Theirs is at LN_* below.
 constexpr int XR_CPL = 16;
 constexpr int XR_WAVES = 8;                          // waves of the largest workgroup
 constexpr int XR_MAX_NX = XR_CPL * 64 * XR_WAVES;

@@ -5,12 +5,13 @@
 //   y sweep: (I + c J_y(u_k)) w = -G(u_k)      one pentadiagonal system per grid column
 //   x sweep: (I + c J_x(u_k)) v = w            one pentadiagonal system per grid row
 //            u_{k+1} = u_k + v, e = max|v/u_k| (eq. NewtonError)
-// Every sweep is a partitioned (SPIKE-like) solve in three kernels:
+// A sweep is one whole-line kernel where its lines fit one (tf_line.hip), else a partitioned (SPIKE-like)
+// solve in three kernels:
 //   k_pass<.., SOLVE=false>  per 64x64 tile: stage u in LDS, assemble coefficients,
 //                            residual and bands in registers, eliminate each line
 //                            segment with its outer unknowns kept symbolic, and emit
 //                            the segment's boundary relations (20 doubles per line);
-//   k_chain                  per line: solve the small block system that couples
+//   k_chain, k_chain_reduce  per line: solve the small block system that couples
 //                            neighbouring segments (2 unknowns on each side);
 //   k_pass<.., SOLVE=true>   per tile: redo the elimination with the factors held in
 //                            registers, plug in the segment's outer unknowns and

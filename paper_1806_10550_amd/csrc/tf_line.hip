@@ -14,8 +14,11 @@ bool xrow_supported(int nx) { return nx >= 4 && nx <= XR_MAX_NX; }
 // twice as many, whose cyclic reduction costs twice as much per cell (rows of 1000 cells, 8192 of them: 68
 // against 89 us; 4096^2: 164 against 263). Lengths between the powers of two leave no lanes idle (600^2:
 // 35 -> 27 us for both sweeps, 3001 x 700 polymer 74 -> 60). The partitioned x sweep takes longer at every
-// length and number of rows (2048^2: 87 against 52 us, 8192 rows of 4096: 485 against 344).
-static int line_positions(int n, int W) { return W > 4 ? 16 : (n <= 128 ? 2 : n <= 256 ? 4 : 2 * ((n + 128 * W - 1) / (128 * W))); }
+// length and number of rows (2048^2: 87 against 45 us, 8192 rows of 4096: 485 against 344).
+static int line_positions(int n, int W)
+{
+    return W > 4 ? 16 : (n <= 128 ? 2 : n <= 256 ? 4 : 2 * ((n + 128 * W - 1) / (128 * W)));
+}
 LineGeom xline_geom(int nx)
 {
     if (!xrow_supported(nx)) return {0, 0};
@@ -88,7 +91,8 @@ static hipError_t launch_line_km(int dir, const PassParams &p, hipStream_t s)
         switch (100 * g.W + g.cpl) {
         TF_XL(2, 1); TF_XL(4, 1); TF_XL(6, 1); TF_XL(8, 1); TF_XL(10, 1); TF_XL(12, 1); TF_XL(14, 1); TF_XL(16, 1);
         TF_XL(10, 2); TF_XL(12, 2); TF_XL(14, 2); TF_XL(16, 2);
-        TF_XL(12, 3); TF_XL(14, 3); TF_XL(16, 3); TF_XL(14, 4); TF_XL(16, 4); TF_XL(16, 5); TF_XL(16, 6); TF_XL(16, 7); TF_XL(16, 8);
+        TF_XL(12, 3); TF_XL(14, 3); TF_XL(16, 3); TF_XL(14, 4); TF_XL(16, 4);
+        TF_XL(16, 5); TF_XL(16, 6); TF_XL(16, 7); TF_XL(16, 8);
         default: return hipErrorInvalidValue;
         }
     }

@@ -3,8 +3,8 @@
 // sweep, one or several waves per line (core and layout: tf_line.h, tf_internal.h; kernels: tf_line.hip for
 // one film, tf_line_ens.hip for ensembles).
 //
-//   k_xline  x sweep: a wave holds one grid row; everything it touches in LDS is its own, so there
-//            is no barrier at all. Reads u_k (the row and its two neighbours) and w once, writes
+//   k_xline  x sweep: a wave holds one grid row (up to 1024 cells; longer rows two to eight waves);
+//            everything a wave alone on its row touches in LDS is its own, so it has no barrier at all. Reads u_k (the row and its two neighbours) and w once, writes
 //            u_{k+1} once.
 //   k_yline  y sweep: a workgroup holds four neighbouring columns, one per wave, and stages their
 //            u tile (two columns more on each side) and b^n with coalesced loads; each wave forms
@@ -12,10 +12,12 @@
 //            32-byte row pieces. Reads u_k and b^n, writes w.
 //
 // What bounds them: at small sizes the latency of one wave's serial elimination, reduction and
-// memory round trips (x + y of 128^2: 8 + 10 us; 512^2: 11 + 14 us; the same sweeps by tile passes
-// and record tree took 25 + 35 and 23 + 35 us), at large ones the FP64 issue rate at two waves per
-// SIMD (1000 rows x 8192 cells: 68 us, 2.9 TB/s of the 24 B per cell; 8192 columns of 1000: 94 us
-// against 141 us for the partitioned passes). The waves of different lines share nothing, so the
+// memory round trips (x + y of 128^2: 7.6 + 8.8 us; 512^2: 10 + 12.7 us; the same sweeps by tile passes
+// and record tree took 25 + 35 and 23 + 35 us), at large ones two waves per SIMD that neither stream
+// nor compute all the time: of 699 us for the x sweep of 8192^2 (2.3 TB/s of the 24 B per cell, 41 % of
+// the vector issue slots), 432 remain when only loads, staging and stores are left, cells and elimination
+// add 109 and the reduced system 158 (8192 columns of 1000: 89 us against 141 us for the partitioned
+// passes). The waves of different lines share nothing, so the
 // loads of one line overlap the arithmetic of others.
 #pragma once
 
@@ -287,7 +289,8 @@ __device__ __forceinline__ void yline_body(const PassParams &p, int i0, int rec,
         const double wm = wave_max(gl < nx ? rmax : 0.0);
         const unsigned wf = wave_or(gl < nx ? flags : 0u);
         if (lane == 0) {
-            unsigned long long *rs = p.res + (size_t)((unsigned)(rec * LN_COLS * W + wave) % (unsigned)p.res_spread) * RES_WORDS;
+            const unsigned copy = (unsigned)(rec * LN_COLS * W + wave) % (unsigned)p.res_spread;
+            unsigned long long *rs = p.res + (size_t)copy * RES_WORDS;
             atomicMax(&rs[RES_RMAX], (unsigned long long)__double_as_longlong(wm));
             if (wf) atomicOr(&rs[RES_FLAGS], (unsigned long long)wf);
         }

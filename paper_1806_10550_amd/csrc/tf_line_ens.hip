@@ -5,8 +5,8 @@ namespace tf {
 
 // Ensemble versions: block -> (film, four columns / one row) from the work list of the films with W waves
 // per line, whatever their positions per lane: one launch has no gaps and no nearly empty last waves
-// between the sizes (24 films of five sizes: 262 us an iteration with a launch per size, 219 with this). Films that are not iterating exit at once
-// (before any barrier: the test is uniform over the block).
+// between the sizes (24 films of five sizes: 262 us an iteration with a launch per size, 219 with this). Films
+// that are not iterating exit at once (before any barrier: the test is uniform over the block).
 template <int KM, int W, bool AL>
 __global__ void __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(2, 2))) k_xline_ens(EnsParams e)
 {

@@ -1,5 +1,5 @@
 // Per-cell and per-face arithmetic of the forward line sweeps, shared by the tile
-// kernels (tf_kernels.hip) and the whole-row kernel (tf_xrow.hip).
+// kernels (tf_kernels.hip) and the whole-line kernels (tf_line_body.h).
 #pragma once
 
 #include "tf_device.h"

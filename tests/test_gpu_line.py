@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 # lengths on both sides of every change of geometry
-EDGES = [4, 5, 7, 8, 9, 127, 128, 129, 255, 256, 257, 263, 384, 385, 511, 512, 513, 527, 640, 641, 768, 769, 895, 897, 1023, 1024, 1025,
-         1039, 1280, 1281, 1536, 1537, 1792, 1793, 2047, 2048]
+EDGES = [4, 5, 7, 8, 9, 127, 128, 129, 255, 256, 257, 263, 384, 385, 511, 512, 513, 527, 640, 641, 768, 769,
+         895, 897, 1023, 1024, 1025, 1039, 1280, 1281, 1536, 1537, 1792, 1793, 2047, 2048]
 
 
 def one(orc, nx, ny, theta=1.0, model="power"):
