@@ -85,7 +85,8 @@ __device__ __forceinline__ void chain_reduce(const ChainParams &c, int l0, doubl
     for (int d = 1; d < nj; d <<= 1) {
         // a line takes steps until its junctions are decoupled (ln_decoupled), whatever the lines beside it
         const bool in = q < nj && !c.full;
-        bool go = c.full || !(ln_decoupled(J.Ab, J.Cb, in, in) && ln_decoupled(J.At, J.Ct, in, in));
+        bool go = c.full || !(ln_decoupled(J.Ab, J.Cb, in ? J.rb0 : 0.0, in ? J.rb1 : 0.0, in, in)
+                             && ln_decoupled(J.At, J.Ct, in ? J.rt0 : 0.0, in ? J.rt1 : 0.0, in, in));
         if (WJ > 1) {
             if ((tid & 63) == 0) flag[tid / 64] = go;
             __syncthreads(); // (also: the records / the last step's halves have been read)

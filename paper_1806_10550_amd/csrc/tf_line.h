@@ -143,13 +143,15 @@ __device__ __forceinline__ void ln_step(M2 &A, M2 &C, double &r0, double &r1, co
 // Whether no entry of A (if a) and C (if c) of any lane of the wave reaches 2^-100. The couplings square
 // with every step of the reduction (for I + c J they fall like exp(-distance / (4 c)^(1/4)), distance in
 // cells), and an update is compared with u > 0 only in the sum u + v: below 2^-100 of the largest one
-// nothing of the rest of the line reaches it. NaN and infinity count as coupled. Tests on high words.
-__device__ __forceinline__ bool ln_decoupled(const M2 &A, const M2 &C, bool a, bool c)
+// nothing of the rest of the line reaches it. NaN and infinity, in the right-hand side r too, count as coupled:
+// they spread over the line as in an elimination. Tests on high words.
+__device__ __forceinline__ bool ln_decoupled(const M2 &A, const M2 &C, double r0, double r1, bool a, bool c)
 {
     auto hi = [](double x) { return (unsigned)__double2hiint(x) & 0x7fffffffu; };
     const unsigned ma = max(max(hi(A.a), hi(A.b)), max(hi(A.c), hi(A.d)));
     const unsigned mc = max(max(hi(C.a), hi(C.b)), max(hi(C.c), hi(C.d)));
-    return __all(max(a ? ma : 0u, c ? mc : 0u) < (unsigned)(1023 - 100) << 20);
+    const bool finite = max(hi(r0), hi(r1)) < 0x7ff00000u;
+    return __all(finite && max(a ? ma : 0u, c ? mc : 0u) < (unsigned)(1023 - 100) << 20);
 }
 
 // Top pair record of a lane: x_0 = sum g_k Z_k, x_1 = sum h_k Z_k over the interior (g, h: the
@@ -254,7 +256,7 @@ __device__ __forceinline__ void ln_pairs(double2 *xch, int lane, int nsub, const
         wave_lds_sync();
         // past the wave's ends A or C is zero
         ln_step(A, C, r0, r1, xch, max(lane - d, 0), min(lane + d, 63));
-        if (!FULL && CPL > 4 && ln_decoupled(A, C, true, true)) break;
+        if (!FULL && CPL > 4 && ln_decoupled(A, C, r0, r1, true, true)) break;
     }
     B0 = r0;
     B1 = r1;
@@ -302,7 +304,7 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
         ln_step(A, C, r0, r1, xch, lane >= d ? lane - d : 64, lane + d < 63 ? lane + d : 65);
         // lanes whose A or C reaches a lane of the wave (the others hold G's)
         const bool a = lane >= 2 * d && lane < 63, c = lane + 2 * d < 63;
-        if (!FULL && ln_decoupled(A, C, a, c)) {
+        if (!FULL && ln_decoupled(A, C, r0, r1, a, c)) {
             if (a) A = {0.0, 0.0, 0.0, 0.0};
             if (c) C = {0.0, 0.0, 0.0, 0.0};
             break;
@@ -335,7 +337,7 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
         g1 = K.c * s0 + K.d * s1;
 #pragma unroll 1
         for (int d = 1; d < W; d <<= 1) {
-            if (!FULL && ln_decoupled(gA, gC, true, true)) break;
+            if (!FULL && ln_decoupled(gA, gC, g0, g1, true, true)) break;
             __asm__ volatile("" ::: "memory");
             ln_put(xch, lane, gA, gC, g0, g1);
             wave_lds_sync();

@@ -85,6 +85,49 @@ def test_stored_band_lines_match_oracle(orc, n, transposed):
             assert np.max(np.abs(x[:, l] - ref)) <= 1e-12 * max(1.0, np.max(np.abs(ref))), (n, nl, l)
 
 
+@pytest.mark.parametrize("dt", [1e-9, 1e-3, 10.0])
+@pytest.mark.parametrize("nx,ny,xsweep", [(100, 90, "row"), (512, 300, "row"), (1500, 700, "row"), (640, 1300, "row"),
+                                          (4200, 70, "row"), (200, 2600, "partitioned")])
+def test_weak_and_strong_coupling_match_oracle(orc, nx, ny, xsweep, dt):
+    """The reduction takes no step or many. Bound: pivots good to 11 units of 2^-53 and the norms of the
+    two factors, 1 + 16 c / ds^4 max f0 each (at least the suite's 1e-12). It holds while I + c J is
+    definite; at dt = 1e3 the film's growing modes make it indefinite, and neither these solvers nor a
+    merge tree or the partition meet it (1e-7 to 1e-3 of the update)."""
+    ds = 0.67347
+    un = synth.noise_film(nx, ny, seed=nx + ny, amp=0.01)
+    g = Grid(nx, ny, ds)
+    g.set_model(10.0, 0.1, 3, 2)
+    g.set_xsweep(xsweep)
+    u = torch.from_numpy(un).to(DEV)
+    out = torch.empty_like(u)
+    g.newton_iteration(u, u, out, dt)
+    uo = orc.adi_iteration(orc.Model(kappa=10.0, b=0.1, n=3.0, m=2.0), un, un, ds, dt, 1.0)[0]
+    c = dt * 1.05 / ds ** 4
+    tol = max(1e-12, 11 * 2.0 ** -53 * 2 * (1.0 + 16.0 * c))
+    assert np.max(np.abs(out.cpu().numpy() - uo)) <= tol * np.max(np.abs(uo))
+    g.close()
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("xsweep", ["row", "partitioned"])
+@pytest.mark.parametrize("nx,ny", [(100, 90), (512, 300), (1500, 700), (600, 1500), (70, 2600), (4200, 70)])
+def test_non_finite_right_side_reaches_the_whole_film(nx, ny, xsweep, bad):
+    """u^n non-finite in one cell, u_k finite (so are all bands): the elimination carries it through that
+    column and then through every row, however weakly the cells are coupled."""
+    un = synth.noise_film(nx, ny, seed=nx + ny, amp=0.01)
+    g = Grid(nx, ny, 0.67347)
+    g.set_model(10.0, 0.1, 3, 2)
+    g.set_xsweep(xsweep)
+    uk = torch.from_numpy(un).to(DEV)
+    u = uk.clone()
+    u[ny // 3, nx // 2] = bad
+    out = torch.zeros_like(uk)
+    _, _, flags = g.newton_iteration(u, uk, out, 0.2)
+    assert flags != 0
+    assert not bool(torch.isfinite(out).any())
+    g.close()
+
+
 @pytest.mark.parametrize("transposed", [False, True])
 @pytest.mark.parametrize("n", [64, 248, 256, 500, 777, 1500])
 def test_stored_band_lines_are_as_exact_as_elimination(n, transposed):
