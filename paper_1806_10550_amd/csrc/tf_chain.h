@@ -7,7 +7,8 @@
 //   x_q = R_q + A_q B_{q-1} + C_q T_{q+2}       (A, C: 4 x 2),
 // which couples x_q to the B half of its left and the T half of its right neighbour: log2(P - 1) steps of
 // cyclic reduction, each a 4 x 4 solve in 2 x 2 blocks, leave x_q alone. The couplings of an ordinary film span
-// 64 cells and vanish after one or two steps; a line then takes no more (stored-band solves take all). One lane
+// 64 cells and vanish after one or two steps; a line then takes no more (stored-band solves take all). Lines whose
+// couplings grow (LN_GROWN) are eliminated segment by segment instead. One lane
 // per junction; a workgroup holds CH_LINES lines so that records move in 64-byte pieces.
 #pragma once
 
@@ -33,9 +34,76 @@ __device__ __forceinline__ void ch_mv(const M2 &x, double v0, double v1, double 
 }
 __device__ __forceinline__ M2 m2_neg(const M2 &x) { return {-x.a, -x.b, -x.c, -x.d}; }
 
-// Lines l0 .. l0 + CH_LINES - 1, WJ waves per line (P - 1 <= 64 WJ); buf: ch_lds(WJ) double2, flag: WJ CH_LINES words of LDS.
+// One line's system segment by segment (the recurrence of the tiles' chain, tf_device.h: T_q = tau + N T_{q+1}, B_{q-1} =
+// bt + M T_q), by one wave that fetches the records once more; leaves (B_q, T_{q+1}) in the pairs 8 and 9 of column q.
+template <int PP>
+__device__ __forceinline__ void chain_in_order(const ChainParams &c, int line, double2 *rec)
+{
+    constexpr int NP = NREL / 2;
+    const size_t NL = (size_t)c.nlines;
+    const int P = c.P, lane = threadIdx.x & 63;
+    for (int e = lane; e < NP * P; e += 64)
+        rec[(e % NP) * PP + e / NP] = rec_get2(c.rel + (size_t)(e / NP) * NREL * NL + 2 * (size_t)line, NL, e % NP);
+    wave_lds_sync();
+    double b0 = 0.0, b1 = 0.0; // B_{q-1} = b + M T_q
+    M2 M = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int q = 0; q < P; ++q) {
+        double T[10], B[10];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) {
+            const double2 v = rec[k * PP + q], w = rec[(5 + k) * PP + q];
+            T[2 * k] = v.x; T[2 * k + 1] = v.y;
+            B[2 * k] = w.x; B[2 * k + 1] = w.y;
+        }
+        const M2 Tl = {T[1], T[2], T[6], T[7]}, Tr = {T[3], T[4], T[8], T[9]};
+        const M2 Bl = {B[1], B[2], B[6], B[7]}, Br = {B[3], B[4], B[8], B[9]};
+        const M2 K = inv_i_minus(mul(Tl, M)), N = mul(K, Tr);
+        double s0 = T[0], s1 = T[5];
+        ch_mv(Tl, b0, b1, s0, s1);
+        const double t0 = K.a * s0 + K.b * s1, t1 = K.c * s0 + K.d * s1;
+        ch_mv(M, t0, t1, b0, b1);
+        double n0 = B[0], n1 = B[5];
+        ch_mv(Bl, b0, b1, n0, n1);
+        b0 = n0;
+        b1 = n1;
+        M = m2_ma(mul(Bl, M), N, Br);
+        if (lane == 0) {
+            rec[0 * PP + q] = make_double2(t0, t1);
+            rec[1 * PP + q] = make_double2(N.a, N.b);
+            rec[2 * PP + q] = make_double2(N.c, N.d);
+            rec[3 * PP + q] = make_double2(b0, b1);
+            rec[4 * PP + q] = make_double2(M.a, M.b);
+            rec[5 * PP + q] = make_double2(M.c, M.d);
+        }
+    }
+    double x0 = 0.0, x1 = 0.0; // T_{q+1}: nothing beyond the last segment
+#pragma unroll 1
+    for (int q = P - 1; q > 0; --q) {
+        const double2 t = rec[q], n0 = rec[PP + q], n1 = rec[2 * PP + q];
+        const double2 b = rec[3 * PP + q - 1], m0 = rec[4 * PP + q - 1], m1 = rec[5 * PP + q - 1];
+        const double y0 = __builtin_fma(n0.x, x0, __builtin_fma(n0.y, x1, t.x));
+        x1 = __builtin_fma(n1.x, x0, __builtin_fma(n1.y, x1, t.y));
+        x0 = y0;
+        if (lane == 0) {
+            rec[8 * PP + q - 1] = make_double2(__builtin_fma(m0.x, x0, __builtin_fma(m0.y, x1, b.x)),
+                                               __builtin_fma(m1.x, x0, __builtin_fma(m1.y, x1, b.y)));
+            rec[9 * PP + q - 1] = make_double2(x0, x1);
+        }
+    }
+    wave_lds_sync();
+}
+
+// State of a wave's junctions before a step: its largest coupling's word (down to which of the limits it reaches) and
+// whether its right-hand sides are finite.
+struct ChainState {
+    unsigned m, finite;
+};
+__device__ __forceinline__ bool ch_decoupled(const ChainState &s) { return s.m < LN_DECOUPLED && s.finite != 0u; }
+
+// Lines l0 .. l0 + CH_LINES - 1, WJ waves per line (P - 1 <= 64 WJ); buf: ch_lds(WJ) double2, state: WJ CH_LINES words of LDS.
 template <int WJ>
-__device__ __forceinline__ void chain_reduce(const ChainParams &c, int l0, double2 *buf, int *flag)
+__device__ __forceinline__ void chain_reduce(const ChainParams &c, int l0, double2 *buf, ChainState *state)
 {
     constexpr int PP = ch_pitch(WJ), NT = 64 * WJ * CH_LINES, NP = NREL / 2;
     const size_t NL = (size_t)c.nlines;
@@ -82,23 +150,40 @@ __device__ __forceinline__ void chain_reduce(const ChainParams &c, int l0, doubl
         else wave_lds_sync();
     };
     // junction q's B half at pairs 0..4, its T half at pairs 5..9 of column q
+    const bool in = q < nj;
+    bool grown = false, any_grown = false; // this line; any line of the workgroup (WJ > 1)
     for (int d = 1; d < nj; d <<= 1) {
-        // a line takes steps until its junctions are decoupled (ln_decoupled), whatever the lines beside it
-        const bool in = q < nj && !c.full;
-        bool go = c.full || !(ln_decoupled(J.Ab, J.Cb, in ? J.rb0 : 0.0, in ? J.rb1 : 0.0, in, in)
-                             && ln_decoupled(J.At, J.Ct, in ? J.rt0 : 0.0, in ? J.rt1 : 0.0, in, in));
+        // a line takes steps until its junctions are decoupled or its couplings have grown, whatever the lines beside it
+        const unsigned m = in ? max(max(ln_word(J.Ab), ln_word(J.Cb)), max(ln_word(J.At), ln_word(J.Ct))) : 0u;
+        const unsigned r = in ? max(max(hi_word(J.rb0), hi_word(J.rb1)), max(hi_word(J.rt0), hi_word(J.rt1))) : 0u;
+        const ChainState st = {__any(m >= LN_GROWN) ? LN_GROWN : (__any(m >= LN_DECOUPLED) ? LN_DECOUPLED : 0u),
+                               __all(r < 0x7ff00000u) ? 1u : 0u};
+        bool go;
         if (WJ > 1) {
-            if ((tid & 63) == 0) flag[tid / 64] = go;
+            if ((tid & 63) == 0) state[tid / 64] = st;
             __syncthreads(); // (also: the records / the last step's halves have been read)
             bool any = false;
             go = false;
-            for (int w = 0; w < WJ * CH_LINES; ++w) {
-                any |= flag[w] != 0;
-                go |= w / WJ == ln && flag[w] != 0;
+            for (int l = 0; l < CH_LINES; ++l) {
+                ChainState s = state[l * WJ];
+                for (int w = 1; w < WJ; ++w) {
+                    const ChainState o = state[l * WJ + w];
+                    s = {max(s.m, o.m), s.finite & o.finite};
+                }
+                const bool g = s.m >= LN_GROWN && l0 + l < c.nlines; // (and stays so: it takes no more steps)
+                const bool step = s.m < LN_GROWN && l0 + l < c.nlines && (c.full || !ch_decoupled(s));
+                any_grown |= g;
+                any |= step;
+                if (l == ln) {
+                    grown = g;
+                    go = step;
+                }
             }
             if (!any) break;
-        } else if (!go) {
-            break;
+        } else {
+            grown = st.m >= LN_GROWN && l0 + ln < c.nlines;
+            go = st.m < LN_GROWN && l0 + ln < c.nlines && (c.full || !ch_decoupled(st));
+            if (!go) break;
         }
         __asm__ volatile("" ::: "memory");
         rec[0 * PP + q] = make_double2(J.rb0, J.rb1);
@@ -146,6 +231,15 @@ __device__ __forceinline__ void chain_reduce(const ChainParams &c, int l0, doubl
         const M2 Fb = mul(J.Ab, lA), Ft = mul(J.At, lA), Gb = mul(J.Cb, rC), Gt = mul(J.Ct, rC);
         solve(Fb, Ft, J.Ab, J.At);
         solve(Gb, Gt, J.Cb, J.Ct);
+    }
+    if (grown && tid % (64 * WJ) < 64) chain_in_order<PP>(c, l0 + ln, rec);
+    if (WJ > 1 && any_grown) __syncthreads();
+    if (grown && in) {
+        const double2 b = rec[8 * PP + q], t = rec[9 * PP + q];
+        J.rb0 = b.x;
+        J.rb1 = b.y;
+        J.rt0 = t.x;
+        J.rt1 = t.y;
     }
     // boundary records: segment s takes l = B_{s-1} and r = T_{s+1}; through LDS so that a position's lines
     // are stored together

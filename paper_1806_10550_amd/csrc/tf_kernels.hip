@@ -764,8 +764,8 @@ template <int WJ>
 __global__ void __launch_bounds__(64 * WJ * CH_LINES) k_chain_reduce(ChainParams c, int nblocks)
 {
     __shared__ __align__(16) double2 buf[ch_lds(WJ)];
-    __shared__ int flag[WJ * CH_LINES];
-    chain_reduce<WJ>(c, xcd_tile(blockIdx.x, nblocks) * CH_LINES, buf, flag);
+    __shared__ ChainState state[WJ * CH_LINES];
+    chain_reduce<WJ>(c, xcd_tile(blockIdx.x, nblocks) * CH_LINES, buf, state);
 }
 
 __global__ void __launch_bounds__(128) k_chain(ChainParams c)
@@ -784,10 +784,10 @@ __device__ __forceinline__ ChainParams ens_chain_params(const EnsParams &e, cons
 __global__ void __launch_bounds__(64 * 2 * CH_LINES) k_chain_reduce_ens(EnsParams e, int dir)
 {
     __shared__ __align__(16) double2 buf[ch_lds(2)];
-    __shared__ int flag[2 * CH_LINES];
+    __shared__ ChainState state[2 * CH_LINES];
     const int f = e.items[2 * blockIdx.x], lb = e.items[2 * blockIdx.x + 1];
     if (!e.state[f].active) return;
-    chain_reduce<2>(ens_chain_params(e, e.desc[f], dir), lb * CH_LINES, buf, flag);
+    chain_reduce<2>(ens_chain_params(e, e.desc[f], dir), lb * CH_LINES, buf, state);
 }
 __global__ void __launch_bounds__(128) k_chain_ens(EnsParams e, int dir)
 {

@@ -54,9 +54,11 @@ __device__ __forceinline__ void fold_right(Band &B, int pos) // pos: n-1 (0) or 
 
 // LU step at position k of a lane's sub-segment with the outer unknowns l1 = x_{p0-2},
 // l2 = x_{p0-1} kept symbolic (z: constant part, ph: coefficient of l1, ps: of l2); the
-// factors of every position stay in the arrays for the back-substitution. EXACT: the pivot's
-// reciprocal to the last bits (the stored-band solves, whose result is the answer itself).
-template <int CPL, bool EXACT = false>
+// factors of every position stay in the arrays for the back-substitution. The pivots' reciprocals are good to the
+// last bits: with one refinement (rcp_pivot, as in the tiles) the lanes' pairs lose twice the tiles' digits on stiff
+// films (largest error of an iterate at dt = 50, 128^2: tiles 5.0e-13, one refinement 9.9e-13, two 3.4e-13; 512 x 300
+// at dt = 100: 5.1e-9, 5.3e-9, 1.5e-9) for less than 1 % of the time (newton 128^2 28.2 -> 28.3 us, 8192^2 1563 -> 1566).
+template <int CPL>
 __device__ __forceinline__ void xr_elim(int k, const Band &B, double rhs, double (&fa)[CPL], double (&fb)[CPL],
                                         double (&fz)[CPL], double (&fph)[CPL], double (&fps)[CPL])
 {
@@ -68,7 +70,7 @@ __device__ __forceinline__ void xr_elim(int k, const Band &B, double rhs, double
     const double ps2 = k >= 2 ? fps[k - 2] : (k == 1 ? 1.0 : 0.0), ps1 = k >= 1 ? fps[k - 1] : 1.0;
     const double gam = B.b - B.a * al2;
     const double mu = B.c - B.a * be2 - gam * al1;
-    const double rm = EXACT ? rcp(mu) : rcp_pivot(mu);
+    const double rm = rcp(mu);
     fa[k] = (B.d - gam * be1) * rm;
     fb[k] = B.e * rm;
     fz[k] = (rhs - B.a * z2 - gam * z1) * rm;
@@ -140,18 +142,123 @@ __device__ __forceinline__ void ln_step(M2 &A, M2 &C, double &r0, double &r1, co
     r1 = K.c * s0 + K.d * s1;
 }
 
-// Whether no entry of A (if a) and C (if c) of any lane of the wave reaches 2^-100. The couplings square
-// with every step of the reduction (for I + c J they fall like exp(-distance / (4 c)^(1/4)), distance in
-// cells), and an update is compared with u > 0 only in the sum u + v: below 2^-100 of the largest one
-// nothing of the rest of the line reaches it. NaN and infinity, in the right-hand side r too, count as coupled:
-// they spread over the line as in an elimination. Tests on high words.
-__device__ __forceinline__ bool ln_decoupled(const M2 &A, const M2 &C, double r0, double r1, bool a, bool c)
+// High word of the largest |entry| of a block (its exponent and leading bits); NaN and infinity above all.
+__device__ __forceinline__ unsigned hi_word(double x) { return (unsigned)__double2hiint(x) & 0x7fffffffu; }
+__device__ __forceinline__ unsigned ln_word(const M2 &x)
 {
-    auto hi = [](double x) { return (unsigned)__double2hiint(x) & 0x7fffffffu; };
-    const unsigned ma = max(max(hi(A.a), hi(A.b)), max(hi(A.c), hi(A.d)));
-    const unsigned mc = max(max(hi(C.a), hi(C.b)), max(hi(C.c), hi(C.d)));
-    const bool finite = max(hi(r0), hi(r1)) < 0x7ff00000u;
-    return __all(finite && max(a ? ma : 0u, c ? mc : 0u) < (unsigned)(1023 - 100) << 20);
+    return max(max(hi_word(x.a), hi_word(x.b)), max(hi_word(x.c), hi_word(x.d)));
+}
+constexpr unsigned LN_DECOUPLED = (1023u - 100u) << 20; // 2^-100
+// Couplings from which a reduction is not trusted: 16. While the matrix is definite they stay below about 8,
+// and the reduction is as exact as an elimination. Once the film's growing modes make I + c J indefinite they
+// pass 1e2 to 1e6 in its steps and the (I - D)^-1 lose as many digits (lines of 777 cells at dt = 1000, worst
+// of 200: 6e-4 of the solution where elimination in order keeps 1e-7); such lines are solved again in order
+// (ln_serial). 0.2 <= dt <= 50: no line of a noise film, dt = 70 a tenth to a half, dt >= 100 all.
+constexpr unsigned LN_GROWN = (1023u + 4u) << 20;
+
+// Whether the wave's couplings (ma, mc: ln_word of A and C, 0 where they reach no lane of the wave) are all below
+// 2^-100. They square with every step of the reduction (for I + c J they fall like exp(-distance / (4 c)^(1/4)),
+// distance in cells), and an update is compared with u > 0 only in the sum u + v: below 2^-100 of the largest one
+// nothing of the rest of the line reaches it. NaN and infinity, in the right-hand side r too, count as coupled:
+// they spread over the line as in an elimination.
+__device__ __forceinline__ bool ln_decoupled(unsigned ma, unsigned mc, double r0, double r1)
+{
+    return __all(max(hi_word(r0), hi_word(r1)) < 0x7ff00000u && max(ma, mc) < LN_DECOUPLED);
+}
+
+// Value of lane s (uniform over the wave).
+__device__ __forceinline__ double ln_bcast(double x, int s)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane((int)b, s), hi = __builtin_amdgcn_readlane((int)(b >> 32), s);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// The equations B_s = r_s + A_s B_{s-1} + C_s B_{s+1} of the lanes first ..= last (uniform) by elimination in
+// order: afterwards every one of these lanes holds its B_s = r + A B_{first-1} + C B_{last+1} (OUTER false: there
+// is nothing beyond them, A and C are not formed). For lines whose couplings grow in a reduction. All lanes carry the
+// recurrence; the records stay in the exchange space, so that the path takes few registers from the usual one.
+template <bool OUTER>
+__device__ __forceinline__ void ln_serial(double2 *xch, int lane, int first, int last, M2 &A, M2 &C, double &r0,
+                                          double &r1)
+{
+    __asm__ volatile("" ::: "memory");
+    ln_put(xch, lane, A, C, r0, r1);
+    wave_lds_sync();
+    M2 a, c;
+    double q0, q1;
+    ln_get(xch, first, a, c, q0, q1);
+#pragma unroll 1
+    for (int s = first + 1; s <= last; ++s) {
+        M2 eA, eC;
+        double e0, e1;
+        ln_get(xch, s, eA, eC, e0, e1);
+        const M2 K = inv_i_minus(mul(eA, c));
+        const double s0 = __builtin_fma(eA.a, q0, __builtin_fma(eA.b, q1, e0));
+        const double s1 = __builtin_fma(eA.c, q0, __builtin_fma(eA.d, q1, e1));
+        q0 = K.a * s0 + K.b * s1;
+        q1 = K.c * s0 + K.d * s1;
+        if (OUTER) a = mul(K, mul(eA, a));
+        c = mul(K, eC);
+        if (lane == 0) ln_put(xch, s, a, c, q0, q1);
+    }
+#pragma unroll 1
+    for (int s = last - 1; s >= first; --s) {
+        M2 eA, eC;
+        double e0, e1;
+        ln_get(xch, s, eA, eC, e0, e1);
+        const double s0 = __builtin_fma(eC.a, q0, __builtin_fma(eC.b, q1, e0));
+        q1 = __builtin_fma(eC.c, q0, __builtin_fma(eC.d, q1, e1));
+        q0 = s0;
+        if (OUTER) {
+            a = m2_ma(eC, a, eA);
+            c = mul(eC, c);
+        }
+        if (lane == 0) ln_put(xch, s, a, c, q0, q1);
+    }
+    wave_lds_sync();
+    ln_get(xch, lane, A, C, r0, r1);
+}
+
+// Two cells per lane: the rows themselves (bands b, right-hand sides f) of the lanes first .. 63 by plain
+// elimination. The pairs' equations, each divided by its unpivoted 2 x 2 block, cost a digit more than
+// the wider lanes' on indefinite lines (128 cells at dt = 100, median: 1.2e-12 in order by pairs, 5e-13 by rows).
+__device__ __forceinline__ void ln_rows(int lane, int first, const Band (&b)[2], const double (&f)[2], double &B0,
+                                        double &B1)
+{
+    double al2 = 0.0, be2 = 0.0, z2 = 0.0, al1 = 0.0, be1 = 0.0, z1 = 0.0; // of the two rows before
+    double oa[2], ob[2], oz[2];                                             // of this lane's rows
+#pragma unroll
+    for (int k = 0; k < 2; ++k) oa[k] = ob[k] = oz[k] = 0.0;
+#pragma unroll 1
+    for (int s = first; s < 64; ++s) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const double a = ln_bcast(b[k].a, s), gam = ln_bcast(b[k].b, s) - a * al2;
+            const double rm = rcp(ln_bcast(b[k].c, s) - a * be2 - gam * al1);
+            const double al = (ln_bcast(b[k].d, s) - gam * be1) * rm, be = ln_bcast(b[k].e, s) * rm;
+            const double z = (ln_bcast(f[k], s) - a * z2 - gam * z1) * rm;
+            al2 = al1; be2 = be1; z2 = z1;
+            al1 = al; be1 = be; z1 = z;
+            if (lane == s) {
+                oa[k] = al;
+                ob[k] = be;
+                oz[k] = z;
+            }
+        }
+    }
+    double x1 = 0.0, x2 = 0.0;
+#pragma unroll 1
+    for (int s = 63; s >= first; --s) {
+        const double v1 = ln_bcast(oz[1], s) - ln_bcast(oa[1], s) * x1 - ln_bcast(ob[1], s) * x2;
+        const double v0 = ln_bcast(oz[0], s) - ln_bcast(oa[0], s) * v1 - ln_bcast(ob[0], s) * x1;
+        x2 = v1;
+        x1 = v0;
+        if (lane == s) {
+            B0 = v0;
+            B1 = v1;
+        }
+    }
 }
 
 // Top pair record of a lane: x_0 = sum g_k Z_k, x_1 = sum h_k Z_k over the interior (g, h: the
@@ -211,9 +318,9 @@ __device__ __forceinline__ void ln_equation(const double (&fa)[CPL], const doubl
     C = mul(K, mul(Br, nTb));
 }
 
-// The pair's own equation once more, with the neighbours' solutions: the rounding errors of the reduction's
-// steps shrink by the couplings (stored-band solves of 248 cells, four a lane: 3.1e-16 -> 2.3e-16 of the
-// solution's norm).
+// The pair's own equation once more, with the neighbours' solutions: where the couplings are below one the
+// rounding errors of the reduction's steps shrink by them (stored-band solves of 248 cells, four a lane:
+// 3.1e-16 -> 2.3e-16 of the solution's norm). Not for grown lines, whose errors they would multiply.
 __device__ __forceinline__ void ln_again(const M2 &A, const M2 &C, double r0, double r1, double l0, double l1, double n0,
                                          double n1, double &B0, double &B1)
 {
@@ -221,19 +328,23 @@ __device__ __forceinline__ void ln_again(const M2 &A, const M2 &C, double r0, do
     B1 = __builtin_fma(A.c, l0, __builtin_fma(A.d, l1, __builtin_fma(C.c, n0, __builtin_fma(C.d, n1, r1))));
 }
 
-// The separator pair (B0, B1) of every lane and its left neighbour's (l1, l2) for a line held by
-// one wave. nsub: lanes that hold part of the line (the last nsub of the wave). Every lane calls it.
-// FULL: all steps of the reduction (the stored-band solves, whose results are the answer at every
-// magnitude); else it ends when the lanes are decoupled, of an ordinary film after three of the six steps at
-// 16 positions per lane (x sweep of 8192^2 771 -> 705 us, x + y of 2048^2 111 -> 102). Lanes of four cells
-// decouple a step early at best, which the test costs: they take all steps (128^2: 29.0 against 29.4 us).
-template <int CPL, bool FULL = false>
-__device__ __forceinline__ void ln_pairs(double2 *xch, int lane, int nsub, const double (&fa)[CPL],
-                                         const double (&fb)[CPL], const double (&fz)[CPL], const double (&fph)[CPL],
-                                         const double (&fps)[CPL], double &B0, double &B1, double &l1, double &l2)
+// The factors behind an opaque barrier: what is formed from them again afterwards is not kept in registers
+// from the first time.
+template <int CPL>
+__device__ __forceinline__ void ln_launder(double (&fa)[CPL], double (&fb)[CPL], double (&fz)[CPL], double (&fph)[CPL],
+                                           double (&fps)[CPL])
 {
-    M2 A, C;
-    double r0, r1;
+#pragma unroll
+    for (int k = 0; k < CPL; ++k)
+        __asm__ volatile("" : "+v"(fa[k]), "+v"(fb[k]), "+v"(fz[k]), "+v"(fph[k]), "+v"(fps[k]));
+}
+
+// Equation (A, C, r) of every lane's pair for a line held by one wave.
+template <int CPL>
+__device__ __forceinline__ void ln_own(double2 *xch, int lane, const double (&fa)[CPL], const double (&fb)[CPL],
+                                       const double (&fz)[CPL], const double (&fph)[CPL], const double (&fps)[CPL],
+                                       M2 &A, M2 &C, double &r0, double &r1)
+{
     if constexpr (CPL == 2) {
         // the pair is the whole lane: its two relations are the equation (T_{s+1} = B_{s+1})
         ln_bottom<CPL>(fa, fb, fz, fph, fps, lane == 63, A, C, r0, r1);
@@ -248,54 +359,102 @@ __device__ __forceinline__ void ln_pairs(double2 *xch, int lane, int nsub, const
         ln_equation<CPL>(fa, fb, fz, fph, fps, lane == 63, Tl, Tb, n0, n1, A, C, r0, r1);
     }
     if (lane == 0) A = {0.0, 0.0, 0.0, 0.0};
+}
+
+// The separator pair (B0, B1) of every lane and its left neighbour's (l1, l2) for a line held by
+// one wave. nsub: lanes that hold part of the line (the last nsub of the wave). Every lane calls it.
+// FULL: all steps of the reduction (the stored-band solves, whose results are the answer at every
+// magnitude); else it ends when the lanes are decoupled, of an ordinary film after three of
+// the six steps at 16 positions per lane (x sweep of 8192^2 771 -> 705 us, x + y of 2048^2 111 -> 102). Lanes
+// of two or four cells decouple a step early at best, which the test costs: they take all steps (256^2 and 128^2).
+// Lines whose couplings grow past LN_GROWN are solved in order instead; lines of two cells per lane return true
+// then and leave it to the caller, who has the rows (ln_rows).
+template <int CPL, bool FULL = false>
+__device__ __forceinline__ bool ln_pairs(double2 *xch, int lane, int nsub, double (&fa)[CPL],
+                                         double (&fb)[CPL], double (&fz)[CPL], double (&fph)[CPL], double (&fps)[CPL],
+                                         double &B0, double &B1, double &l1, double &l2)
+{
+    M2 A, C;
+    double r0, r1;
+    ln_own<CPL>(xch, lane, fa, fb, fz, fph, fps, A, C, r0, r1);
     const M2 A0 = A, C0 = C;
     const double q0 = r0, q1 = r1;
+    unsigned grown = max(ln_word(A), ln_word(C));
     for (int d = 1; d < nsub; d <<= 1) {
         __asm__ volatile("" ::: "memory");
         ln_put(xch, lane, A, C, r0, r1);
         wave_lds_sync();
         // past the wave's ends A or C is zero
         ln_step(A, C, r0, r1, xch, max(lane - d, 0), min(lane + d, 63));
-        if (!FULL && CPL > 4 && ln_decoupled(A, C, r0, r1, true, true)) break;
+        const unsigned ma = ln_word(A), mc = ln_word(C);
+        grown = max(grown, max(ma, mc));
+        if (!FULL && CPL > 4 && ln_decoupled(ma, mc, r0, r1)) break;
+    }
+    const bool again = __any(lane >= 64 - nsub && grown >= LN_GROWN);
+    if (CPL > 2 && again) {
+        if (FULL) {
+            A = A0;
+            C = C0;
+            r0 = q0;
+            r1 = q1;
+        } else {
+            ln_launder<CPL>(fa, fb, fz, fph, fps);
+            ln_own<CPL>(xch, lane, fa, fb, fz, fph, fps, A, C, r0, r1);
+        }
+        ln_serial<false>(xch, lane, 64 - nsub, 63, A, C, r0, r1);
     }
     B0 = r0;
     B1 = r1;
-    if (FULL) ln_again(A0, C0, q0, q1, lane_prev(r0), lane_prev(r1), lane_next(r0), lane_next(r1), B0, B1);
+    if (FULL && !again) ln_again(A0, C0, q0, q1, lane_prev(r0), lane_prev(r1), lane_next(r0), lane_next(r1), B0, B1);
     l1 = lane_prev(B0);
     l2 = lane_prev(B1);
+    return again;
 }
 
 // The same for a line held by W consecutive waves (wv: this wave's place on the line, bnd: LN_BND
-// doubles per wave of the line, shared by its waves, disjoint from xch). The pairs of each wave's
-// lane 63 (G) are the separators of the upper level: cyclic reduction inside a wave keeps
-// G_{wv-1} and G_wv symbolic, because a neighbour beyond lane 0 is the record "itself" (A = I) and
-// one beyond lane 62 likewise (C = I). Each wave then solves the W equations of the G's in its
-// first lanes. Every thread of the workgroup calls it; on entry the factors of every lane are
+// doubles per wave of the line, shared by its waves, disjoint from xch; lz: the first lane of the line's first
+// wave that holds part of it). The pairs of each wave's lane 63 (G) are the separators of the upper level:
+// cyclic reduction inside a wave keeps G_{wv-1} and G_wv symbolic, because a neighbour beyond lane 0 is the
+// record "itself" (A = I) and one beyond lane 62 likewise (C = I). Each wave then solves the W equations of
+// the G's in its first lanes. A wave whose couplings grow solves its own lanes in order, and likewise the G's; the
+// other waves of the line take no notice. Every thread of the workgroup calls it; on entry the factors of every lane are
 // done and xch is still in use by other waves (the first barrier below frees it).
 template <int CPL, bool FULL = false>
-__device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane, int wv, int W, const double (&fa)[CPL],
-                                            const double (&fb)[CPL], const double (&fz)[CPL], const double (&fph)[CPL],
-                                            const double (&fps)[CPL], double &B0, double &B1, double &l1, double &l2)
+__device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane, int wv, int W, int lz,
+                                            double (&fa)[CPL], double (&fb)[CPL], double (&fz)[CPL],
+                                            double (&fph)[CPL], double (&fps)[CPL], double &B0, double &B1, double &l1,
+                                            double &l2)
 {
     double *const mb = bnd + (size_t)wv * LN_BND;
-    M2 A, C, Tl, Tb;
-    double r0, r1, n0, n1;
-    ln_top<CPL>(fa, fb, fz, fph, fps, Tl, Tb, n0, n1);
-    if (lane == 0) ln_put1(mb, Tl, Tb, n0, n1);
-    __syncthreads();
-    ln_put(xch, lane, Tl, Tb, n0, n1);
+    M2 A, C;
+    double r0, r1;
+    // a lane's equation from its own and the next lane's top pair (lane 63: the next wave's lane 0)
+    auto equation = [&] {
+        M2 Tl, Tb;
+        double n0, n1;
+        if (lane < 63) ln_get(xch, lane + 1, Tl, Tb, n0, n1);
+        else ln_get1(wv + 1 < W ? mb + LN_BND : mb, Tl, Tb, n0, n1);
+        ln_equation<CPL>(fa, fb, fz, fph, fps, lane == 63 && wv == W - 1, Tl, Tb, n0, n1, A, C, r0, r1);
+        if (lane == 0 && wv == 0) A = {0.0, 0.0, 0.0, 0.0};
+    };
+    {
+        M2 Tl, Tb;
+        double n0, n1;
+        ln_top<CPL>(fa, fb, fz, fph, fps, Tl, Tb, n0, n1);
+        if (lane == 0) ln_put1(mb, Tl, Tb, n0, n1);
+        __syncthreads();
+        ln_put(xch, lane, Tl, Tb, n0, n1);
+    }
     if (lane < 2) {
         const double i = lane == 0 ? 1.0 : 0.0;
         ln_put(xch, 64 + lane, M2{i, 0.0, 0.0, i}, M2{1.0 - i, 0.0, 0.0, 1.0 - i}, 0.0, 0.0);
     }
     wave_lds_sync();
-    if (lane < 63) ln_get(xch, lane + 1, Tl, Tb, n0, n1);
-    else ln_get1(wv + 1 < W ? mb + LN_BND : mb, Tl, Tb, n0, n1);
-    ln_equation<CPL>(fa, fb, fz, fph, fps, lane == 63 && wv == W - 1, Tl, Tb, n0, n1, A, C, r0, r1);
-    if (lane == 0 && wv == 0) A = {0.0, 0.0, 0.0, 0.0};
+    equation();
     if (lane == 63) ln_put1(mb + 30, A, C, r0, r1);
     const M2 A0 = A, C0 = C;
     const double q0 = r0, q1 = r1;
+    unsigned grown = max(ln_word(A), ln_word(C));
 #pragma unroll 1
     for (int d = 1; d < 64; d <<= 1) {
         __asm__ volatile("" ::: "memory");
@@ -304,11 +463,33 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
         ln_step(A, C, r0, r1, xch, lane >= d ? lane - d : 64, lane + d < 63 ? lane + d : 65);
         // lanes whose A or C reaches a lane of the wave (the others hold G's)
         const bool a = lane >= 2 * d && lane < 63, c = lane + 2 * d < 63;
-        if (!FULL && ln_decoupled(A, C, r0, r1, a, c)) {
+        const unsigned ma = ln_word(A), mc = ln_word(C);
+        grown = max(grown, max(ma, mc));
+        if (!FULL && ln_decoupled(a ? ma : 0u, c ? mc : 0u, r0, r1)) {
             if (a) A = {0.0, 0.0, 0.0, 0.0};
             if (c) C = {0.0, 0.0, 0.0, 0.0};
             break;
         }
+    }
+    const int first = wv == 0 ? lz : 0;
+    const bool again = __any(lane >= first && lane < 63 && grown >= LN_GROWN);
+    if (again) {
+        if (FULL) {
+            A = A0;
+            C = C0;
+            r0 = q0;
+            r1 = q1;
+        } else {
+            ln_launder<CPL>(fa, fb, fz, fph, fps);
+            M2 Tl, Tb;
+            double n0, n1;
+            ln_top<CPL>(fa, fb, fz, fph, fps, Tl, Tb, n0, n1);
+            __asm__ volatile("" ::: "memory");
+            ln_put(xch, lane, Tl, Tb, n0, n1);
+            wave_lds_sync();
+            equation();
+        }
+        ln_serial<true>(xch, lane, first, 62, A, C, r0, r1);
     }
     if (lane == 0) ln_put1(mb + 10, A, C, r0, r1);
     if (lane == 62) ln_put1(mb + 20, A, C, r0, r1);
@@ -316,32 +497,44 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
     // equation of G_i on lane i: lane 63's own with lane 62's and the next wave's lane 0's records
     {
         const int i = min(lane, W - 1);
-        const double *b = bnd + (size_t)i * LN_BND;
-        M2 gA, gC, nA, nC;
+        M2 gA, gC;
         double g0, g1;
-        ln_get1(b + 30, gA, gC, g0, g1);
-        ln_get1(b + 20, nA, nC, n0, n1);
-        M2 D = mul(gA, nC);
-        const M2 lA = mul(gA, nA);
-        double s0 = __builtin_fma(gA.a, n0, __builtin_fma(gA.b, n1, g0));
-        double s1 = __builtin_fma(gA.c, n0, __builtin_fma(gA.d, n1, g1));
-        ln_get1((i + 1 < W ? b + LN_BND : b) + 10, nA, nC, n0, n1); // the last wave's C is zero
-        D = m2_ma(gC, nA, D);
-        s0 = __builtin_fma(gC.a, n0, __builtin_fma(gC.b, n1, s0));
-        s1 = __builtin_fma(gC.c, n0, __builtin_fma(gC.d, n1, s1));
-        const M2 K = inv_i_minus(D);
-        gA = mul(K, lA);
-        gC = mul(K, mul(gC, nC));
-        if (i == 0) gA = {0.0, 0.0, 0.0, 0.0};
-        g0 = K.a * s0 + K.b * s1;
-        g1 = K.c * s0 + K.d * s1;
+        auto outer = [&] {
+            const double *b = bnd + (size_t)i * LN_BND;
+            M2 nA, nC;
+            double n0, n1;
+            ln_get1(b + 30, gA, gC, g0, g1);
+            ln_get1(b + 20, nA, nC, n0, n1);
+            M2 D = mul(gA, nC);
+            const M2 lA = mul(gA, nA);
+            double s0 = __builtin_fma(gA.a, n0, __builtin_fma(gA.b, n1, g0));
+            double s1 = __builtin_fma(gA.c, n0, __builtin_fma(gA.d, n1, g1));
+            ln_get1((i + 1 < W ? b + LN_BND : b) + 10, nA, nC, n0, n1); // the last wave's C is zero
+            D = m2_ma(gC, nA, D);
+            s0 = __builtin_fma(gC.a, n0, __builtin_fma(gC.b, n1, s0));
+            s1 = __builtin_fma(gC.c, n0, __builtin_fma(gC.d, n1, s1));
+            const M2 K = inv_i_minus(D);
+            gA = mul(K, lA);
+            gC = mul(K, mul(gC, nC));
+            if (i == 0) gA = {0.0, 0.0, 0.0, 0.0};
+            g0 = K.a * s0 + K.b * s1;
+            g1 = K.c * s0 + K.d * s1;
+        };
+        outer();
+        unsigned gw = max(ln_word(gA), ln_word(gC));
 #pragma unroll 1
         for (int d = 1; d < W; d <<= 1) {
-            if (!FULL && ln_decoupled(gA, gC, g0, g1, true, true)) break;
+            if (!FULL && ln_decoupled(ln_word(gA), ln_word(gC), g0, g1)) break;
             __asm__ volatile("" ::: "memory");
             ln_put(xch, lane, gA, gC, g0, g1);
             wave_lds_sync();
             ln_step(gA, gC, g0, g1, xch, max(i - d, 0), min(i + d, W - 1));
+            gw = max(gw, max(ln_word(gA), ln_word(gC)));
+        }
+        if (__any(gw >= LN_GROWN)) {
+            __asm__ volatile("" ::: "memory");
+            outer();
+            ln_serial<false>(xch, lane, 0, W - 1, gA, gC, g0, g1);
         }
         __asm__ volatile("" ::: "memory");
         xch[lane] = make_double2(g0, g1);
@@ -359,7 +552,7 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
     l2 = lane_prev(B1);
     l1 = lane == 0 ? p0 : l1;
     l2 = lane == 0 ? p1 : l2;
-    if (FULL) {
+    if (FULL && !again) {
         double b0, b1;
         ln_again(A0, C0, q0, q1, l1, l2, lane_next(B0), lane_next(B1), b0, b1);
         B0 = lane == 63 ? B0 : b0; // (its right neighbour is another wave's)

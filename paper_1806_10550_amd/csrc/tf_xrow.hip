@@ -110,13 +110,14 @@ k_sbline(int nl, int np, const double *bands, const double *rhs, double *out, un
     double fa[CPL], fb[CPL], fz[CPL], fph[CPL], fps[CPL];
 #pragma unroll
     for (int k = 0; k < CPL; ++k)
-        xr_elim<CPL, true>(k, Band{v[0][k], v[1][k], v[2][k], v[3][k], v[4][k]}, v[5][k], fa, fb, fz, fph, fps);
+        xr_elim<CPL>(k, Band{v[0][k], v[1][k], v[2][k], v[3][k], v[4][k]}, v[5][k], fa, fb, fz, fph, fps);
     // (a barrier frees the staging space:) the waves' exchange records, then their solutions
     double *const priv = lds + wave * ln_priv(CPL);
     double2 *const xch = reinterpret_cast<double2 *>(priv);
     double B0, B1, l1, l2;
     if constexpr (W > 1) {
-        ln_pairs_mw<CPL, true>(xch, bnd + ln * W * LN_BND, lane, wv, W, fa, fb, fz, fph, fps, B0, B1, l1, l2);
+        ln_pairs_mw<CPL, true>(xch, bnd + ln * W * LN_BND, lane, wv, W, sh / CPL, fa, fb, fz, fph, fps, B0, B1, l1,
+                               l2);
     } else {
         __syncthreads();
         ln_pairs<CPL, true>(xch, lane, (np + CPL - 1) / CPL, fa, fb, fz, fph, fps, B0, B1, l1, l2);
