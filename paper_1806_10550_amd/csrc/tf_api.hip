@@ -281,11 +281,24 @@ struct Result {
     int flags;
     double mass, hmin; // of that iterate (mass only)
 };
-tf_status read_result(tf_grid *g, bool batch, bool mass, Result *out)
+// Mass and minimum of the last iterate from the records its x sweep left (Sec. "Conservation of Mass"),
+// combined in a fixed order into pinned memory: no extra read of h.
+tf_status enqueue_mass(tf_grid *g)
 {
     double *hm = reinterpret_cast<double *>(g->hres + 8);
+    return timed(g, P_MASS, [&] { return tf::launch_mass_tiles(g->mpart, mass_records(g), hm, g->stream); });
+}
+void read_mass(const tf_grid *g, double *mass, double *hmin)
+{
+    const volatile unsigned long long *w = g->hres + 8;
+    const unsigned long long m = w[0], h = w[1];
+    std::memcpy(mass, &m, sizeof(double));
+    std::memcpy(hmin, &h, sizeof(double));
+}
+tf_status read_result(tf_grid *g, bool batch, bool mass, Result *out)
+{
     if (mass) {
-        const tf_status st = timed(g, P_MASS, [&] { return tf::launch_mass_tiles(g->mpart, mass_records(g), hm, g->stream); });
+        const tf_status st = enqueue_mass(g);
         if (st != TF_OK) return st;
     }
     TF_HIP(tf::launch_result(g->res, RES_SLOTS, batch ? control_words(g) : nullptr, g->epoch, g->iter - 1, g->hres,
@@ -300,8 +313,8 @@ tf_status read_result(tf_grid *g, bool batch, bool mass, Result *out)
     std::memcpy(&out->r, &r, sizeof(double));
     std::memcpy(&out->e_prev, &ep, sizeof(double));
     out->flags = (int)w[4];
-    out->mass = mass ? hm[0] : 0.0;
-    out->hmin = mass ? hm[1] : 0.0;
+    out->mass = out->hmin = 0.0;
+    if (mass) read_mass(g, &out->mass, &out->hmin);
     return TF_OK;
 }
 
@@ -419,7 +432,8 @@ tf_status do_step(tf_grid *g, double *dt_inout, tf_step_info *info)
                 uk = dst;
             }
             Result R;
-            if ((st = read_result(g, batch, diag, &R)) != TF_OK) return st;
+            // (a batch that ends a step carries the mass with it; single iterations leave it to the accepted one, below)
+            if ((st = read_result(g, batch, diag && batch, &R)) != TF_OK) return st;
             const int done = (int)(R.it - first) + 1;   // iterations that ran
             if (done < n && (n - done) % 2 != 0) uk = prev; // the iterate of iteration R.it
             g->iter = R.it + 1; // launches that stood down left their slots untouched
@@ -439,6 +453,13 @@ tf_status do_step(tf_grid *g, double *dt_inout, tf_step_info *info)
         }
         if (!accepted && bad == 0) ++iters; // iterations exhausted: reported as one past the limit
         if (accepted) {
+            // combining the records is one workgroup's work (ny W records): once per step, not per iteration
+            if (diag && !batch) {
+                if ((st = enqueue_mass(g)) != TF_OK) return st;
+                TF_HIP(hipStreamSynchronize(g->stream));
+                if (g->prof) prof_flush(g);
+                read_mass(g, &mass, &hmin);
+            }
             g->cur = uk;
             g->last_iters = iters;
             status = TF_OK;
