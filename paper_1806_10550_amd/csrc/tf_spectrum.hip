@@ -42,19 +42,20 @@ __global__ void __launch_bounds__(256) k_spec_load(const double *__restrict__ h,
 }
 
 // T[c][j] = F[j][c] for the columns c < nc of the half spectrum (rows of pitch2 complex values), through
-// a 32 x 32 LDS tile.
+// a 32 x 32 LDS tile; zero for nc <= c < nb, which the column plan transforms with the rest (what an earlier,
+// wider window left there would grow by each transform).
 __global__ void __launch_bounds__(256) k_spec_columns(const hipfftDoubleComplex *__restrict__ F, int n, int pitch2,
-                                                      int nc, hipfftDoubleComplex *__restrict__ T)
+                                                      int nc, int nb, hipfftDoubleComplex *__restrict__ T)
 {
     __shared__ hipfftDoubleComplex t[32][33];
     const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32, x = threadIdx.x & 31, y = threadIdx.x >> 5;
 #pragma unroll
     for (int r = y; r < 32; r += 8)
-        if (r0 + r < n && c0 + x < nc) t[r][x] = F[(size_t)(r0 + r) * pitch2 + c0 + x];
+        t[r][x] = r0 + r < n && c0 + x < nc ? F[(size_t)(r0 + r) * pitch2 + c0 + x] : hipfftDoubleComplex{0.0, 0.0};
     __syncthreads();
 #pragma unroll
     for (int c = y; c < 32; c += 8)
-        if (c0 + c < nc && r0 + x < n) T[(size_t)(c0 + c) * n + r0 + x] = t[x][c];
+        if (c0 + c < nb && r0 + x < n) T[(size_t)(c0 + c) * n + r0 + x] = t[x][c];
 }
 
 // A[(wy + E) * W + (wx + E)] = |F(wx mod n, wy mod n)| / n^2 for wx, wy in [-E, E], from the
@@ -268,9 +269,6 @@ tf_status get_work(int n, size_t small_doubles, size_t groups, int nc, SpecWork 
             return sfail(TF_ENOMEM, "spectrum buffer allocation failed");
         }
         w.col_cap = col_need;
-        // columns past the ones asked for are transformed with the rest of the batch: finite values
-        if (hipMemset(w.colbuf, 0, col_need * sizeof(hipfftDoubleComplex)) != hipSuccess)
-            return sfail(TF_EDEVICE, "spectrum buffer setup failed");
     }
     if (w.small_cap < small_doubles) {
         if (w.small) (void)hipFree(w.small);
@@ -359,9 +357,10 @@ tf_status tf_radial_spectrum(const double *h, int n, double ds, double h0, doubl
         return sfail(TF_EDEVICE, "hipfftExecD2Z failed");
     size_t sx = 1, sy = n / 2 + 1;
     if (nc > 0) {
-        tf::k_spec_columns<<<dim3((nc + 31) / 32, (n + 31) / 32), 256, 0, s>>>(F, n, n / 2 + 1, nc, wk->colbuf);
+        const int nb = col_batch(nc);
+        tf::k_spec_columns<<<dim3((nb + 31) / 32, (n + 31) / 32), 256, 0, s>>>(F, n, n / 2 + 1, nc, nb, wk->colbuf);
         if (hipGetLastError() != hipSuccess) return sfail(TF_EDEVICE, "spectrum transpose launch failed");
-        const hipfftHandle col = wk->cols[col_batch(nc)];
+        const hipfftHandle col = wk->cols[nb];
         F = wk->colbuf;
         if (hipfftSetStream(col, s) != HIPFFT_SUCCESS || hipfftExecZ2Z(col, F, F, HIPFFT_FORWARD) != HIPFFT_SUCCESS)
             return sfail(TF_EDEVICE, "hipfftExecZ2Z failed");
