@@ -277,9 +277,12 @@ tf_status tf_jacobian_apply_t(tf_grid *g, const double *u, const double *mu, dou
  * number of groups. TF_EINVAL when capacity is too small (npoints then holds the number
  * needed) or qmax spans more than 2^26 groups. Each group's sum is formed in a fixed order, so
  * the output is bit-reproducible. Work is enqueued on `stream` (hipStream_t, NULL = default)
- * and the call returns after it has finished. The FFT plan and device scratch (8 n (n + 2)
- * bytes, 16 n bytes per transformed column of the window, the smoothing window, the group
- * means and an index of the window by group, about 4 pi M bytes) are kept per (device, n) for later calls until tf_spectrum_release; calls are
+ * and the call returns after it has finished. Kept per (device, n) for later calls until
+ * tf_spectrum_release: the FFT plans (with the library's own work areas; of column transforms one per
+ * batch size 64, 128, 256, ... used), device scratch (8 n (n + 2) bytes; 16 n bytes per column of the
+ * largest batch used, which is less than twice the columns the window reads, or 64; the smoothing
+ * window; 8 bytes per nonempty group; an index of the window by group, about 4 pi M bytes for
+ * groups up to m = M) and 8 bytes of pinned host memory per nonempty group. Calls are
  * serialised by a lock. */
 tf_status tf_radial_spectrum(const double *h, int n, double ds, double h0, double sigma, double qmax, void *stream,
                              double *q_out, double *s_out, int *count_out, int capacity, int *npoints);

@@ -230,13 +230,10 @@ int col_batch(int nc)
     return b;
 }
 
-// nc: columns of the half spectrum to transform, or 0 for the full 2D transform. Called with g_spec_mu
-// held.
-tf_status get_work(int n, size_t small_doubles, size_t groups, int nc, SpecWork **out)
+// Plans, buffers and scratch of one call. groups: nonempty groups, whose means come back through pinned memory;
+// nc: columns of the half spectrum to transform, or 0 for the full 2D transform. Called with g_spec_mu held.
+tf_status get_work(SpecWork &w, int n, size_t small_doubles, size_t groups, int nc)
 {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return sfail(TF_EDEVICE, "hipGetDevice failed");
-    SpecWork &w = g_spec[WorkKey{dev, n}];
     if (nc == 0 && !w.has_full) {
         if (hipfftPlan2d(&w.full, n, n, HIPFFT_D2Z) != HIPFFT_SUCCESS) return sfail(TF_EDEVICE, "hipfftPlan2d failed");
         w.has_full = true;
@@ -290,7 +287,6 @@ tf_status get_work(int n, size_t small_doubles, size_t groups, int nc, SpecWork 
         }
         w.hmean_cap = groups;
     }
-    *out = &w;
     return TF_OK;
 }
 
@@ -332,17 +328,23 @@ tf_status tf_radial_spectrum(const double *h, int n, double ds, double h0, doubl
         for (double &v : w) v /= z;
     }
     hipStream_t s = (hipStream_t)stream;
+    std::lock_guard<std::mutex> lk(g_spec_mu);
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return sfail(TF_EDEVICE, "hipGetDevice failed");
+    SpecWork *const wk = &g_spec[WorkKey{dev, n}];
+    tf_status st = get_index(*wk, n, R, M);
+    if (st != TF_OK) return st;
+    const int ng = (int)wk->gm.size();
     // small scratch: A (W x W) | B (Wr x W) | C (Wr x Wr) | weights | group means
     const size_t oA = 0, oB = oA + (size_t)W * W, oC = oB + (size_t)W * Wr, oW = oC + (size_t)Wr * Wr,
-                 oS = oW + w.size(), small = oS + (size_t)(M + 1);
-    std::lock_guard<std::mutex> lk(g_spec_mu);
-    // the columns 0 .. E (and their mirror images) are all the window reads
+                 oS = oW + w.size(), small = oS + ng;
+    // The columns 0 .. E (and their mirror images) are all the window reads. Up to half of the half spectrum they win
+    // over the full transform, batches rounded up to a power of two included (whole call, us, columns / full: 2674^2 with
+    // 80 columns 326 / 537, 401 491 / 652, 602 712 / 785, 669 760 / 843; 1637^2 409 columns 376 / 484; 4096^2 122
+    // 241 / 309, 1024 946 / 991; 1024^2 51 75 / 77, 256 126 / 129), up to n = 512 only for lengths with larger prime
+    // factors (401^2 79 / 86): there one launch more costs powers of two 3 to 5 us (512^2 58 / 52, 128^2 57 / 54).
     const int nc = 2 * (E + 1) <= n / 2 + 1 ? E + 1 : 0;
-    SpecWork *wk;
-    tf_status st = get_work(n, small, (size_t)(M + 1), nc, &wk);
-    if (st != TF_OK) return st;
-    if ((st = get_index(*wk, n, R, M)) != TF_OK) return st;
-    const int ng = (int)wk->gm.size();
+    if ((st = get_work(*wk, n, small, ng, nc)) != TF_OK) return st;
     StreamDrain drain{s};
     double *A = wk->small + oA, *B = wk->small + oB, *C = wk->small + oC, *wd = wk->small + oW,
            *mean = wk->small + oS;

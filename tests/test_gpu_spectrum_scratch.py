@@ -44,3 +44,24 @@ def test_narrow_windows_after_a_wide_one():
     for _ in range(230):
         last = at(70)
     assert all(np.array_equal(x, y) for x, y in zip(first, last))
+
+
+def test_group_scratch_is_sized_by_the_groups():
+    """Between a window's inscribed circle and its corners only groups are added: the scratch grows by the added
+    groups' means and their index, not by every m between (of which a quarter or fewer are sums of two squares)."""
+    n = 4096
+    h = torch.full((n, n), 0.5, dtype=torch.float64, device=DEV)
+    free = lambda: torch.cuda.mem_get_info()[0]
+    spectrum_release()
+    k = 2.0 * math.pi / n
+    c1 = radial_spectrum(h, 1.0, 0.5, 0.0, (n // 2 + 0.1) * k)[2]
+    torch.cuda.empty_cache()
+    before = free()
+    c2 = radial_spectrum(h, 1.0, 0.5, 0.0, 0.7072 * n * k)[2]
+    torch.cuda.empty_cache()
+    grown = before - free()
+    groups, members = len(c2) - len(c1), int(c2.sum() - c1.sum())
+    assert (groups, members) == (338580, 3599105)       # counted on the integers
+    # means (8 B) and offsets (4 B) by group, positions (4 B) by member; three allocations of 2 MiB granularity
+    assert grown <= 12 * groups + 4 * members + 3 * 2 * (2 << 20)
+    spectrum_release()
