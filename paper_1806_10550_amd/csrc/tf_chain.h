@@ -8,7 +8,7 @@
 // which couples x_q to the B half of its left and the T half of its right neighbour: log2(P - 1) steps of
 // cyclic reduction, each a 4 x 4 solve in 2 x 2 blocks, leave x_q alone. The couplings of an ordinary film span
 // 64 cells and vanish after one or two steps; a line then takes no more (stored-band solves take all). Lines whose
-// couplings grow (LN_GROWN) are eliminated segment by segment instead. One lane
+// couplings grow (LN_GROWN) are eliminated in order instead. One lane
 // per junction; a workgroup holds CH_LINES lines so that records move in 64-byte pieces.
 #pragma once
 
@@ -34,61 +34,130 @@ __device__ __forceinline__ void ch_mv(const M2 &x, double v0, double v1, double 
 }
 __device__ __forceinline__ M2 m2_neg(const M2 &x) { return {-x.a, -x.b, -x.c, -x.d}; }
 
-// One line's system segment by segment (the recurrence of the tiles' chain, tf_device.h: T_q = tau + N T_{q+1}, B_{q-1} =
-// bt + M T_q), by one wave that fetches the records once more; leaves (B_q, T_{q+1}) in the pairs 8 and 9 of column q.
+// One line's system in order (the recurrence of the tiles' chain, tf_device.h), by one wave that fetches the records once
+// more; leaves (B_q, T_{q+1}) in the pairs 8 and 9 of column q. In two levels, so that the serial length is a fifth of
+// the line's: lane j takes the segments 8 j .. 8 j + 7 in terms of its outer pairs l = B_{8j-1} and T beyond, then the
+// groups are chained with all lanes carrying the recurrence, then lane j goes back through its segments (64 lines of 128
+// segments, the iteration of a 64 x 8192 film: segment after segment 228 us, this 142).
 template <int PP>
 __device__ __forceinline__ void chain_in_order(const ChainParams &c, int line, double2 *rec)
 {
-    constexpr int NP = NREL / 2;
+    constexpr int NP = NREL / 2, G = 8;
     const size_t NL = (size_t)c.nlines;
-    const int P = c.P, lane = threadIdx.x & 63;
+    const int P = c.P, lane = threadIdx.x & 63, ng = (P + G - 1) / G;
     for (int e = lane; e < NP * P; e += 64)
         rec[(e % NP) * PP + e / NP] = rec_get2(c.rel + (size_t)(e / NP) * NREL * NL + 2 * (size_t)line, NL, e % NP);
     wave_lds_sync();
-    double b0 = 0.0, b1 = 0.0; // B_{q-1} = b + M T_q
-    M2 M = {0.0, 0.0, 0.0, 0.0};
+    const M2 zero = {0.0, 0.0, 0.0, 0.0};
+    const int first = G * min(lane, ng - 1), last = min(first + G, P) - 1;
+    // the group's first pair T = F + Fl l + Fr T'' and last pair B = b + bl l + M T'', T'' the pair beyond its last segment
+    double F0 = 0.0, F1 = 0.0, b0 = 0.0, b1 = 0.0;
+    M2 Fl = zero, Fr = {1.0, 0.0, 0.0, 1.0}, bl = {1.0, 0.0, 0.0, 1.0}, M = zero;
+    if (lane < ng) {
 #pragma unroll 1
-    for (int q = 0; q < P; ++q) {
-        double T[10], B[10];
+        for (int q = first; q <= last; ++q) {
+            double T[10], B[10];
 #pragma unroll
-        for (int k = 0; k < 5; ++k) {
-            const double2 v = rec[k * PP + q], w = rec[(5 + k) * PP + q];
-            T[2 * k] = v.x; T[2 * k + 1] = v.y;
-            B[2 * k] = w.x; B[2 * k + 1] = w.y;
-        }
-        const M2 Tl = {T[1], T[2], T[6], T[7]}, Tr = {T[3], T[4], T[8], T[9]};
-        const M2 Bl = {B[1], B[2], B[6], B[7]}, Br = {B[3], B[4], B[8], B[9]};
-        const M2 K = inv_i_minus(mul(Tl, M)), N = mul(K, Tr);
-        double s0 = T[0], s1 = T[5];
-        ch_mv(Tl, b0, b1, s0, s1);
-        const double t0 = K.a * s0 + K.b * s1, t1 = K.c * s0 + K.d * s1;
-        ch_mv(M, t0, t1, b0, b1);
-        double n0 = B[0], n1 = B[5];
-        ch_mv(Bl, b0, b1, n0, n1);
-        b0 = n0;
-        b1 = n1;
-        M = m2_ma(mul(Bl, M), N, Br);
-        if (lane == 0) {
+            for (int k = 0; k < 5; ++k) {
+                const double2 v = rec[k * PP + q], w = rec[(5 + k) * PP + q];
+                T[2 * k] = v.x; T[2 * k + 1] = v.y;
+                B[2 * k] = w.x; B[2 * k + 1] = w.y;
+            }
+            const M2 Tl = {T[1], T[2], T[6], T[7]}, Tr = {T[3], T[4], T[8], T[9]};
+            const M2 Bl = {B[1], B[2], B[6], B[7]}, Br = {B[3], B[4], B[8], B[9]};
+            // B_{q-1} = b + bl l + M T_q gives T_q = t + tl l + N T_{q+1}, then B_q
+            const M2 K = inv_i_minus(mul(Tl, M)), N = mul(K, Tr), tl = mul(K, mul(Tl, bl));
+            double s0 = T[0], s1 = T[5];
+            ch_mv(Tl, b0, b1, s0, s1);
+            const double t0 = K.a * s0 + K.b * s1, t1 = K.c * s0 + K.d * s1;
+            ch_mv(M, t0, t1, b0, b1);
+            double n0 = B[0], n1 = B[5];
+            ch_mv(Bl, b0, b1, n0, n1);
+            b0 = n0;
+            b1 = n1;
+            bl = mul(Bl, m2_ma(M, tl, bl));
+            M = m2_ma(mul(Bl, M), N, Br);
+            ch_mv(Fr, t0, t1, F0, F1);
+            Fl = m2_ma(Fr, tl, Fl);
+            Fr = mul(Fr, N);
             rec[0 * PP + q] = make_double2(t0, t1);
-            rec[1 * PP + q] = make_double2(N.a, N.b);
-            rec[2 * PP + q] = make_double2(N.c, N.d);
-            rec[3 * PP + q] = make_double2(b0, b1);
-            rec[4 * PP + q] = make_double2(M.a, M.b);
-            rec[5 * PP + q] = make_double2(M.c, M.d);
+            rec[1 * PP + q] = make_double2(tl.a, tl.b);
+            rec[2 * PP + q] = make_double2(tl.c, tl.d);
+            rec[3 * PP + q] = make_double2(N.a, N.b);
+            rec[4 * PP + q] = make_double2(N.c, N.d);
+            rec[5 * PP + q] = make_double2(b0, b1);
+            rec[6 * PP + q] = make_double2(bl.a, bl.b);
+            rec[7 * PP + q] = make_double2(bl.c, bl.d);
+            rec[8 * PP + q] = make_double2(M.a, M.b);
+            rec[9 * PP + q] = make_double2(M.c, M.d);
         }
     }
-    double x0 = 0.0, x1 = 0.0; // T_{q+1}: nothing beyond the last segment
+    auto bc = [](const M2 &x, int j) { return M2{ln_bcast(x.a, j), ln_bcast(x.b, j), ln_bcast(x.c, j), ln_bcast(x.d, j)}; };
+    // over the groups: T = t + N T'' and, of the group before, B = p + Q T (kept by the group's lane)
+    double t0 = 0.0, t1 = 0.0, p0 = 0.0, p1 = 0.0;
+    M2 N = zero, Q = zero;
+    {
+        double B0 = 0.0, B1 = 0.0;
+        M2 BM = zero;
 #pragma unroll 1
-    for (int q = P - 1; q > 0; --q) {
-        const double2 t = rec[q], n0 = rec[PP + q], n1 = rec[2 * PP + q];
-        const double2 b = rec[3 * PP + q - 1], m0 = rec[4 * PP + q - 1], m1 = rec[5 * PP + q - 1];
-        const double y0 = __builtin_fma(n0.x, x0, __builtin_fma(n0.y, x1, t.x));
-        x1 = __builtin_fma(n1.x, x0, __builtin_fma(n1.y, x1, t.y));
-        x0 = y0;
-        if (lane == 0) {
-            rec[8 * PP + q - 1] = make_double2(__builtin_fma(m0.x, x0, __builtin_fma(m0.y, x1, b.x)),
-                                               __builtin_fma(m1.x, x0, __builtin_fma(m1.y, x1, b.y)));
-            rec[9 * PP + q - 1] = make_double2(x0, x1);
+        for (int j = 0; j < ng; ++j) {
+            const M2 Tl = bc(Fl, j), Bl = bc(bl, j);
+            const M2 K = inv_i_minus(mul(Tl, BM)), n = mul(K, bc(Fr, j));
+            double s0 = ln_bcast(F0, j), s1 = ln_bcast(F1, j);
+            ch_mv(Tl, B0, B1, s0, s1);
+            const double u0 = K.a * s0 + K.b * s1, u1 = K.c * s0 + K.d * s1;
+            if (lane == j) {
+                t0 = u0;
+                t1 = u1;
+                p0 = B0;
+                p1 = B1;
+                N = n;
+                Q = BM;
+            }
+            ch_mv(BM, u0, u1, B0, B1);
+            double n0 = ln_bcast(b0, j), n1 = ln_bcast(b1, j);
+            ch_mv(Bl, B0, B1, n0, n1);
+            B0 = n0;
+            B1 = n1;
+            BM = m2_ma(mul(Bl, BM), n, bc(M, j));
+        }
+    }
+    double l0 = 0.0, l1 = 0.0, x0 = 0.0, x1 = 0.0; // the group's outer pairs
+    {
+        double y0 = 0.0, y1 = 0.0; // nothing beyond the last segment
+#pragma unroll 1
+        for (int j = ng - 1; j >= 0; --j) {
+            if (lane == j) {
+                x0 = y0;
+                x1 = y1;
+            }
+            double z0 = ln_bcast(t0, j), z1 = ln_bcast(t1, j);
+            ch_mv(bc(N, j), y0, y1, z0, z1);
+            y0 = z0;
+            y1 = z1;
+            if (lane == j) {
+                l0 = p0;
+                l1 = p1;
+                ch_mv(Q, y0, y1, l0, l1);
+            }
+        }
+    }
+    __asm__ volatile("" ::: "memory");
+    if (lane < ng) {
+#pragma unroll 1
+        for (int q = last; q >= first; --q) {
+            const double2 t = rec[q], u0 = rec[PP + q], u1 = rec[2 * PP + q], n0 = rec[3 * PP + q], n1 = rec[4 * PP + q];
+            const double2 b = rec[5 * PP + q], v0 = rec[6 * PP + q], v1 = rec[7 * PP + q], m0 = rec[8 * PP + q],
+                          m1 = rec[9 * PP + q];
+            double s0 = b.x, s1 = b.y, y0 = t.x, y1 = t.y;
+            ch_mv(M2{v0.x, v0.y, v1.x, v1.y}, l0, l1, s0, s1);
+            ch_mv(M2{m0.x, m0.y, m1.x, m1.y}, x0, x1, s0, s1);
+            ch_mv(M2{u0.x, u0.y, u1.x, u1.y}, l0, l1, y0, y1);
+            ch_mv(M2{n0.x, n0.y, n1.x, n1.y}, x0, x1, y0, y1);
+            rec[8 * PP + q] = make_double2(s0, s1);
+            rec[9 * PP + q] = make_double2(x0, x1);
+            x0 = y0;
+            x1 = y1;
         }
     }
     wave_lds_sync();

@@ -153,7 +153,7 @@ constexpr unsigned LN_DECOUPLED = (1023u - 100u) << 20; // 2^-100
 // and the reduction is as exact as an elimination. Once the film's growing modes make I + c J indefinite they
 // pass 1e2 to 1e6 in its steps and the (I - D)^-1 lose as many digits (lines of 777 cells at dt = 1000, worst
 // of 200: 6e-4 of the solution where elimination in order keeps 1e-7); such lines are solved again in order
-// (ln_serial). 0.2 <= dt <= 50: no line of a noise film, dt = 70 a tenth to a half, dt >= 100 all.
+// (ln_in_order). 0.2 <= dt <= 50: no line of a noise film, dt = 70 a tenth to a half, dt >= 100 all.
 constexpr unsigned LN_GROWN = (1023u + 4u) << 20;
 
 // Whether the wave's couplings (ma, mc: ln_word of A and C, 0 where they reach no lane of the wave) are all below
@@ -174,25 +174,22 @@ __device__ __forceinline__ double ln_bcast(double x, int s)
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
-// The equations B_s = r_s + A_s B_{s-1} + C_s B_{s+1} of the lanes first ..= last (uniform) by elimination in
-// order: afterwards every one of these lanes holds its B_s = r + A B_{first-1} + C B_{last+1} (OUTER false: there
-// is nothing beyond them, A and C are not formed). For lines whose couplings grow in a reduction. All lanes carry the
-// recurrence; the records stay in the exchange space, so that the path takes few registers from the usual one.
-template <bool OUTER>
-__device__ __forceinline__ void ln_serial(double2 *xch, int lane, int first, int last, M2 &A, M2 &C, double &r0,
-                                          double &r1)
+// One chain of equations in order over the records at xch[at(0)] .. xch[at(n - 1)], B_i = r + A B_{i-1} + C B_{i+1}: each
+// is left as B_i = r + A (what lies before the first) + C (what lies beyond the last); OUTER false: there is nothing
+// there and A is not formed. Every lane carries a recurrence (its own chain's: at depends on the lane), `put` the
+// one that writes; the records stay in the exchange space, so that the path takes few registers from the usual one.
+template <bool OUTER, class At>
+__device__ __forceinline__ void ln_chain(double2 *xch, int n, bool put, At at)
 {
-    __asm__ volatile("" ::: "memory");
-    ln_put(xch, lane, A, C, r0, r1);
     wave_lds_sync();
     M2 a, c;
     double q0, q1;
-    ln_get(xch, first, a, c, q0, q1);
+    ln_get(xch, at(0), a, c, q0, q1);
 #pragma unroll 1
-    for (int s = first + 1; s <= last; ++s) {
+    for (int i = 1; i < n; ++i) {
         M2 eA, eC;
         double e0, e1;
-        ln_get(xch, s, eA, eC, e0, e1);
+        ln_get(xch, at(i), eA, eC, e0, e1);
         const M2 K = inv_i_minus(mul(eA, c));
         const double s0 = __builtin_fma(eA.a, q0, __builtin_fma(eA.b, q1, e0));
         const double s1 = __builtin_fma(eA.c, q0, __builtin_fma(eA.d, q1, e1));
@@ -200,63 +197,70 @@ __device__ __forceinline__ void ln_serial(double2 *xch, int lane, int first, int
         q1 = K.c * s0 + K.d * s1;
         if (OUTER) a = mul(K, mul(eA, a));
         c = mul(K, eC);
-        if (lane == 0) ln_put(xch, s, a, c, q0, q1);
+        __asm__ volatile("" ::: "memory"); // (read by every lane of the chain before it is written)
+        if (put) ln_put(xch, at(i), a, c, q0, q1);
     }
 #pragma unroll 1
-    for (int s = last - 1; s >= first; --s) {
+    for (int i = n - 2; i >= 0; --i) {
         M2 eA, eC;
         double e0, e1;
-        ln_get(xch, s, eA, eC, e0, e1);
+        __asm__ volatile("" ::: "memory");
+        ln_get(xch, at(i), eA, eC, e0, e1);
         const double s0 = __builtin_fma(eC.a, q0, __builtin_fma(eC.b, q1, e0));
         q1 = __builtin_fma(eC.c, q0, __builtin_fma(eC.d, q1, e1));
         q0 = s0;
-        if (OUTER) {
-            a = m2_ma(eC, a, eA);
-            c = mul(eC, c);
-        }
-        if (lane == 0) ln_put(xch, s, a, c, q0, q1);
+        if (OUTER) a = m2_ma(eC, a, eA);
+        c = mul(eC, c);
+        __asm__ volatile("" ::: "memory");
+        if (put) ln_put(xch, at(i), a, c, q0, q1);
     }
     wave_lds_sync();
-    ln_get(xch, lane, A, C, r0, r1);
 }
 
-// Two cells per lane: the rows themselves (bands b, right-hand sides f) of the lanes first .. 63 by plain
-// elimination. The pairs' equations, each divided by its unpivoted 2 x 2 block, cost a digit more than
-// the wider lanes' on indefinite lines (128 cells at dt = 100, median: 1.2e-12 in order by pairs, 5e-13 by rows).
-__device__ __forceinline__ void ln_rows(int lane, int first, const Band (&b)[2], const double (&f)[2], double &B0,
-                                        double &B1)
+// The equations of lanes 0 .. 62 by elimination in order, for waves whose couplings grow: afterwards B_s = r + A L + C G
+// with L what lies before lane 0 and G the pair of lane 63, which keeps its equation. Lanes before `first` hold no part
+// of the line. In two levels of eight, so that the serial length is a fifth of the wave's: the seven lanes between
+// two separators (lanes 7, 15, .. 55) in terms of them, all groups at once, then the separators in terms of L and G
+// (one iteration of such a film, polymer at dt = 0.2, 2048^2: lane after lane 357 us, this 205, the reduction alone 154;
+// 512^2: 89, 54, 40; the tile passes take 195 and 78). No digit lost against lane after lane beyond the spread of films.
+__device__ __forceinline__ void ln_in_order(double2 *xch, int lane, int first, M2 &A, M2 &C, double &r0, double &r1)
 {
-    double al2 = 0.0, be2 = 0.0, z2 = 0.0, al1 = 0.0, be1 = 0.0, z1 = 0.0; // of the two rows before
-    double oa[2], ob[2], oz[2];                                             // of this lane's rows
-#pragma unroll
-    for (int k = 0; k < 2; ++k) oa[k] = ob[k] = oz[k] = 0.0;
-#pragma unroll 1
-    for (int s = first; s < 64; ++s) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const double a = ln_bcast(b[k].a, s), gam = ln_bcast(b[k].b, s) - a * al2;
-            const double rm = rcp(ln_bcast(b[k].c, s) - a * be2 - gam * al1);
-            const double al = (ln_bcast(b[k].d, s) - gam * be1) * rm, be = ln_bcast(b[k].e, s) * rm;
-            const double z = (ln_bcast(f[k], s) - a * z2 - gam * z1) * rm;
-            al2 = al1; be2 = be1; z2 = z1;
-            al1 = al; be1 = be; z1 = z;
-            if (lane == s) {
-                oa[k] = al;
-                ob[k] = be;
-                oz[k] = z;
-            }
-        }
+    const M2 zero = {0.0, 0.0, 0.0, 0.0};
+    const int g8 = lane & ~7;
+    if (lane < first) {
+        A = C = zero;
+        r0 = r1 = 0.0;
     }
-    double x1 = 0.0, x2 = 0.0;
-#pragma unroll 1
-    for (int s = 63; s >= first; --s) {
-        const double v1 = ln_bcast(oz[1], s) - ln_bcast(oa[1], s) * x1 - ln_bcast(ob[1], s) * x2;
-        const double v0 = ln_bcast(oz[0], s) - ln_bcast(oa[0], s) * v1 - ln_bcast(ob[0], s) * x1;
-        x2 = v1;
-        x1 = v0;
-        if (lane == s) {
-            B0 = v0;
-            B1 = v1;
+    __asm__ volatile("" ::: "memory");
+    ln_put(xch, lane, A, C, r0, r1);
+    if (lane < 2) {
+        const double i = lane == 0 ? 1.0 : 0.0;
+        ln_put(xch, 64 + lane, M2{i, 0.0, 0.0, i}, M2{1.0 - i, 0.0, 0.0, 1.0 - i}, 0.0, 0.0);
+    }
+    ln_chain<true>(xch, 7, (lane & 7) == 0, [&](int i) { return g8 + i; });
+    // (lane, right neighbour: any lane beside the separators will do, they alone take the step)
+    if ((lane & 7) == 7 && lane < 63) {
+        ln_step(A, C, r0, r1, xch, lane - 1, lane + 1);
+        ln_put(xch, lane, A, C, r0, r1);
+    }
+    ln_chain<true>(xch, 7, lane == 0, [&](int i) { return 8 * i + 7; });
+    if (lane < 63) {
+        M2 nA, nC, a, c;
+        double n0, n1;
+        ln_get(xch, lane, a, c, r0, r1);
+        A = a;
+        C = c;
+        if ((lane & 7) != 7) {
+            ln_get(xch, lane < 8 ? 64 : g8 - 1, nA, nC, n0, n1);
+            A = mul(a, nA);
+            C = mul(a, nC);
+            r0 = __builtin_fma(a.a, n0, __builtin_fma(a.b, n1, r0));
+            r1 = __builtin_fma(a.c, n0, __builtin_fma(a.d, n1, r1));
+            ln_get(xch, lane >= 56 ? 65 : g8 + 7, nA, nC, n0, n1);
+            A = m2_ma(c, nA, A);
+            C = m2_ma(c, nC, C);
+            r0 = __builtin_fma(c.a, n0, __builtin_fma(c.b, n1, r0));
+            r1 = __builtin_fma(c.c, n0, __builtin_fma(c.d, n1, r1));
         }
     }
 }
@@ -367,10 +371,9 @@ __device__ __forceinline__ void ln_own(double2 *xch, int lane, const double (&fa
 // magnitude); else it ends when the lanes are decoupled, of an ordinary film after three of
 // the six steps at 16 positions per lane (x sweep of 8192^2 771 -> 705 us, x + y of 2048^2 111 -> 102). Lanes
 // of two or four cells decouple a step early at best, which the test costs: they take all steps (256^2 and 128^2).
-// Lines whose couplings grow past LN_GROWN are solved in order instead; lines of two cells per lane return true
-// then and leave it to the caller, who has the rows (ln_rows).
+// Lines whose couplings grow past LN_GROWN are solved in order instead.
 template <int CPL, bool FULL = false>
-__device__ __forceinline__ bool ln_pairs(double2 *xch, int lane, int nsub, double (&fa)[CPL],
+__device__ __forceinline__ void ln_pairs(double2 *xch, int lane, int nsub, double (&fa)[CPL],
                                          double (&fb)[CPL], double (&fz)[CPL], double (&fph)[CPL], double (&fps)[CPL],
                                          double &B0, double &B1, double &l1, double &l2)
 {
@@ -379,7 +382,7 @@ __device__ __forceinline__ bool ln_pairs(double2 *xch, int lane, int nsub, doubl
     ln_own<CPL>(xch, lane, fa, fb, fz, fph, fps, A, C, r0, r1);
     const M2 A0 = A, C0 = C;
     const double q0 = r0, q1 = r1;
-    unsigned grown = max(ln_word(A), ln_word(C));
+    unsigned grown = lane >= 64 - nsub ? max(ln_word(A), ln_word(C)) : 0u;
     for (int d = 1; d < nsub; d <<= 1) {
         __asm__ volatile("" ::: "memory");
         ln_put(xch, lane, A, C, r0, r1);
@@ -387,11 +390,11 @@ __device__ __forceinline__ bool ln_pairs(double2 *xch, int lane, int nsub, doubl
         // past the wave's ends A or C is zero
         ln_step(A, C, r0, r1, xch, max(lane - d, 0), min(lane + d, 63));
         const unsigned ma = ln_word(A), mc = ln_word(C);
-        grown = max(grown, max(ma, mc));
+        if (lane >= 64 - nsub) grown = max(grown, max(ma, mc));
         if (!FULL && CPL > 4 && ln_decoupled(ma, mc, r0, r1)) break;
     }
-    const bool again = __any(lane >= 64 - nsub && grown >= LN_GROWN);
-    if (CPL > 2 && again) {
+    const bool again = __any(grown >= LN_GROWN);
+    if (again) {
         if (FULL) {
             A = A0;
             C = C0;
@@ -401,14 +404,23 @@ __device__ __forceinline__ bool ln_pairs(double2 *xch, int lane, int nsub, doubl
             ln_launder<CPL>(fa, fb, fz, fph, fps);
             ln_own<CPL>(xch, lane, fa, fb, fz, fph, fps, A, C, r0, r1);
         }
-        ln_serial<false>(xch, lane, 64 - nsub, 63, A, C, r0, r1);
+        ln_in_order(xch, lane, 64 - nsub, A, C, r0, r1);
+        // lane 63: B = r + A B_62 and B_62 = r_62 + C_62 B
+        const M2 c = {ln_bcast(C.a, 62), ln_bcast(C.b, 62), ln_bcast(C.c, 62), ln_bcast(C.d, 62)}, a = {
+            ln_bcast(A.a, 63), ln_bcast(A.b, 63), ln_bcast(A.c, 63), ln_bcast(A.d, 63)};
+        const double s0 = ln_bcast(r0, 62), s1 = ln_bcast(r1, 62);
+        const M2 K = inv_i_minus(mul(a, c));
+        const double t0 = __builtin_fma(a.a, s0, __builtin_fma(a.b, s1, ln_bcast(r0, 63)));
+        const double t1 = __builtin_fma(a.c, s0, __builtin_fma(a.d, s1, ln_bcast(r1, 63)));
+        const double g0 = K.a * t0 + K.b * t1, g1 = K.c * t0 + K.d * t1;
+        r0 = lane == 63 ? g0 : __builtin_fma(C.a, g0, __builtin_fma(C.b, g1, r0));
+        r1 = lane == 63 ? g1 : __builtin_fma(C.c, g0, __builtin_fma(C.d, g1, r1));
     }
     B0 = r0;
     B1 = r1;
     if (FULL && !again) ln_again(A0, C0, q0, q1, lane_prev(r0), lane_prev(r1), lane_next(r0), lane_next(r1), B0, B1);
     l1 = lane_prev(B0);
     l2 = lane_prev(B1);
-    return again;
 }
 
 // The same for a line held by W consecutive waves (wv: this wave's place on the line, bnd: LN_BND
@@ -454,7 +466,8 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
     if (lane == 63) ln_put1(mb + 30, A, C, r0, r1);
     const M2 A0 = A, C0 = C;
     const double q0 = r0, q1 = r1;
-    unsigned grown = max(ln_word(A), ln_word(C));
+    const int first = wv == 0 ? lz : 0;
+    unsigned grown = lane >= first && lane < 63 ? max(ln_word(A), ln_word(C)) : 0u;
 #pragma unroll 1
     for (int d = 1; d < 64; d <<= 1) {
         __asm__ volatile("" ::: "memory");
@@ -464,15 +477,14 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
         // lanes whose A or C reaches a lane of the wave (the others hold G's)
         const bool a = lane >= 2 * d && lane < 63, c = lane + 2 * d < 63;
         const unsigned ma = ln_word(A), mc = ln_word(C);
-        grown = max(grown, max(ma, mc));
+        if (lane >= first && lane < 63) grown = max(grown, max(ma, mc));
         if (!FULL && ln_decoupled(a ? ma : 0u, c ? mc : 0u, r0, r1)) {
             if (a) A = {0.0, 0.0, 0.0, 0.0};
             if (c) C = {0.0, 0.0, 0.0, 0.0};
             break;
         }
     }
-    const int first = wv == 0 ? lz : 0;
-    const bool again = __any(lane >= first && lane < 63 && grown >= LN_GROWN);
+    const bool again = __any(grown >= LN_GROWN);
     if (again) {
         if (FULL) {
             A = A0;
@@ -489,7 +501,7 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
             wave_lds_sync();
             equation();
         }
-        ln_serial<true>(xch, lane, first, 62, A, C, r0, r1);
+        ln_in_order(xch, lane, first, A, C, r0, r1);
     }
     if (lane == 0) ln_put1(mb + 10, A, C, r0, r1);
     if (lane == 62) ln_put1(mb + 20, A, C, r0, r1);
@@ -534,7 +546,9 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
         if (__any(gw >= LN_GROWN)) {
             __asm__ volatile("" ::: "memory");
             outer();
-            ln_serial<false>(xch, lane, 0, W - 1, gA, gC, g0, g1);
+            ln_put(xch, lane, gA, gC, g0, g1);
+            ln_chain<false>(xch, W, lane == 0, [](int w) { return w; });
+            ln_get(xch, i, gA, gC, g0, g1);
         }
         __asm__ volatile("" ::: "memory");
         xch[lane] = make_double2(g0, g1);

@@ -105,7 +105,6 @@ __device__ __forceinline__ void xline_body(const PassParams &p, int j, int rec, 
         else wave_lds_sync();
     }
     double fa[CPL], fb[CPL], fz[CPL], fph[CPL], fps[CPL];
-    Band rows[2]; // two cells per lane: the rows, should the line be solved in order
     {
         const double *bu = sU + ln_at<CPL>(w0 + CPL * lane), *bx = s2 + ln_at<CPL>(w0 + CPL * lane);
         auto cell = [&](int t) {
@@ -127,7 +126,6 @@ __device__ __forceinline__ void xline_body(const PassParams &p, int j, int rec, 
             if (k >= CPL - 2 && re) fold_right(B, CPL - 1 - k);
             if (k == kz && slot == lz) fold_left(B, 0);
             if (k == (kz + 1) % CPL && slot == lz + (kz == CPL - 1 ? 1 : 0)) fold_left(B, 1);
-            if (CPL == 2) rows[k % 2] = B;
             xr_elim<CPL>(k, B, wr[k], fa, fb, fz, fph, fps);
             c0 = cp;
             fm = fp;
@@ -135,14 +133,8 @@ __device__ __forceinline__ void xline_body(const PassParams &p, int j, int rec, 
     }
     double B0, B1, l1, l2;
     double2 *const xch = reinterpret_cast<double2 *>(priv);
-    if constexpr (MW) {
-        ln_pairs_mw<CPL>(xch, bnd, lane, wv, W, sh / CPL, fa, fb, fz, fph, fps, B0, B1, l1, l2);
-    } else {
-        const int nsub = (nx + CPL - 1) / CPL;
-        const bool grown = ln_pairs<CPL>(xch, lane, nsub, fa, fb, fz, fph, fps, B0, B1, l1, l2);
-        if constexpr (CPL == 2)
-            if (grown) ln_rows(lane, 64 - nsub, rows, wr, B0, B1);
-    }
+    if constexpr (MW) ln_pairs_mw<CPL>(xch, bnd, lane, wv, W, sh / CPL, fa, fb, fz, fph, fps, B0, B1, l1, l2);
+    else ln_pairs<CPL>(xch, lane, (nx + CPL - 1) / CPL, fa, fb, fz, fph, fps, B0, B1, l1, l2);
     {
         // back-substitution from the lane's pair and its left neighbour's; v goes to the wave's space
         double *v2 = priv + (CPL + 1) * lane;
@@ -252,8 +244,6 @@ __device__ __forceinline__ void yline_body(const PassParams &p, int i0, int rec,
     __syncthreads();
     const int gl = i0 + col; // grid column of this wave
     double fa[CPL], fb[CPL], fz[CPL], fph[CPL], fps[CPL];
-    Band rows[2]; // two cells per lane: the rows, should the line be solved in order
-    double rhs[2];
     double rmax = 0.0;
     unsigned flags = 0;
     {
@@ -290,10 +280,6 @@ __device__ __forceinline__ void yline_body(const PassParams &p, int i0, int rec,
             if (k >= CPL - 2 && re) fold_right(B, CPL - 1 - k);
             if (k == kz && slot == lz) fold_left(B, 0);
             if (k == (kz + 1) % CPL && slot == lz + (kz == CPL - 1 ? 1 : 0)) fold_left(B, 1);
-            if (CPL == 2) {
-                rows[k % 2] = B;
-                rhs[k % 2] = -G;
-            }
             xr_elim<CPL>(k, B, -G, fa, fb, fz, fph, fps);
             c0 = cp;
             fm = fp;
@@ -319,10 +305,7 @@ __device__ __forceinline__ void yline_body(const PassParams &p, int i0, int rec,
                          B0, B1, l1, l2);
     } else {
         __syncthreads();
-        const int nsub = (ny + CPL - 1) / CPL;
-        const bool grown = ln_pairs<CPL>(xch, lane, nsub, fa, fb, fz, fph, fps, B0, B1, l1, l2);
-        if constexpr (CPL == 2)
-            if (grown) ln_rows(lane, 64 - nsub, rows, rhs, B0, B1);
+        ln_pairs<CPL>(xch, lane, (ny + CPL - 1) / CPL, fa, fb, fz, fph, fps, B0, B1, l1, l2);
     }
     {
         double *v2 = priv + (CPL + 1) * lane;
