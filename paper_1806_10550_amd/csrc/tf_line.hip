@@ -33,8 +33,13 @@ LineGeom xline_geom(int nx)
 // (700 x 1300: 37 against 53 us partitioned, 1637^2 79 against 91, 2700 x 1637 114 against 124, 4000 x 1500
 // 135 against 151; 1100 x 1300 70 against 69, 2200 x 1300 100 against 95) and, with 16 positions per lane,
 // in at most two rounds (2048^2 108 against 114, 3000 x 2000 157 against 145).
+// Short columns in wide films: the partitioned passes stream them better once four-column workgroups are many
+// (power law, whole / partitioned y sweep in us: 12000 x 64 38/41, 16384 x 64 49/42, 65536 x 64 164/80, 65536 x 4 94/45;
+// 12000 x 128 42/51, 16384 x 128 53/52, 65536 x 128 175/130; 16384 x 129 66/67, 32768 x 129 121/105), from four tile
+// rows on never (65536 x 200 221/233, 65536 x 1000 whole 0.7 of the time).
 LineGeom yline_geom(int km, int nx, int ny)
 {
+    if (ny <= 3 * TILE && nx > (ny <= TILE ? 12288 : 16384)) return {0, 0};
     if (ny < 4 || ny > 2048 || (ny > 1024 && nx > 4096)) return {0, 0};
     if (km == KM_NLC && ny > 1024) {
         constexpr int round = 256 * LN_COLS; // columns
