@@ -212,7 +212,7 @@ tf_status tf_ensemble_destroy(tf_ensemble *e);
 /* scheme as for tf_set_scheme (theta in [0.5, 1]; theta < 1 allocates one packed field) */
 tf_status tf_ensemble_set_scheme(tf_ensemble *e, const tf_scheme *s);
 /* x-sweep line solver of every film (see tf_set_xsweep): TF_XSWEEP_AUTO gives film f the
- * variant tf_xsweep_choice(nx_f, rows of all films) (the default at creation); TF_XSWEEP_ROW the
+ * variant tf_xsweep_choice gives it (rows of all films; the default at creation); TF_XSWEEP_ROW the
  * whole-row kernel for every film whose rows fit a 4-wave workgroup (nx <= 4096; the others
  * stay partitioned); TF_XSWEEP_PARTITIONED the partitioned solver for all. The whole-row
  * films of an ensemble share one launch per iteration. tf_ensemble_xsweep returns a film's
@@ -358,9 +358,10 @@ int tf_autotune_choice(int length, int batch, int transposed);
  * too). TF_EINVAL for length or batch below 4. Grids (tf_create) and ensembles
  * (tf_ensemble_create, per film, with ny = the rows of all its films, since its x sweep is one
  * launch over all of them) take the variant tf_xsweep_choice(nx, ny) returns at creation: the
- * tuned entry of the nearest shape (log distance below 0.7), else the whole-row kernel; for
- * rows above 4096 cells never the whole-row kernel in ensembles or in films of fewer than 64
- * rows.
+ * tuned entry of the nearest shape (log distance below 0.7), else the whole-row kernel, but for
+ * rows of at most 64 cells in one film of more than 20480 rows the partitioned solver (in an
+ * ensemble by the film's own rows); for rows above 4096 cells never the whole-row kernel in
+ * ensembles or in films of fewer than 64 rows.
  * Returns 0 (partitioned) or 1 (whole-row). */
 tf_status tf_autotune_xsweep(int length, int batch, const char *cache_path);
 int tf_xsweep_choice(int nx, int ny);

@@ -727,8 +727,11 @@ namespace tf {
 // else the whole-row kernel (faster than the partitioned solver's three launches at every length and
 // number of rows measured, figures at xline_geom in tf_line.hip). Rows above 4096 cells take it in films of
 // at least 64 rows (8192 x 64: 25 against 69 us, 8192^2: 818 against 900); shorter films keep the
-// partitioned solver tf_xsweep_choice has always returned for them.
-int xsweep_choice(int nx, int ny)
+// partitioned solver tf_xsweep_choice has always returned for them. Rows of one tile in films of more than 20480 rows
+// stream better through the tile passes (whole / partitioned, us: 64 x 16384 39/40, 64 x 20000 47/48, 64 x 32768 71/50,
+// 64 x 65536 126/84, 4 x 20000 27/32, 4 x 32768 40/34; 128 x 32768 77/85); as many rows of small films do not (512 films
+// of 64^2, a step: 3.84 ms whole, 4.14 partitioned). ny: rows of the launch, film_ny: of the film.
+int xsweep_choice(int nx, int ny, int film_ny)
 {
     if (!xrow_supported(nx) || (nx > XR_ROW4_MAX_NX && ny < 64)) return 0;
     TuneTable &t = tune_table();
@@ -741,7 +744,7 @@ int xsweep_choice(int nx, int ny)
         if (d < best_d) { best_d = d; v = kv.second.variant; }
     }
     if (v >= 0 && best_d < 0.7) return v;
-    return 1;
+    return nx <= TILE && film_ny > 20480 ? 0 : 1;
 }
 } // namespace tf
 
@@ -1396,7 +1399,7 @@ tf_status tf_autotune_xsweep(int length, int batch, const char *cache_path)
     return TF_OK;
 }
 
-int tf_xsweep_choice(int nx, int ny) { return tf::xsweep_choice(nx, ny); }
+int tf_xsweep_choice(int nx, int ny) { return tf::xsweep_choice(nx, ny, ny); }
 
 tf_status tf_autotune_load(const char *cache_path)
 {

@@ -545,7 +545,7 @@ tf_status tf_create(int nx, int ny, double ds, void *stream, tf_grid **out)
     g->S = tf_scheme{1.0, 1e-10, 1e-6, 1.0, 0.5, 1.1, 5000, 5, 0};
     g->Px = tf::seg_count(nx);
     g->Py = tf::seg_count(ny);
-    g->xsweep = tf::xsweep_choice(nx, ny) == 1 ? TF_XSWEEP_ROW : TF_XSWEEP_PARTITIONED;
+    g->xsweep = tf::xsweep_choice(nx, ny, ny) == 1 ? TF_XSWEEP_ROW : TF_XSWEEP_PARTITIONED;
     if (hipGetDevice(&g->device) != hipSuccess) {
         delete g;
         return fail(TF_EDEVICE, "hipGetDevice failed");
@@ -685,7 +685,7 @@ tf_status tf_set_xsweep(tf_grid *g, int variant)
 {
     if (g == nullptr) return fail(TF_EINVAL, "grid is NULL");
     if (variant == TF_XSWEEP_AUTO)
-        variant = tf::xsweep_choice(g->nx, g->ny) == 1 ? TF_XSWEEP_ROW : TF_XSWEEP_PARTITIONED;
+        variant = tf::xsweep_choice(g->nx, g->ny, g->ny) == 1 ? TF_XSWEEP_ROW : TF_XSWEEP_PARTITIONED;
     if (variant != TF_XSWEEP_PARTITIONED && variant != TF_XSWEEP_ROW)
         return fail(TF_EINVAL, "unknown x-sweep variant");
     if (variant == TF_XSWEEP_ROW && !tf::xrow_supported(g->nx))

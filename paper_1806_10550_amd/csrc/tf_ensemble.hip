@@ -248,7 +248,7 @@ int total_rows(const tf_ensemble *e)
 int auto_xsweep(const tf_ensemble *e, int f)
 {
     const int nx = e->desc[f].nx;
-    return nx <= tf::XR_ROW4_MAX_NX ? tf::xsweep_choice(nx, total_rows(e)) : 0;
+    return nx <= tf::XR_ROW4_MAX_NX ? tf::xsweep_choice(nx, total_rows(e), e->desc[f].ny) : 0;
 }
 
 // Work-list capacity for any choice of x-sweep variants.

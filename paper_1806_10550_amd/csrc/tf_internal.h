@@ -277,9 +277,9 @@ bool sbline_supported(int np);
 hipError_t launch_sbline(bool trans, bool pm, int mode, int nl, int np, const double *bands, const double *rhs,
                          double *out, unsigned long long *red, hipStream_t s,
                          const unsigned long long *stop = nullptr);
-// x-sweep variant for a film of nx x ny cells (0: partitioned, 1: whole-row): the autotuned
-// choice for the nearest shape, else the built-in rule (tf_adjoint.hip).
-int xsweep_choice(int nx, int ny);
+// x-sweep variant for ny rows of nx cells in one launch, film_ny of them this film's (0: partitioned, 1: whole-row): the
+// autotuned choice for the nearest shape, else the built-in rule (tf_adjoint.hip).
+int xsweep_choice(int nx, int ny, int film_ny);
 // The same over an ensemble's films with W waves per line, of x sweeps only those whose rows fill their
 // lanes (aligned: cpl divides nx) or only the others (items: (film, block of four columns or row,
 // positions per lane), film -1: none); km: the KernelModel every film shares.

@@ -1,11 +1,11 @@
 """Films with very many short lines: on both sides of the lines between the whole-line kernels and the tile passes
-(columns of one and up to three tiles) the sweep taken and the iterate against the oracle."""
+(columns of one and up to three tiles, rows of one tile) the sweep taken and the iterate against the oracle."""
 import numpy as np
 import pytest
 import torch
 
 from paper_1806_10550_amd import synth
-from paper_1806_10550_amd.lib import Grid
+from paper_1806_10550_amd.lib import Grid, xsweep_choice
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -35,3 +35,10 @@ def iterate(orc, nx, ny):
 def test_short_columns(orc, nx, ny, whole):
     used = iterate(orc, nx, ny)
     assert ("yline" in used) == whole and ("relations_y" in used) != whole
+
+
+@pytest.mark.parametrize("nx,ny,whole", [(64, 20480, True), (64, 20481, False), (5, 20481, False), (65, 20481, True)])
+def test_short_rows(orc, nx, ny, whole):
+    assert xsweep_choice(nx, ny) == ("row" if whole else "partitioned")
+    used = iterate(orc, nx, ny)
+    assert ("xrow" in used) == whole and ("relations_x" in used) != whole
