@@ -174,7 +174,7 @@ void build_items(tf_ensemble *e, std::vector<int> &items)
         const tf::LineGeom yg = tf::yline_geom(e->km, d.nx, d.ny), xg = e->xsweep[f] == 1 ? tf::xline_geom(d.nx)
                                                                                          : tf::LineGeom{0, 0};
         const int tyx = (d.nx + tf::TILE - 1) / tf::TILE, txy = (d.ny + tf::TILE - 1) / tf::TILE;
-        for (int j = 0; j < tf::bn_tiles_y(d.ny); ++j)
+        for (int j = 0; j < tf::bn_tiles_y(d.nx, d.ny); ++j)
             for (int i = 0; i < tf::bn_tiles_x(d.nx); ++i) bnt.insert(bnt.end(), {f, i, j});
         if (yg.W > 0) {
             yl[yg.W - 1].push_back({f, (d.nx + tf::LN_COLS - 1) / tf::LN_COLS, yg.cpl});
@@ -257,7 +257,7 @@ size_t max_items(const tf_ensemble *e)
     size_t n = 0;
     for (const auto &d : e->desc) {
         const size_t yt = (size_t)d.Py * ((d.nx + tf::TILE - 1) / tf::TILE);
-        n += 3 * yt + 3 * (size_t)tf::bn_tiles_x(d.nx) * tf::bn_tiles_y(d.ny);
+        n += 3 * yt + 3 * (size_t)tf::bn_tiles_x(d.nx) * tf::bn_tiles_y(d.nx, d.ny);
         n += 2 * (size_t)d.nx + 3 * (size_t)((d.nx + tf::LN_COLS - 1) / tf::LN_COLS); // (chain blocks: at most one per line)
         n += 3 * (size_t)((d.ny + tf::TILE - 1) / tf::TILE) * d.Px + 5 * (size_t)d.ny;
     }

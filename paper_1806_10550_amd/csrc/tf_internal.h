@@ -307,7 +307,7 @@ hipError_t launch_pass_ens(int dir, bool solve, int km, const EnsParams &e, hipS
 // b^n of every active film at the first iteration of an attempt (items: (film, tx, ty) over the
 // bn_tiles_x x bn_tiles_y tiles of each film)
 int bn_tiles_x(int nx);
-int bn_tiles_y(int ny);
+int bn_tiles_y(int nx, int ny);
 hipError_t launch_bn_ens(const EnsParams &e, hipStream_t s);
 // items: (film, block of chain_lines lines) of the films whose chains are reduced, or of the others
 hipError_t launch_chain_ens(const EnsParams &e, int dir, bool reduced, hipStream_t s);

@@ -803,12 +803,19 @@ __global__ void __launch_bounds__(128) k_chain_ens(EnsParams e, int dir)
 // Used for b^n = u^n - (1 - theta) dt D(u^n) and for testing D.
 // ------------------------------------------------------------------------------------
 //
-// A wave streams FD_R rows of 64 columns through its registers (one u row loaded, one row of cells
+// A wave streams R rows of 64 columns through its registers (one u row loaded, one row of cells
 // evaluated and one row of results written per step); x neighbours come from whole-wave DPP shifts,
 // so the two outer lanes on each side only feed the others and 60 columns are owned. No LDS and no
-// barrier; every cell is evaluated 1.2 times instead of five. Bound by HBM for the cheap models
+// barrier; a cell is evaluated 1.2 times with 16 rows, 1.6 with four, instead of five. Bound by HBM for the cheap models
 // (16 B per cell) and by the FP64 rate of the tanh switch for NLC (1637^2: 55 -> 26 us).
-constexpr int FD_X = 60, FD_R = 16, FD_Y = 4 * FD_R; // a workgroup: four waves, one below the other
+constexpr int FD_X = 60;                    // a workgroup: four waves, one below the other
+// Rows per wave: a small film is left to the latency of a wave's rows, and short strips give more waves (whole call, us,
+// 16 / 4 rows: 128^2 21.6 / 18.8, NLC 25.5 / 19.9; 1024^2 24.4 / 23.3, NLC 30.5 / 27.8; 2048^2 33.1 / 32.4, NLC 45.6 / 44.0;
+// evaluating five cells for each took 18.3 at 128^2); from some 8M cells on the halo rows' evaluation counts for the
+// costly models (4096^2 71 / 69, NLC 108 / 116).
+constexpr int FD_R = 16, FD_RS = 4;
+__host__ __device__ constexpr bool fd_small(int nx, int ny) { return (size_t)nx * ny <= (size_t)1 << 23; }
+__host__ __device__ constexpr int fd_tile(int nx, int ny) { return 4 * (fd_small(nx, ny) ? FD_RS : FD_R); }
 
 struct FCell {
     double u, lap, f0, f1;
@@ -822,8 +829,8 @@ __device__ __forceinline__ double face_flux(const FCell &L, const FCell &R, doub
 }
 
 // D(u), the flux differences of eq. GovEqnCell2 with zero boundary fluxes, on the rows j0 .. j0 +
-// FD_R - 1 of the columns i0 .. i0 + FD_X - 1: store(j, i, u, D).
-template <bool P32, bool NOF0, class Store>
+// R - 1 of the columns i0 .. i0 + FD_X - 1: store(j, i, u, D).
+template <bool P32, bool NOF0, int R, class Store>
 __device__ __forceinline__ void flux_div_rows(const double *u, int nx, int ny, int i0, int j0, double ids, double ids2,
                                               const Model &M, Store store)
 {
@@ -832,9 +839,9 @@ __device__ __forceinline__ void flux_div_rows(const double *u, int nx, int ny, i
     if (j0 >= ny) return;                          // uniform over the wave
     const bool own = lane >= 2 && lane < 2 + FD_X && i < nx;
     const double *col = u + (unsigned)crefl(i, nx);
-    double v[FD_R + 4];                            // rows j0 - 2 .. j0 + FD_R + 1
+    double v[R + 4];                               // rows j0 - 2 .. j0 + R + 1
 #pragma unroll
-    for (int r = 0; r < FD_R + 4; ++r) v[r] = col[(size_t)crefl(j0 - 2 + r, ny) * nx];
+    for (int r = 0; r < R + 4; ++r) v[r] = col[(size_t)crefl(j0 - 2 + r, ny) * nx];
     auto cell = [&](int r) {                       // row j0 - 2 + r
         FCell c;
         c.u = v[r];
@@ -847,7 +854,7 @@ __device__ __forceinline__ void flux_div_rows(const double *u, int nx, int ny, i
     double Fs = face_flux<NOF0>(cell(1), c, ids);
     if (j0 == 0) Fs = 0.0;
 #pragma unroll
-    for (int r = 2; r < FD_R + 2; ++r) {
+    for (int r = 2; r < R + 2; ++r) {
         const int j = j0 + r - 2;
         if (j < ny) {
             const FCell n = cell(r + 1);
@@ -863,19 +870,19 @@ __device__ __forceinline__ void flux_div_rows(const double *u, int nx, int ny, i
     }
 }
 
-template <bool P32, bool NOF0>
+template <bool P32, bool NOF0, int R>
 __global__ void __launch_bounds__(256) k_flux_divergence(int nx, int ny, double ids, double ids2, Model M,
                                                          const double *u, double alpha, double beta,
                                                          const double *add, double *out)
 {
-    const int j0 = blockIdx.y * FD_Y + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * FD_R;
-    flux_div_rows<P32, NOF0>(u, nx, ny, blockIdx.x * FD_X, j0, ids, ids2, M, [&](int j, int i, double, double D) {
+    const int j0 = (blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * R;
+    flux_div_rows<P32, NOF0, R>(u, nx, ny, blockIdx.x * FD_X, j0, ids, ids2, M, [&](int j, int i, double, double D) {
         const size_t o = (size_t)j * nx + i;
         out[o] = (add != nullptr ? alpha * add[o] : 0.0) + beta * D;
     });
 }
 
-// Ensemble b^n = u^n - (1 - theta) dt D(u^n), block -> one FD_X x FD_Y tile of a film that is active
+// Ensemble b^n = u^n - (1 - theta) dt D(u^n), block -> one FD_X x fd_tile tile of a film that is active
 // and at the first iteration of its attempt (the same arithmetic as k_flux_divergence with
 // alpha = 1, so the ensemble matches the single film).
 __global__ void __launch_bounds__(256) k_bn_ens(EnsParams e)
@@ -890,13 +897,20 @@ __global__ void __launch_bounds__(256) k_bn_ens(EnsParams e)
     double *bn = e.bn + d.off;
     const double ids = 1.0 / d.ds, ids2 = ids * ids;
     const double beta = -(1.0 - e.theta) * s->dt;
-    const int j0 = ty * FD_Y + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * FD_R;
+    const int row = 4 * ty + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); // of strips
     auto store = [&](int j, int i, double u, double D) { bn[(size_t)j * d.nx + i] = u + beta * D; };
-    if (d.M.p32) flux_div_rows<true, false>(un, d.nx, d.ny, tx * FD_X, j0, ids, ids2, d.M, store);
-    else flux_div_rows<false, false>(un, d.nx, d.ny, tx * FD_X, j0, ids, ids2, d.M, store);
+#define TF_BN(P, R) flux_div_rows<P, false, R>(un, d.nx, d.ny, tx * FD_X, R * row, ids, ids2, d.M, store)
+    if (fd_small(d.nx, d.ny)) {
+        if (d.M.p32) TF_BN(true, FD_RS);
+        else TF_BN(false, FD_RS);
+    } else {
+        if (d.M.p32) TF_BN(true, FD_R);
+        else TF_BN(false, FD_R);
+    }
+#undef TF_BN
 }
 int bn_tiles_x(int nx) { return (nx + FD_X - 1) / FD_X; }
-int bn_tiles_y(int ny) { return (ny + FD_Y - 1) / FD_Y; }
+int bn_tiles_y(int nx, int ny) { return (ny + fd_tile(nx, ny) - 1) / fd_tile(nx, ny); }
 
 // ------------------------------------------------------------------------------------
 // Mass diagnostic: per-block compensated (Neumaier) sum, minimum and NaN flag, reduced
@@ -1160,13 +1174,28 @@ hipError_t launch_chain(const ChainParams &c, hipStream_t s)
     return hipGetLastError();
 }
 
+template <bool NOF0>
+static hipError_t launch_fd(int nx, int ny, double ids, double ids2, const Model &M, const double *u, double alpha,
+                            double beta, const double *add, double *out, hipStream_t s)
+{
+    const bool small = fd_small(nx, ny);
+    const dim3 grid(bn_tiles_x(nx), bn_tiles_y(nx, ny)), block(256);
+#define TF_FD(P, R) k_flux_divergence<P, NOF0, R><<<grid, block, 0, s>>>(nx, ny, ids, ids2, M, u, alpha, beta, add, out)
+    if (M.p32) {
+        if (small) TF_FD(true, FD_RS);
+        else TF_FD(true, FD_R);
+    } else {
+        if (small) TF_FD(false, FD_RS);
+        else TF_FD(false, FD_R);
+    }
+#undef TF_FD
+    return hipGetLastError();
+}
+
 hipError_t launch_flux_divergence(int nx, int ny, double ids, double ids2, const Model &M, const double *u,
                                   double alpha, double beta, const double *add, double *out, hipStream_t s)
 {
-    const dim3 grid(bn_tiles_x(nx), bn_tiles_y(ny)), block(256);
-    if (M.p32) k_flux_divergence<true, false><<<grid, block, 0, s>>>(nx, ny, ids, ids2, M, u, alpha, beta, add, out);
-    else k_flux_divergence<false, false><<<grid, block, 0, s>>>(nx, ny, ids, ids2, M, u, alpha, beta, add, out);
-    return hipGetLastError();
+    return launch_fd<false>(nx, ny, ids, ids2, M, u, alpha, beta, add, out, s);
 }
 
 // f0, f0', f1, f1' of the model at n thicknesses (out[4k + 0..3]).
@@ -1193,10 +1222,7 @@ hipError_t launch_model_coeffs(const Model &M, const double *h, int n, double *o
 hipError_t launch_flux_divergence_f1(int nx, int ny, double ids, double ids2, const Model &M, const double *u,
                                      double *out, hipStream_t s)
 {
-    const dim3 grid(bn_tiles_x(nx), bn_tiles_y(ny)), block(256);
-    if (M.p32) k_flux_divergence<true, true><<<grid, block, 0, s>>>(nx, ny, ids, ids2, M, u, 0.0, 1.0, nullptr, out);
-    else k_flux_divergence<false, true><<<grid, block, 0, s>>>(nx, ny, ids, ids2, M, u, 0.0, 1.0, nullptr, out);
-    return hipGetLastError();
+    return launch_fd<true>(nx, ny, ids, ids2, M, u, 0.0, 1.0, nullptr, out, s);
 }
 
 int mass_blocks(size_t n)
