@@ -238,30 +238,29 @@ __device__ __forceinline__ void ln_in_order(double2 *xch, int lane, int first, M
         ln_put(xch, 64 + lane, M2{i, 0.0, 0.0, i}, M2{1.0 - i, 0.0, 0.0, 1.0 - i}, 0.0, 0.0);
     }
     ln_chain<true>(xch, 7, (lane & 7) == 0, [&](int i) { return g8 + i; });
-    // (lane, right neighbour: any lane beside the separators will do, they alone take the step)
+    // a separator's equation with its two neighbours' in terms of the separators (own records are read again rather
+    // than held in registers meanwhile)
     if ((lane & 7) == 7 && lane < 63) {
+        ln_get(xch, lane, A, C, r0, r1);
         ln_step(A, C, r0, r1, xch, lane - 1, lane + 1);
         ln_put(xch, lane, A, C, r0, r1);
     }
     ln_chain<true>(xch, 7, lane == 0, [&](int i) { return 8 * i + 7; });
-    if (lane < 63) {
-        M2 nA, nC, a, c;
+    ln_get(xch, lane, A, C, r0, r1);
+    if ((lane & 7) != 7) {
+        M2 nA, nC;
         double n0, n1;
-        ln_get(xch, lane, a, c, r0, r1);
-        A = a;
-        C = c;
-        if ((lane & 7) != 7) {
-            ln_get(xch, lane < 8 ? 64 : g8 - 1, nA, nC, n0, n1);
-            A = mul(a, nA);
-            C = mul(a, nC);
-            r0 = __builtin_fma(a.a, n0, __builtin_fma(a.b, n1, r0));
-            r1 = __builtin_fma(a.c, n0, __builtin_fma(a.d, n1, r1));
-            ln_get(xch, lane >= 56 ? 65 : g8 + 7, nA, nC, n0, n1);
-            A = m2_ma(c, nA, A);
-            C = m2_ma(c, nC, C);
-            r0 = __builtin_fma(c.a, n0, __builtin_fma(c.b, n1, r0));
-            r1 = __builtin_fma(c.c, n0, __builtin_fma(c.d, n1, r1));
-        }
+        const M2 a = A, c = C;
+        ln_get(xch, lane < 8 ? 64 : g8 - 1, nA, nC, n0, n1);
+        A = mul(a, nA);
+        C = mul(a, nC);
+        r0 = __builtin_fma(a.a, n0, __builtin_fma(a.b, n1, r0));
+        r1 = __builtin_fma(a.c, n0, __builtin_fma(a.d, n1, r1));
+        ln_get(xch, lane >= 56 ? 65 : g8 + 7, nA, nC, n0, n1);
+        A = m2_ma(c, nA, A);
+        C = m2_ma(c, nC, C);
+        r0 = __builtin_fma(c.a, n0, __builtin_fma(c.b, n1, r0));
+        r1 = __builtin_fma(c.c, n0, __builtin_fma(c.d, n1, r1));
     }
 }
 
@@ -370,7 +369,8 @@ __device__ __forceinline__ void ln_own(double2 *xch, int lane, const double (&fa
 // FULL: all steps of the reduction (the stored-band solves, whose results are the answer at every
 // magnitude); else it ends when the lanes are decoupled, of an ordinary film after three of
 // the six steps at 16 positions per lane (x sweep of 8192^2 771 -> 705 us, x + y of 2048^2 111 -> 102). Lanes
-// of two or four cells decouple a step early at best, which the test costs: they take all steps (256^2 and 128^2).
+// of two or four cells decouple a step early at best, which the test costs (128^2 with four a lane, a call: 29.0 us with
+// all steps, 29.4 with the test): they take all steps.
 // Lines whose couplings grow past LN_GROWN are solved in order instead.
 template <int CPL, bool FULL = false>
 __device__ __forceinline__ void ln_pairs(double2 *xch, int lane, int nsub, double (&fa)[CPL],
@@ -394,7 +394,7 @@ __device__ __forceinline__ void ln_pairs(double2 *xch, int lane, int nsub, doubl
         if (!FULL && CPL > 4 && ln_decoupled(ma, mc, r0, r1)) break;
     }
     const bool again = __any(grown >= LN_GROWN);
-    if (again) {
+    if (__builtin_expect(again, 0)) {
         if (FULL) {
             A = A0;
             C = C0;
@@ -485,7 +485,7 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
         }
     }
     const bool again = __any(grown >= LN_GROWN);
-    if (again) {
+    if (__builtin_expect(again, 0)) {
         if (FULL) {
             A = A0;
             C = C0;
@@ -543,7 +543,7 @@ __device__ __forceinline__ void ln_pairs_mw(double2 *xch, double *bnd, int lane,
             ln_step(gA, gC, g0, g1, xch, max(i - d, 0), min(i + d, W - 1));
             gw = max(gw, max(ln_word(gA), ln_word(gC)));
         }
-        if (__any(gw >= LN_GROWN)) {
+        if (__builtin_expect(__any(gw >= LN_GROWN), 0)) {
             __asm__ volatile("" ::: "memory");
             outer();
             ln_put(xch, lane, gA, gC, g0, g1);
