@@ -128,7 +128,7 @@ tf_status tf_set_diagnostics(tf_grid *g, int mass_every_step);
  *                          the interface chain of each row, then the segment solves
  *                          (any nx);
  *   TF_XSWEEP_ROW          one kernel: each row is held by one to eight waves, which eliminate
- *                          sub-segments of 4 to 16 cells per lane and couple them by cyclic
+ *                          sub-segments of 2 to 16 cells per lane and couple them by cyclic
  *                          reduction across the lanes (4 <= nx <= 8192);
  *   TF_XSWEEP_AUTO         the choice of tf_xsweep_choice (the default at tf_create).
  * TF_EINVAL for an unknown variant or TF_XSWEEP_ROW with nx > 8192. tf_get_xsweep returns
@@ -311,7 +311,7 @@ tf_status tf_spectrum_maxima(const double *q, const double *s, int npoints, doub
  * transposed != 0 solves with the transposed matrices. variant: 0 = partitioned
  * (64-cell segments, interface chain), 1 = one lane per line (Thomas), 2 = block cyclic
  * reduction in LDS (one workgroup per line, n <= 2048), 3 = whole lines in one kernel
- * (sub-segments of 4 to 16 cells per lane coupled by cyclic reduction across the lanes,
+ * (sub-segments of 2 to 16 cells per lane coupled by cyclic reduction across the lanes,
  * 4 <= n <= 4096),
  * -1 = the autotuned choice. No pivoting: the matrices must be factorable without it.
  * Allocates and frees the scratch of the chosen variant (variants 2 and 3 need none);

@@ -35,10 +35,9 @@ constexpr int XR_MAX_NX = XR_CPL * 64 * XR_WAVES;
 __host__ __device__ constexpr int xr_lds(int waves) { return waves * 2400; }
 constexpr int XR_ROW4_MAX_NX = XR_CPL * 64 * 4;      // rows a 4-wave workgroup holds
 
-// Geometry of the whole-row sweep and of the whole-line solver (host and device).
-// A row of nx cells is held by S = ceil(nx / 16) lanes; lane s owns the 16 positions
-// q = nx - 16 (S - s) + k, k < 16 (lane 0 may start before the row). Staged rows number
-// their positions w = q + 16 S - nx = 16 s + k from lane 0's first one (w >= -2 covers the two
+// That unused geometry (host and device): a row of nx cells is held by S = ceil(nx / 16) lanes;
+// lane s owns the 16 positions q = nx - 16 (S - s) + k, k < 16 (lane 0 may start before the row).
+// Staged rows number their positions w = q + 16 S - nx = 16 s + k from lane 0's first one (w >= -2 covers the two
 // cells before it) and store them at xr_at(w): one padding double every 16, so that lanes
 // reading their cells in step (stride 17 doubles) hit distinct banks, and lane s's block
 // starts at 17 s + 3, so that a lane's accesses sit at constant offsets xr_off(t) of its
@@ -78,7 +77,6 @@ __host__ __device__ inline XRowGeom xrow_geom(int nx)
 // per lane (an even number, 2 to 16), W waves per line, right-aligned: slot s (64 wave + lane) owns the
 // positions w = CPL s + k, cell q = w - sh with sh = 64 W CPL - n < 64 CPL; positions before the
 // line (w < sh, in the first wave) hold copies of its first cells and are decoupled from it.
-constexpr int LN_MAXW = 8;                    // waves of the longest line
 // LDS offset of position w (-2 <= w <= 64 W CPL + 1) in a line's row: one padding double per lane,
 // so that lanes reading in step (stride CPL + 1) hit distinct banks.
 template <int CPL>
@@ -259,8 +257,8 @@ hipError_t launch_flux_divergence_f1(int nx, int ny, double ids, double ids2, co
 hipError_t launch_pass(int dir, bool solve, const PassParams &p, hipStream_t s);
 bool xrow_supported(int nx);
 // Whole-line sweeps (tf_line.hip): dir 0 does the whole y sweep, reading u (u_k) and in2 (b^n) and
-// writing out (w), with max|G| in res; dir 1 the whole x sweep like launch_xrow, one mass record per
-// wave. Geometry of a line of n cells (W = 0: not supported).
+// writing out (w), with max|G| in res; dir 1 the whole x sweep, reading u and in2 (w) and writing out (u_{k+1}) with
+// max|v/u_k| and the flags in res and one mass record per wave. Geometry of a line of n cells (W = 0: not supported).
 struct LineGeom {
     int cpl, W; // positions per lane, waves per line
 };
@@ -294,14 +292,14 @@ hipError_t launch_flux_divergence(int nx, int ny, double ids, double ids2, const
                                   const double *u, double alpha, double beta, const double *add,
                                   double *out, hipStream_t s);
 hipError_t launch_mass(const double *u, size_t n, double *partials, int nblocks, hipStream_t s);
-// Combine ntiles per-tile mass records {s, c, min, -} (PassParams::mass) in a fixed order into
-// out = {sum, min}.
 // The record of the iteration a batch ended with, combined over its copies, into host-visible memory
 // `out` (8 words): {stopped (ctl[0] == epoch), iteration, max|v/u_k|, max|G|, flags, max|v/u_k| of the
 // iteration before}. res: the slots (`slots` of them, iteration i in slot i % slots); last: the last
 // iteration enqueued, reported when the batch was not stopped.
 hipError_t launch_result(const unsigned long long *res, int slots, const unsigned long long *ctl,
                          unsigned long long epoch, unsigned long long last, unsigned long long *out, hipStream_t s);
+// Combine ntiles per-tile mass records {s, c, min, -} (PassParams::mass) in a fixed order into
+// out = {sum, min}.
 hipError_t launch_mass_tiles(const double *part, int ntiles, double *out, hipStream_t s);
 hipError_t launch_pass_ens(int dir, bool solve, int km, const EnsParams &e, hipStream_t s);
 // b^n of every active film at the first iteration of an attempt (items: (film, tx, ty) over the

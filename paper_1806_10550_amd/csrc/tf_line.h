@@ -369,8 +369,8 @@ __device__ __forceinline__ void ln_own(double2 *xch, int lane, const double (&fa
 // FULL: all steps of the reduction (the stored-band solves, whose results are the answer at every
 // magnitude); else it ends when the lanes are decoupled, of an ordinary film after three of
 // the six steps at 16 positions per lane (x sweep of 8192^2 771 -> 705 us, x + y of 2048^2 111 -> 102). Lanes
-// of two or four cells decouple a step early at best, which the test costs (128^2 with four a lane, a call: 29.0 us with
-// all steps, 29.4 with the test): they take all steps.
+// of two or four cells decouple a step early at best, which the test costs (lines of 256; 128^2 when it still had four a lane, a
+// call: 29.0 us with all steps, 29.4 with the test): they take all steps.
 // Lines whose couplings grow past LN_GROWN are solved in order instead.
 template <int CPL, bool FULL = false>
 __device__ __forceinline__ void ln_pairs(double2 *xch, int lane, int nsub, double (&fa)[CPL],

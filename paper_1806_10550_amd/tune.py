@@ -6,8 +6,10 @@
 
 Each shape is timed by tf_autotune for plain and for transposed solves (partitioned,
 Thomas with 64/128/256 lines per workgroup, block cyclic reduction for lengths <= 2048,
-whole lines for lengths <= 4096; lengths and batches by twos, so that every shape between
-them is within the distance at which an entry counts),
+whole lines for lengths <= 4096; lengths and batches by twos, so that every shape up to
+16384 lines is within the distance at which an entry counts, 0.7 in |ln length| + |ln batch|:
+at most 0.35 + 0.35. Between 16384 and 65536 lines only shapes near an entry are: 32768
+lines are 0.69 from either, so lengths off the list take the untuned rule there),
 and each x-sweep shape (row length, number of rows) by tf_autotune_xsweep (partitioned
 against whole-row), and appended as one JSON line to
 FILE (default: autotune_<arch>.jsonl beside this module). tf_autotune_load (or
