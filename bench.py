@@ -62,15 +62,26 @@ def sq_file(config="large8192"):
     return os.path.join(ROOT, "profiles", f"sq_{config}.json")
 
 
+def counter_record(path):
+    """The committed counter summary at `path`, or beside it that of the whole-line kernels (line_kernels_*; the
+    plain names hold the tile passes where a workload no longer runs them), whichever was taken on the kernel
+    sources in the tree; None when neither was."""
+    for p in (path, os.path.join(os.path.dirname(path), "line_kernels_" + os.path.basename(path))):
+        try:
+            with open(p) as f:
+                t = json.load(f)
+        except (OSError, ValueError):
+            continue
+        if t.get("kernel_hash") == kernel_hash():
+            return t
+    return None
+
+
 def fp64_flops_for(kernel, config="large8192"):
     """FP64 flops per launch of a kernel class from the committed SQ counter summary, or None
     when absent or taken on different kernel sources."""
-    try:
-        with open(sq_file(config)) as f:
-            t = json.load(f)
-    except (OSError, ValueError):
-        return None
-    if t.get("kernel_hash") != kernel_hash():
+    t = counter_record(sq_file(config))
+    if t is None:
         return None
     v = t.get("kernels", {}).get(kernel, {}).get("SQ_INSTS_VALU_FLOPS_FP64")
     # the counter adds each wave instruction's flops once (FMA 2, MUL/ADD 1): x 64 lanes
@@ -89,12 +100,8 @@ def copy_rate_gbs():
 def iteration_traffic(ncells, config="large8192"):
     """HBM bytes of one Newton iteration (the sweep launches) from the committed counter
     summary of the workload, or None when absent or taken on different kernel sources."""
-    try:
-        with open(traffic_file(config)) as f:
-            t = json.load(f)
-    except (OSError, ValueError):
-        return None
-    if t.get("kernel_hash") != kernel_hash():
+    t = counter_record(traffic_file(config))
+    if t is None:
         return None
     ks = t.get("kernels", {})
     parts = [["yline"] if "yline" in ks else ["relations_y", "solve_y", "chain"],
@@ -109,12 +116,8 @@ def iteration_traffic(ncells, config="large8192"):
 def traffic_for(kernel, ncells, config="large8192"):
     """HBM bytes per launch from the committed rocprofv3 counter summary, or None when
     absent or taken on different kernel sources."""
-    try:
-        with open(traffic_file(config)) as f:
-            t = json.load(f)
-    except (OSError, ValueError):
-        return None
-    if t.get("kernel_hash") != kernel_hash() or kernel not in t.get("kernels", {}):
+    t = counter_record(traffic_file(config))
+    if t is None or kernel not in t.get("kernels", {}):
         return None
     k = t["kernels"][kernel]
     return (k["fetch_kib"] + k["write_kib"]) * 1024.0 * t.get("copy_scale", 1.0)
