@@ -223,8 +223,9 @@ int tf_ensemble_xsweep(const tf_ensemble *e, int film);
 long long tf_ensemble_size(const tf_ensemble *e);
 /* host array of nfilms offsets (in doubles) of each film in the packed buffer */
 tf_status tf_ensemble_offsets(const tf_ensemble *e, long long *offsets);
-/* Borrow the packed state (device, tf_ensemble_size doubles); films holding h <= 0 or
- * NaN are marked TF_ENONPOS and never stepped. Resets every film's time and status. */
+/* Borrow the packed state (device, tf_ensemble_size doubles), after the work enqueued on
+ * the stream given to tf_ensemble_create; films holding h <= 0 or NaN are marked
+ * TF_ENONPOS and never stepped. Resets every film's time and status. */
 tf_status tf_ensemble_bind(tf_ensemble *e, double *packed_dev);
 /* Advance every film by nsteps accepted steps. dt_per_film (host, nfilms): dt to try in,
  * next dt out. status_per_film (host, nullable): TF_OK, TF_ENOCONV or TF_ENONPOS per film

@@ -114,6 +114,18 @@ void drop_graph(tf_ensemble *e)
     e->graph = nullptr;
 }
 
+// Orders the ensemble's own stream, which waits for no other by itself, after the work enqueued on the caller's.
+tf_status after_user(tf_ensemble *e)
+{
+    hipEvent_t ev;
+    TF_EHIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+    hipError_t err = hipEventRecord(ev, e->user);
+    if (err == hipSuccess) err = hipStreamWaitEvent(e->stream, ev, 0);
+    (void)hipEventDestroy(ev);
+    TF_EHIP(err);
+    return TF_OK;
+}
+
 tf_status ensure_graph(tf_ensemble *e)
 {
     if (e->exec) return TF_OK;
@@ -452,6 +464,10 @@ tf_status tf_ensemble_set_model_polymer(tf_ensemble *e, double C, double Cst, do
 tf_status tf_ensemble_bind(tf_ensemble *e, double *packed_dev)
 {
     if (e == nullptr) return efail(TF_EINVAL, "ensemble is NULL");
+    if (packed_dev != nullptr) {
+        const tf_status st = after_user(e); // the state may still be on its way
+        if (st != TF_OK) return st;
+    }
     e->buf0 = packed_dev;
     drop_graph(e);
     std::memset(e->h_state, 0, e->nfilms * sizeof(tf::FilmState));
@@ -468,12 +484,8 @@ tf_status tf_ensemble_step(tf_ensemble *e, int nsteps, double *dt_per_film, int 
     if (e->buf0 == nullptr) return efail(TF_ESTATE, "no packed state bound (tf_ensemble_bind)");
     for (int f = 0; f < e->nfilms; ++f)
         if (!(dt_per_film[f] > 0.0)) return efail(TF_EINVAL, "dt must be positive for every film");
-    // order after the caller's stream
-    hipEvent_t ev;
-    TF_EHIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-    TF_EHIP(hipEventRecord(ev, e->user));
-    TF_EHIP(hipStreamWaitEvent(e->stream, ev, 0));
-    (void)hipEventDestroy(ev);
+    tf_status st = after_user(e);
+    if (st != TF_OK) return st;
     // load the per-film dt, clear iteration totals
     TF_EHIP(hipMemcpyAsync(e->h_state, e->d_state, e->nfilms * sizeof(tf::FilmState), hipMemcpyDeviceToHost,
                            e->stream));
@@ -484,8 +496,7 @@ tf_status tf_ensemble_step(tf_ensemble *e, int nsteps, double *dt_per_film, int 
     }
     TF_EHIP(hipMemcpyAsync(e->d_state, e->h_state, e->nfilms * sizeof(tf::FilmState), hipMemcpyHostToDevice,
                            e->stream));
-    tf_status st = ensure_graph(e);
-    if (st != TF_OK) return st;
+    if ((st = ensure_graph(e)) != TF_OK) return st;
     for (int s = 0; s < nsteps; ++s) {
         TF_EHIP(tf::launch_ens_begin(e->d_state, e->nfilms, e->stream));
         int done = 0;

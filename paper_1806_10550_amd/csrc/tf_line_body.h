@@ -12,9 +12,9 @@
 //            32-byte row pieces. Reads u_k and b^n, writes w.
 //
 // What bounds them: at small sizes the latency of one wave's serial elimination, reduction and
-// memory round trips (x + y of 128^2: 7.6 + 8.8 us; 512^2: 10 + 12.7 us; the same sweeps by tile passes
-// and record tree took 25 + 35 and 23 + 35 us), at large ones two waves per SIMD that neither stream
-// nor compute all the time: of 699 us for the x sweep of 8192^2 (2.3 TB/s of the 24 B per cell, 41 % of
+// memory round trips (kernel trace, x + y of 128^2: 5.7 + 7.2 us; 512^2: 7.8 + 11 us; the same sweeps by tile passes
+// and record tree took 25 + 35 and 23 + 35 us between events), at large ones two waves per SIMD that neither stream
+// nor compute all the time: of 699 us for the x sweep of 8192^2 (kernel trace of 120 passes; 2.3 TB/s of the 24 B per cell, 41 % of
 // the vector issue slots), 432 remain when only loads, staging and stores are left, cells and elimination
 // add 109 and the reduced system 158 (8192 columns of 1000: 89 us against 141 us for the partitioned
 // passes). The waves of different lines share nothing, so the
