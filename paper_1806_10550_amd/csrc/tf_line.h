@@ -57,7 +57,8 @@ __device__ __forceinline__ void fold_right(Band &B, int pos) // pos: n-1 (0) or 
 // factors of every position stay in the arrays for the back-substitution. The pivots' reciprocals are good to the
 // last bits: with one refinement (rcp_pivot, as in the tiles) the lanes' pairs lose twice the tiles' digits on stiff
 // films (largest error of an iterate at dt = 50, 128^2: tiles 5.0e-13, one refinement 9.9e-13, two 3.4e-13; 512 x 300
-// at dt = 100: 5.1e-9, 5.3e-9, 1.5e-9) for less than 1 % of the time (newton 128^2 28.2 -> 28.3 us, 8192^2 1563 -> 1566).
+// at dt = 100: 5.1e-9, 5.3e-9, 1.5e-9) for up to 2 % of a sweep (y + x of 1637^2 NLC 127.3 -> 129.3 us, of 2048^2 109.5 -> 111.3; a call at 128^2
+// 28.2 -> 28.3, at 8192^2 1563 -> 1566).
 template <int CPL>
 __device__ __forceinline__ void xr_elim(int k, const Band &B, double rhs, double (&fa)[CPL], double (&fb)[CPL],
                                         double (&fz)[CPL], double (&fph)[CPL], double (&fps)[CPL])
